@@ -76,7 +76,8 @@ typedef struct {
   int32_t dw_accumulate; /* 0: dW is overwritten (default); 1: dW += gradient */
   /* Bound on the backward's logit-gradient buffers for one vocabulary chunk:
    * G, roundup(max_act, 256) * Vc * 2 bytes, for AGRL_BF16 (dW reads G
-   * transposed); G and G^T, twice that at 4 bytes per element, for AGRL_F32.
+   * transposed); twice that at 4 bytes per element for AGRL_F32 (G, and as much
+   * again for partial sums).
    * The backward walks the vocabulary in equal chunks of Vc columns (a
    * multiple of 256), as few as fit the bound; 0 selects 4 GiB.  The full
    * T x V logit gradient is held only when it fits the bound. */
@@ -84,9 +85,9 @@ typedef struct {
   /* Optional instrumentation: NULL, or a host array of 8 hipEvent_t.  The
    * library records events[2k] on `stream` just before and events[2k+1] just
    * after its matrix-core launch k: 0 forward logits, 1 backward logit
-   * recompute, 2 dW product, 3 dH product.  For AGRL_BF16 the dW and dH
-   * products run as one launch, bracketed by events 4/5, and events 6/7 are
-   * recorded back to back.  With several vocabulary chunks the last chunk's
+   * recompute, 2 dW product, 3 dH product.  The dW and dH products run as
+   * one launch, bracketed by events 4/5, and events 6/7 are recorded back
+   * to back.  With several vocabulary chunks the last chunk's
    * launches are the ones bracketed. */
   void* const* phase_events;
   /* KL penalty against a reference policy (App. A: the PPO and GRPO

@@ -1,29 +1,26 @@
-// Persistent "NT" GEMM on the gfx950 matrix cores: C[M, N] = A[M, K] * B[N, K]^T,
-// both operands K-contiguous (the bf16 kernel can also read A transposed from
-// its stage-tiled storage), fp32 accumulation, with a fused epilogue functor.
+// Persistent bf16 "NT" GEMM on the gfx950 matrix cores: C[M, N] = A[M, K] * B[N, K]^T,
+// both operands K-contiguous (A can also be read transposed from its stage-tiled
+// storage), fp32 accumulation, with a fused epilogue functor.
 //
 // Block tile 256 x 256, 4 waves in a 2 x 2 arrangement, each wave owning a
 // 128 x 128 sub-tile as 4 x 4 blocks of 32 x 32 MFMA accumulators
-// (v_mfma_f32_32x32x16_bf16 for bf16, v_mfma_f32_32x32x2_f32 for fp32), or, in
-// the bf16 kernel's 16 x 16 mode, as 8 x 8 blocks of v_mfma_f32_16x16x32_bf16
-// accumulators (half the accumulator traffic per flop: under the board power
-// limit the chip then holds a higher clock).
-// Each K stage moves 128 bytes of every tile row (64 bf16 or 32 fp32) from
-// global memory straight into LDS (no register staging), double-buffered (one
-// barrier per stage in the 32 x 32 loops; in the 16 x 16 loop a second one in
-// the middle of the stage, so that a stage's copies have until then to land).
-// The 16-byte chunk c of tile row r is stored at chunk
-// c ^ ((r >> 1) & 7): a 128-bit LDS read serves 16 lanes per pass from a
-// 256-byte window (two 128-byte rows), and this places the 16 rows such a pass
-// touches in 16 distinct bank groups.
+// (v_mfma_f32_32x32x16_bf16), or, in the 16 x 16 mode, as 8 x 8 blocks of
+// v_mfma_f32_16x16x32_bf16 accumulators (half the accumulator traffic per flop:
+// under the board power limit the chip then holds a higher clock).
+// Each K stage moves 128 bytes of every tile row from global memory straight into
+// LDS (no register staging), double-buffered (one barrier per stage in the 32 x 32
+// loop; in the 16 x 16 loop a second one in the middle of the stage, so that a
+// stage's copies have until then to land).  The 16-byte chunk c of tile row r is
+// stored at chunk c ^ ((r >> 1) & 7): a 128-bit LDS read serves 16 lanes per pass
+// from a 256-byte window (two 128-byte rows), and this places the 16 rows such a
+// pass touches in 16 distinct bank groups.
 //
 // The grid is persistent (about one workgroup per compute unit, since a block
 // holds 128 KiB of LDS).  The row counts M and N and the K extent may be read
 // from device memory, so a launch sized for an upper bound does only the work
-// the data needs without a host round trip.  Tile order: workgroups are dealt to
-// the 8 XCDs round-robin, so each full round of tiles is renumbered to give
-// every XCD a contiguous run, and runs are laid out group_m row-tiles deep so
-// the 32 workgroups of an XCD share A and B panels in its L2.
+// the data needs without a host round trip.  Workgroups are dealt to the 8 XCDs
+// round-robin, and the tile queues (below) keep an XCD's workgroups on a compact
+// block of tiles that shares its A and B panels in the XCD's L2.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -53,17 +50,6 @@ static_assert(EPI_GS + 128 * EPI_G_ROW <= EPI_META, "G staging below the per-row
 constexpr int BF16_KERNEL_LDS = EPI_STAGE_LDS > GEMM_LDS ? EPI_STAGE_LDS : GEMM_LDS;
 constexpr int GEMM_THREADS = 256;
 
-template <typename T>
-struct KStage;
-template <>
-struct KStage<__bf16> {
-  static constexpr int BK = 64;
-};
-template <>
-struct KStage<float> {
-  static constexpr int BK = 32;
-};
-
 struct GemmShape {
   const void* A;
   int64_t lda;             // elements
@@ -73,8 +59,8 @@ struct GemmShape {
   const int32_t* m_dev;    // rows of A read on the device
   int32_t N;               // rows of B (used when n_dev == nullptr)
   const int32_t* n_dev;    // rows of B read on the device
-  int32_t K;               // multiple of BK (used when k_dev == nullptr)
-  const int32_t* k_dev;    // K read on the device, rounded up to BK
+  int32_t K;               // multiple of 64 (used when k_dev == nullptr)
+  const int32_t* k_dev;    // K read on the device, rounded up to a stage
   int32_t group_m;         // row-tiles per tile-order group
   // bf16 kernel only.  a_tiled / b_tiled: the operand is stored stage-tiled,
   // 1 in row-block order (tiled_index; lda / ldb = its padded K extent, a
@@ -120,178 +106,11 @@ __device__ __forceinline__ int acc_col(int wn, int j, int lane) {
   return wn * 128 + j * 32 + (lane & 31);
 }
 
-__device__ __forceinline__ void map_tile(int t, int grid, int total, int tiles_m, int tiles_n,
-                                         int group_m, int& tm, int& tn) {
-  int L = t;
-  const int round = t / grid;
-  if ((grid & 7) == 0 && (round + 1) * grid <= total) {
-    const int b = t - round * grid;
-    L = round * grid + (b & 7) * (grid >> 3) + (b >> 3);
-  }
-  const int width = group_m * tiles_n;
-  const int grp = L / width;
-  const int first = grp * group_m;
-  const int gsz = min(tiles_m - first, group_m);
-  const int rem = L - grp * width;
-  tm = first + rem % gsz;
-  tn = rem / gsz;
-}
-
 // Swizzle of a tile row: the chunk offset XORed into its 16-byte chunks.
 __device__ __forceinline__ int row_swizzle(int r) { return (r >> 1) & 7; }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) void glb_void_t;
-
-// One K stage as direct global -> LDS copies (global_load_lds_dwordx4): each
-// instruction moves 8 tile rows (1 KiB) and writes LDS contiguously, lane i at
-// byte 16 * i.  Lane i therefore fetches logical chunk (i & 7) ^ row_swizzle(row)
-// of row i / 8, which lands it at the swizzled position.  Wave w copies rows
-// [64 w, 64 w + 64) of both the A and the B tile.  Rows past M or N are clamped
-// to the last valid row (their products are discarded by the epilogue).
-__device__ __forceinline__ void dma_stage(uint8_t* st, const uint8_t* A, int64_t lda_b, int m0,
-                                          int M, const uint8_t* B, int64_t ldb_b, int n0, int N,
-                                          int64_t k0_b, int wave, int lane) {
-  const int rl = lane >> 3;
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const int r0 = wave * 64 + b * 8;
-    const int c = (lane & 7) ^ row_swizzle(r0 + rl);
-    const int64_t ra = min(m0 + r0 + rl, M - 1);
-    const int64_t rb = min(n0 + r0 + rl, N - 1);
-    __builtin_amdgcn_global_load_lds((glb_void_t*)(A + ra * lda_b + k0_b + c * 16),
-                                     (lds_void_t*)(st + r0 * LDS_ROW), 16, 0, 0);
-    __builtin_amdgcn_global_load_lds((glb_void_t*)(B + rb * ldb_b + k0_b + c * 16),
-                                     (lds_void_t*)(st + GBM * LDS_ROW + r0 * LDS_ROW), 16, 0, 0);
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ void compute_stage(const uint8_t* st, f32x16 (&acc)[4][4], int wm,
-                                              int wn, int lane);
-
-// bf16: four 16-deep k slices per stage.  Each slice runs half of its 16
-// MFMAs, then issues the LDS reads of the next slice, then the other half, so
-// the wait before a slice only covers reads issued about 256 cycles earlier.
-// (sched_barrier pins that order; the scheduler would otherwise sink every
-// read next to its first use.)
-template <>
-__device__ __forceinline__ void compute_stage<__bf16>(const uint8_t* st, f32x16 (&acc)[4][4],
-                                                      int wm, int wn, int lane) {
-  const int sw = row_swizzle(lane & 31);   // fragment rows start at multiples of 32
-  const uint8_t* As = st + (wm * 128 + (lane & 31)) * LDS_ROW;
-  const uint8_t* Bs = st + GBM * LDS_ROW + (wn * 128 + (lane & 31)) * LDS_ROW;
-  bf16x8 a[2][4], b[2][4];
-  auto load = [&](int kk, bf16x8(&fa)[4], bf16x8(&fb)[4]) {
-    const int chunk = ((kk * 2 + (lane >> 5)) ^ sw) << 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) fa[i] = *(const bf16x8*)(As + i * 32 * LDS_ROW + chunk);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) fb[j] = *(const bf16x8*)(Bs + j * 32 * LDS_ROW + chunk);
-  };
-  auto mfma_rows = [&](int kk, int i0) {
-#pragma unroll
-    for (int i = i0; i < i0 + 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk & 1][i], b[kk & 1][j], acc[i][j],
-                                                            0, 0, 0);
-  };
-  load(0, a[0], b[0]);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    mfma_rows(kk, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (kk < 3) load(kk + 1, a[(kk + 1) & 1], b[(kk + 1) & 1]);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_rows(kk, 2);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-template <>
-__device__ __forceinline__ void compute_stage<float>(const uint8_t* st, f32x16 (&acc)[4][4],
-                                                     int wm, int wn, int lane) {
-  const int sw = row_swizzle(lane & 31);   // fragment rows start at multiples of 32
-  const uint8_t* As = st + (wm * 128 + (lane & 31)) * LDS_ROW;
-  const uint8_t* Bs = st + GBM * LDS_ROW + (wn * 128 + (lane & 31)) * LDS_ROW;
-#pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
-    const int c0 = ((kk * 4 + (lane >> 5) * 2) ^ sw) << 4;
-    const int c1 = ((kk * 4 + (lane >> 5) * 2 + 1) ^ sw) << 4;
-    f32x4 a[4][2], b[4][2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      a[i][0] = *(const f32x4*)(As + i * 32 * LDS_ROW + c0);
-      a[i][1] = *(const f32x4*)(As + i * 32 * LDS_ROW + c1);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      b[j][0] = *(const f32x4*)(Bs + j * 32 * LDS_ROW + c0);
-      b[j][1] = *(const f32x4*)(Bs + j * 32 * LDS_ROW + c1);
-    }
-    // Lane l holds k = (l/32)*8 + e of this 16-wide slice in element e; MFMA e
-    // pairs element e of both operands, so the 8 MFMAs cover all 16 k once.
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e >> 2][e & 3], b[j][e >> 2][e & 3],
-                                                           acc[i][j], 0, 0, 0);
-  }
-}
-
-template <typename T, class Epi>
-__global__ void __launch_bounds__(GEMM_THREADS)
-    __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_nt_kernel(GemmShape g, Epi epi) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[GEMM_LDS];
-  constexpr int BK = KStage<T>::BK;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int M = g.m_dev ? *g.m_dev : g.M;
-  const int N = g.n_dev ? *g.n_dev : g.N;
-  const int K = g.k_dev ? cdiv(*g.k_dev, BK) * BK : g.K;
-  if (M <= 0 || N <= 0) return;
-  const int tiles_m = cdiv(M, GBM), tiles_n = cdiv(N, GBN);
-  const int total = tiles_m * tiles_n;
-  const int nk = K / BK;
-  const uint8_t* A = (const uint8_t*)g.A;
-  const uint8_t* B = (const uint8_t*)g.B;
-  const int64_t lda_b = g.lda * (int64_t)sizeof(T), ldb_b = g.ldb * (int64_t)sizeof(T);
-
-  for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    int tm, tn;
-    map_tile(t, gridDim.x, total, tiles_m, tiles_n, g.group_m, tm, tn);
-    const int m0 = tm * GBM, n0 = tn * GBN;
-    f32x16 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    if (nk > 0) {
-      dma_stage(smem, A, lda_b, m0, M, B, ldb_b, n0, N, 0, wave, lane);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      for (int kt = 0; kt < nk; ++kt) {
-        const uint8_t* cur = smem + (kt & 1) * STAGE_BYTES;
-        if (kt + 1 < nk)
-          dma_stage(smem + ((kt + 1) & 1) * STAGE_BYTES, A, lda_b, m0, M, B, ldb_b, n0, N,
-                    (int64_t)(kt + 1) * BK * (int64_t)sizeof(T), wave, lane);
-        compute_stage<T>(cur, acc, wm, wn, lane);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-      }
-    }
-    epi(acc, m0, n0, tn, M, N, smem, wm, wn, lane, tid);
-    __syncthreads();
-  }
-}
 
 // ---------------------------------------------------------------------------
 // bf16 kernel.  Same tile, waves and swizzle as above, with a software
@@ -1052,161 +871,13 @@ __global__ void __launch_bounds__(GEMM_THREADS)
 // ---------------------------------------------------------------------------
 // Epilogues.  Each receives the finished accumulators of one tile.
 
-// Reductions over the 32 lanes of a half-wave (lanes l and l ^ 16, l ^ 8, ...):
-// four DPP steps inside each 16-lane row (xor 1, xor 2 by quad permutes, then
-// the half-row and row mirrors, which pair lanes whose partial results are
-// already uniform within their quad / half-row), then one swizzle across the
-// two rows.  Every lane of the half-wave ends with the result.
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
-                                                                0xF, 0xF, false));
-}
-__device__ __forceinline__ float swz_xor16(float v) {
-  // ds_swizzle bit mode, 32-lane groups: and 0x1F, or 0, xor 0x10
-  return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F));
-}
-__device__ __forceinline__ float half_wave_max(float v) {
-  v = fmaxf(v, dpp<0xB1>(v));    // quad_perm(1,0,3,2): lane ^ 1
-  v = fmaxf(v, dpp<0x4E>(v));    // quad_perm(2,3,0,1): lane ^ 2
-  v = fmaxf(v, dpp<0x141>(v));   // row_half_mirror: lane i <-> 7 - i within 8
-  v = fmaxf(v, dpp<0x140>(v));   // row_mirror: lane i <-> 15 - i within 16
-  return fmaxf(v, swz_xor16(v));
-}
-__device__ __forceinline__ float half_wave_sum(float v) {
-  v += dpp<0xB1>(v);
-  v += dpp<0x4E>(v);
-  v += dpp<0x141>(v);
-  v += dpp<0x140>(v);
-  return v + swz_xor16(v);
-}
-
-// Forward: per row of the tile, the max and the sum of exp(z - max) over the
-// tile's vocabulary columns (z = acc / temperature), plus the target logit.
-// A wave reduces its 128 columns for the 16 rows of one accumulator block at
-// a time: 16 independent reduction chains keep the DPP steps free of
-// read-after-write stalls.  With scale > 0, max z = scale * max acc and
-// exp(z - m) = exp2(acc * scale * log2(e) - max acc * scale * log2(e)).
-struct EpiLsePartial {
-  const int32_t* y;      // [rows] target id of each compacted row
-  f32x2* part;           // [tiles_n][ld_part] (max, sum exp) per row and vocabulary tile
-  int64_t ld_part;
-  float* zy;             // [rows] logit of the target token
-  float scale;           // 1 / temperature
-
-  template <bool FULL, int i>
-  __device__ __forceinline__ void block(const f32x16 (&acc)[4][4], int n0, int N,
-                                        const int* sy, f32x2* red, int m0, int wm, int wn,
-                                        int lane) const {
-    const float k1 = scale * 1.44269504088896341f;
-    bool ok[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) ok[j] = FULL || n0 + acc_col(wn, j, lane) < N;
-    float mx[16], sm[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float a[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) a[j] = ok[j] ? acc[i][j][r] : -INFINITY;
-      mx[r] = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) mx[r] = fmaxf(mx[r], dpp<0xB1>(mx[r]));
-#pragma unroll
-    for (int r = 0; r < 16; ++r) mx[r] = fmaxf(mx[r], dpp<0x4E>(mx[r]));
-#pragma unroll
-    for (int r = 0; r < 16; ++r) mx[r] = fmaxf(mx[r], dpp<0x141>(mx[r]));
-#pragma unroll
-    for (int r = 0; r < 16; ++r) mx[r] = fmaxf(mx[r], dpp<0x140>(mx[r]));
-#pragma unroll
-    for (int r = 0; r < 16; ++r) mx[r] = fmaxf(mx[r], swz_xor16(mx[r]));
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      // a half-row beyond the vocabulary has max -inf: its sum is 0
-      const float mk = FULL || mx[r] != -INFINITY ? -mx[r] * k1 : 0.0f;
-      float t = 0.0f;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float e = __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], k1, mk));
-        t += FULL || ok[j] ? e : 0.0f;
-      }
-      sm[r] = t;
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sm[r] += dpp<0xB1>(sm[r]);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sm[r] += dpp<0x4E>(sm[r]);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sm[r] += dpp<0x141>(sm[r]);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sm[r] += dpp<0x140>(sm[r]);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sm[r] += swz_xor16(sm[r]);
-    if ((lane & 31) == 0) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        red[wn * GBM + acc_row(wm, i, r, lane)] = f32x2{mx[r] * scale, sm[r]};
-    }
-    // target logit: the lane holding the row's target column (if it is one of
-    // this wave's columns) stores it
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int rl = acc_row(wm, i, r, lane);
-      const int tw = sy[rl] - wn * 128 - (lane & 31);    // 32 * block index if held here
-      float v = 0.0f;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v = tw == 32 * j ? acc[i][j][r] : v;
-      if ((unsigned)tw < 128u && (tw & 31) == 0) zy[m0 + rl] = v * scale;
-    }
-  }
-
-  // the block index must be a compile-time constant: a runtime index into
-  // the accumulator array would move it to scratch memory
-  template <bool FULL>
-  __device__ __forceinline__ void blocks(const f32x16 (&acc)[4][4], int n0, int N,
-                                         const int* sy, f32x2* red, int m0, int wm, int wn,
-                                         int lane) const {
-    block<FULL, 0>(acc, n0, N, sy, red, m0, wm, wn, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    block<FULL, 1>(acc, n0, N, sy, red, m0, wm, wn, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    block<FULL, 2>(acc, n0, N, sy, red, m0, wm, wn, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    block<FULL, 3>(acc, n0, N, sy, red, m0, wm, wn, lane);
-  }
-
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[4][4], int m0, int n0, int tn, int M,
-                                             int N, uint8_t* smem, int wm, int wn, int lane,
-                                             int tid) const {
-    int* sy = (int*)smem;
-    f32x2* red = (f32x2*)(smem + 1024);
-    // target column relative to the tile (-1: dead row; a target outside the
-    // tile matches no column)
-    sy[tid] = (m0 + tid < M) ? y[m0 + tid] - n0 : -1;
-    __syncthreads();
-    if (n0 + GBN <= N)
-      blocks<true>(acc, n0, N, sy, red, m0, wm, wn, lane);
-    else
-      blocks<false>(acc, n0, N, sy, red, m0, wm, wn, lane);
-    __syncthreads();
-    const int row = m0 + tid;
-    if (row < M) {
-      const f32x2 a = red[tid], b = red[GBM + tid];
-      const float m = fmaxf(a.x, b.x);
-      const float s = (a.y > 0.0f ? a.y * __expf(a.x - m) : 0.0f) +
-                      (b.y > 0.0f ? b.y * __expf(b.x - m) : 0.0f);
-      part[(int64_t)tn * ld_part + row] = f32x2{m, s};
-    }
-  }
-};
-
 // Forward partial log-sum-exp on a transposed tile: rows are vocabulary
 // entries (A = W), columns are compacted tokens (B = H_act).  The accumulator
 // layout gives every lane 64 rows of each of its 4 token columns, so the
 // reduction over the tile's vocabulary is lane-local except for one exchange
 // between lanes l and l ^ 32 (the two 4-row halves) and one merge of the two
-// row waves through LDS.  Same outputs as EpiLsePartial: (max, sum exp) per
-// token and vocabulary tile, and the target logit.
+// row waves through LDS: (max, sum exp) per token and vocabulary tile, and the
+// target logit.
 struct EpiLseCols {
   const int32_t* y;      // [tokens] target id of each compacted row
   f32x2* part;           // [tiles_v][ld_part] (max, sum exp) per token and vocabulary tile
@@ -1380,84 +1051,23 @@ struct EpiLseCols {
   }
 };
 
-template <typename T>
-__device__ __forceinline__ T to_store(float v);
-template <>
-__device__ __forceinline__ __bf16 to_store<__bf16>(float v) {
-  return __builtin_bit_cast(__bf16, f32_to_bf16_bits(v));
-}
-template <>
-__device__ __forceinline__ float to_store<float>(float v) {
-  return v;
-}
-
-// Backward recompute: G = gs_n * (1[v == y_n] - exp(z - lse_n)), rounded to T.
-// fp32 writes it as G[row][col] and transposed as Gt[col][row]; bf16 writes G
-// only (stage-tiled).  Rows >= M and columns >= N are written as 0 (they pad
-// the K extent of the next products).
-template <typename T>
-struct LogitGradArgs {
+// Backward recompute: G = gs_n * (1[v == y_n] - exp(z - lse_n)), rounded to bf16.
+// Rows >= M and columns >= N are written as 0 (they pad the K extent of the next
+// products).  The tile is finished in two passes of 128 rows (accumulator blocks
+// i = 2h and 2h + 1 of both wave rows).  A pass stages its G rows row-major in LDS,
+// then they leave as full 128-byte lines of G's column-block stage-tiled layout (dW
+// reads the same G transposed, so no transposed copy is written).  The exponent is
+// evaluated in base 2 with the scale folded in:
+// exp(z - lse) = exp2(acc * scale * log2(e) - lse * log2(e)).
+struct EpiLogitGrad {
   const int32_t* y;
   const float* lse;
   const float* gs;       // dL/dlogp / temperature, per compacted row
-  T* G;                  // fp32: row-major [rows][ldg]; bf16: column-block stage-tiled
-  int64_t ldg;           // fp32: row pitch; bf16: G's padded row count
-  T* Gt;                 // fp32 only: G transposed, row-major [cols][ldgt]
-  int64_t ldgt;
+  __bf16* G;             // column-block stage-tiled
+  int64_t ldg;           // G's padded row count
   float scale;
   int32_t col0;          // vocabulary index of this chunk's column 0
-};
 
-template <typename T>
-struct EpiLogitGrad;
-
-// fp32 (simple kernel): direct stores from the accumulator layout.
-template <>
-struct EpiLogitGrad<float> : LogitGradArgs<float> {
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[4][4], int m0, int n0, int tn, int M,
-                                             int N, uint8_t* smem, int wm, int wn, int lane,
-                                             int tid) const {
-    int* sy = (int*)smem;
-    float* sl = (float*)(smem + 1024);
-    float* sg = (float*)(smem + 2048);
-    const bool live = m0 + tid < M;
-    sy[tid] = live ? y[m0 + tid] - col0 : -1;
-    sl[tid] = live ? lse[m0 + tid] : INFINITY;
-    sg[tid] = live ? gs[m0 + tid] : 0.0f;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int c = n0 + acc_col(wn, j, lane);
-          float vals[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int rl = acc_row(wm, i, r4 * 4 + q, lane);
-            const float p = __expf(acc[i][j][r4 * 4 + q] * scale - sl[rl]);
-            const float g = sg[rl] * ((c == sy[rl] ? 1.0f : 0.0f) - p);
-            vals[q] = c < N ? g : 0.0f;
-            G[(int64_t)(m0 + rl) * ldg + c] = vals[q];
-          }
-          const int rl0 = acc_row(wm, i, r4 * 4, lane);
-          *(f32x4*)(Gt + (int64_t)c * ldgt + m0 + rl0) = f32x4{vals[0], vals[1], vals[2], vals[3]};
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
-};
-
-// bf16 (pipelined kernel).  The tile is finished in two passes of 128 rows
-// (accumulator blocks i = 2h and 2h + 1 of both wave rows).  A pass stages its
-// G rows row-major in LDS, then they leave as full 128-byte lines of G's
-// column-block stage-tiled layout (dW reads the same G transposed, so no
-// transposed copy is written).  The exponent is evaluated in base 2 with the
-// scale folded in: exp(z - lse) = exp2(acc * scale * log2(e) - lse * log2(e)).
-template <>
-struct EpiLogitGrad<__bf16> : LogitGradArgs<__bf16> {
   template <bool FULL, int h>
   __device__ __forceinline__ void stage_pass(const f32x16 (&acc)[4][4], int n0, int N,
                                              uint8_t* smem, int wm, int wn, int lane) const {
@@ -1629,33 +1239,6 @@ struct EpiStore {
   int64_t ldo;
   const int32_t* row_map;   // nullable: output row of each tile row
   int32_t accumulate;
-
-  // simple kernel: direct stores from the accumulator layout
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[4][4], int m0, int n0, int tn, int M,
-                                             int N, uint8_t* smem, int wm, int wn, int lane,
-                                             int tid) const {
-    int* sr = (int*)smem;
-    if (row_map) {
-      sr[tid] = (m0 + tid < M) ? row_map[m0 + tid] : 0;
-      __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rl = acc_row(wm, i, r, lane);
-        if (m0 + rl < M) {
-          const int64_t orow = row_map ? (int64_t)sr[rl] : (int64_t)(m0 + rl);
-          float* dst = out + orow * ldo;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int c = n0 + acc_col(wn, j, lane);
-            if (c < N) dst[c] = accumulate ? dst[c] + acc[i][j][r] : acc[i][j][r];
-          }
-        }
-        if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-      }
-  }
 
   // 16 x 16 accumulator layout.  Pass h stages blocks i = 4 h .. 4 h + 3 of both
   // wave rows (the same tile rows as the 32 x 32 layout's pass h), each block

@@ -16,6 +16,7 @@
 #include "../../include/agrl.h"
 #include "common.hpp"
 #include "gemm.hpp"
+#include "gemm_f32.hpp"
 
 namespace agrl {
 namespace {
@@ -222,49 +223,18 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint8_t* __restr
   }
 }
 
-// dst[c][r] = src[r][c]; rows in [n_rows, n_rows_pad) are written as 0.
-// n_rows comes from ctrl[0] (rounded up to 256 for the padded extent) when
-// ctrl is given.  64 x 64 element tiles through LDS.  With `tiled`, dst is
-// stage-tiled (tiled_index, K = r padded to ld_dst) instead of row-major.
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ src, int64_t ld_src,
-                                                        T* dst, int64_t ld_dst, int64_t n_rows,
-                                                        int64_t n_rows_pad, int64_t n_cols,
-                                                        const int32_t* ctrl, int32_t tiled) {
-  __shared__ T tile[64][65];
-  if (ctrl) {
-    n_rows = ctrl[0];
-    n_rows_pad = round_up(n_rows, kRowPad);
-  }
-  const int64_t r0 = (int64_t)blockIdx.x * 64, c0 = (int64_t)blockIdx.y * 64;
-  if (r0 >= n_rows_pad) return;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int k = 0; k < 16; ++k) {
-    const int rr = ty + 4 * k;
-    const int64_t r = r0 + rr, c = c0 + tx;
-    T v = T(0);
-    if (r < n_rows && c < n_cols) v = src[r * ld_src + c];
-    tile[rr][tx] = v;
-  }
-  __syncthreads();
-  for (int k = 0; k < 16; ++k) {
-    const int cc = ty + 4 * k;
-    const int64_t c = c0 + cc, r = r0 + tx;
-    if (c < n_cols && r < n_rows_pad)
-      dst[tiled ? tiled_index(c, r, ld_dst) : c * ld_dst + r] = tile[tx][cc];
-  }
-}
-
-// bf16 (2-byte) variant of transpose_kernel with 16-byte global accesses: each
-// 64 x 64 tile is read as 8-element row chunks, written to LDS transposed
-// (66-element rows: the 16-bit stores of a wave hit distinct banks), and read
-// back as 8-element chunks of the output rows.  Same arguments and padding
-// rules; d (the source row length) is a multiple of 64.
+// dst = src^T, stage-tiled (tiled_index, K = r padded to ld_dst); rows r in
+// [n_rows, n_rows_pad) are written as 0.  n_rows comes from ctrl[0] (rounded up to
+// 256 for the padded extent) when ctrl is given.  bf16 as raw bits, 16-byte global
+// accesses: each 64 x 64 tile is read as 8-element row chunks, written to LDS
+// transposed (66-element rows: the 16-bit stores of a wave hit distinct banks), and
+// read back as 8-element chunks of the output rows; d (the source row length) is a
+// multiple of 64.
 __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __restrict__ src,
                                                           int64_t ld_src, uint16_t* dst,
                                                           int64_t ld_dst, int64_t n_rows,
                                                           int64_t n_rows_pad, int64_t n_cols,
-                                                          const int32_t* ctrl, int32_t tiled) {
+                                                          const int32_t* ctrl) {
   constexpr int P = 66;
   __shared__ uint16_t tile_t[64 * P];
   if (ctrl) {
@@ -293,7 +263,7 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
     const u32x4 v = {t32[0], t32[1], t32[2], t32[3]};
     const int64_t oc = c0 + c, orr = r0 + 8 * r8;
     if (oc < n_cols && orr < n_rows_pad)
-      *(u32x4*)(dst + (tiled ? tiled_index(oc, orr, ld_dst) : oc * ld_dst + orr)) = v;
+      *(u32x4*)(dst + tiled_index(oc, orr, ld_dst)) = v;
   }
 }
 
@@ -454,7 +424,8 @@ struct Layout {
   int32_t d, V, esize, nblk, tiles_v, merge_blocks;
   size_t ctrl, blk_cnt, blk_off, idx, y_act, adv_act, old_act, ref_act, w_act, lse_act, gs_act,
       zy, blk_sum,
-      blk_clip, H_act, part, Ht, Wt, G, Gt, fwd_total, total;
+      blk_clip, H_act, part, Ht, Wt, G, ph, pw, fwd_total, total;
+  int32_t ph_max, pw_max;      // fp32: parts the gradient products' partial buffers hold
 };
 
 constexpr int64_t kDefaultChunkBytes = (int64_t)4 << 30;
@@ -474,8 +445,8 @@ bool make_layout(int64_t T, int64_t max_act, int32_t d, int32_t V, int32_t dtype
   L->tiles_v = (int32_t)(L->V_pad / GBN);
   L->merge_blocks = (int32_t)(L->A_pad / kMergeRows);
   // vocabulary chunk of the backward: the widest multiple of 256 whose logit
-  // gradient buffers (bf16: G, read transposed by dW; fp32: G and G^T) fit the
-  // budget, then evened out over the chunks this needs
+  // gradient buffers (bf16: G; fp32: twice G, the second half serving the gradient
+  // products' parts) fit the budget, then evened out over the chunks this needs
   const int64_t budget = o.g_chunk_bytes > 0 ? o.g_chunk_bytes : kDefaultChunkBytes;
   const int64_t g_copies = dtype == AGRL_BF16 ? 1 : 2;
   int64_t vc_max = budget / (g_copies * L->A_pad * L->esize) / kRowPad * kRowPad;
@@ -515,7 +486,22 @@ bool make_layout(int64_t T, int64_t max_act, int32_t d, int32_t V, int32_t dtype
   L->Ht = take(d_pad * A * L->esize);
   L->Wt = take(d_pad * L->V_pad * L->esize);
   L->G = take(A * (size_t)L->Vc * L->esize);
-  L->Gt = dtype == AGRL_BF16 ? L->G : take((size_t)L->Vc * A * L->esize);
+  if (dtype == AGRL_F32) {
+    // The fp32 products read H_act and W as they lie: no H^T and W^T.  G, then half
+    // of the rest for the parts of each gradient product (G is budgeted twice)
+    take((size_t)L->Vc * A * L->esize);
+    const size_t g_bytes = A * (size_t)L->Vc * 4;
+    L->G = shared_at;
+    L->ph = shared_at + g_bytes;
+    const size_t half = (off - L->ph) / 2 / 256 * 256;
+    L->pw = L->ph + half;
+    auto parts = [&](size_t rows) {
+      const size_t n = half / (rows * d * 4);
+      return (int32_t)(n < 1 ? 1 : n > 32 ? 32 : n);
+    };
+    L->ph_max = parts(A);
+    L->pw_max = parts((size_t)L->Vc);
+  }
   if (fwd_end > off) off = fwd_end;
   L->total = off;
   return true;
@@ -591,65 +577,66 @@ __global__ void zero_queue_kernel(int32_t* q) {
   if (threadIdx.x < 16) q[threadIdx.x] = 0;
 }
 
-// Launch n (1 or 2) independent products.  bf16: one persistent launch of the
-// pipelined kernel with its tile queues reset first; fp32: one simple launch
-// per product.  The phase's events bracket the whole launch (a second phase
+void record(const agrl_options& o, int event, hipStream_t s) {
+  if (o.phase_events) hipEventRecord(((hipEvent_t*)o.phase_events)[event], s);
+}
+
+// Launch n (1 or 2) independent bf16 products: one persistent launch with its tile
+// queues reset first.  The phase's events bracket the whole launch (a second phase
 // slot, when given, is recorded empty).
-template <typename T, class Epi>
+template <class Epi>
 void launch_gemm(const GemmShape* g, const Epi* e, int n, int max_tiles, int32_t* queue,
                  const agrl_options& o, Phase ph, int ph2, hipStream_t s) {
   int grid = device_cu_count();
   if (max_tiles < grid) grid = max_tiles < 1 ? 1 : max_tiles;
-  hipEvent_t* ev = (hipEvent_t*)o.phase_events;
-  if constexpr (std::is_same<T, __bf16>::value) {
-    GemmBatch<Epi> b;
-    for (int i = 0; i < 2; ++i) {
-      b.g[i] = g[i < n ? i : 0];
-      b.e[i] = e[i < n ? i : 0];
-    }
-    b.n = n;
-    b.queue = queue;
-    // every K a whole number of stage pairs (device-read ones are rounded up
-    // in the kernel, their operands being zero-padded to 256)
-    bool even = true, atr = false;
-    for (int i = 0; i < n; ++i) {
-      even = even && (g[i].k_dev != nullptr || g[i].K % (2 * KStage<T>::BK) == 0);
-      atr = atr || g[i].a_trans;
-    }
-    hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(64), 0, s, queue);
-    if (ev) hipEventRecord(ev[2 * ph], s);
-    // The bf16 store launch is the backward's dH + dW: its operands are
-    // stage-tiled, dW reads G transposed, and both K extents are whole stage
-    // pairs (the vocabulary chunk rounded up to 128, the device-read token count
-    // rounded up in the kernel), so it always runs the 16 x 16 loop.
-    if constexpr (std::is_same<Epi, EpiStore>::value) {
-      (void)atr;
-      (void)even;
-      hipLaunchKernelGGL((gemm_bf16_kernel<Epi, true, true, true>), dim3(grid), dim3(GEMM_THREADS),
-                         0, s, b);
-    } else {
-      if (even)
-        hipLaunchKernelGGL((gemm_bf16_kernel<Epi, true, false, true>), dim3(grid),
-                           dim3(GEMM_THREADS), 0, s, b);
-      else
-        hipLaunchKernelGGL((gemm_bf16_kernel<Epi, false, false>), dim3(grid), dim3(GEMM_THREADS),
-                           0, s, b);
-    }
-    if (ev) hipEventRecord(ev[2 * ph + 1], s);
-    if (ev && ph2 >= 0) {
-      hipEventRecord(ev[2 * ph2], s);
-      hipEventRecord(ev[2 * ph2 + 1], s);
-    }
-  } else {
-    for (int i = 0; i < n; ++i) {
-      // with two problems the first is dH (slot ph2) and the second dW (slot ph)
-      const int p = (n == 2 && ph2 >= 0) ? (i == 0 ? ph2 : ph) : ph;
-      if (ev) hipEventRecord(ev[2 * p], s);
-      hipLaunchKernelGGL((gemm_nt_kernel<T, Epi>), dim3(grid), dim3(GEMM_THREADS), 0, s, g[i],
-                         e[i]);
-      if (ev) hipEventRecord(ev[2 * p + 1], s);
-    }
+  GemmBatch<Epi> b;
+  for (int i = 0; i < 2; ++i) {
+    b.g[i] = g[i < n ? i : 0];
+    b.e[i] = e[i < n ? i : 0];
   }
+  b.n = n;
+  b.queue = queue;
+  hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(64), 0, s, queue);
+  record(o, 2 * ph, s);
+  // The bf16 store launch is the backward's dH + dW: its operands are
+  // stage-tiled, dW reads G transposed, and both K extents are whole stage
+  // pairs (the vocabulary chunk rounded up to 128, the device-read token count
+  // rounded up in the kernel), so it always runs the 16 x 16 loop.
+  if constexpr (std::is_same<Epi, EpiStore>::value) {
+    hipLaunchKernelGGL((gemm_bf16_kernel<Epi, true, true, true>), dim3(grid), dim3(GEMM_THREADS),
+                       0, s, b);
+  } else {
+    // K (the hidden size) a whole number of stage pairs
+    if (g[0].K % (2 * bf16k::SK) == 0)
+      hipLaunchKernelGGL((gemm_bf16_kernel<Epi, true, false, true>), dim3(grid),
+                         dim3(GEMM_THREADS), 0, s, b);
+    else
+      hipLaunchKernelGGL((gemm_bf16_kernel<Epi, false, false>), dim3(grid), dim3(GEMM_THREADS),
+                         0, s, b);
+  }
+  record(o, 2 * ph + 1, s);
+  if (ph2 >= 0) {
+    record(o, 2 * ph2, s);
+    record(o, 2 * ph2 + 1, s);
+  }
+}
+
+// fp32 logits: forward partials, or G of a vocabulary chunk.  64 tokens per tile read
+// W half as often; 32 give twice the tiles, for launches whose wide tiles would not
+// fill the two workgroups that fit a compute unit.  Either side of the line is flat:
+// 38.0 + 42.5 us wide against 41.0 + 36.5 us at V = 4096, d = 256, 1519 tokens (384 wide
+// tiles), 419 + 425 against 430 + 418 us at V = 16391, d = 1024, 1333 tokens.
+template <bool GRAD>
+void launch_logits_f32(const f32k::LogitsArgs& g, int64_t rows, hipStream_t s) {
+  const int tiles_m = cdiv(g.nv, 256);
+  const int64_t wide = cdiv<int64_t>(rows, 64) * tiles_m;
+  if (wide >= 2 * device_cu_count())
+    hipLaunchKernelGGL((f32k::f32_logits_kernel<2, GRAD>), dim3((unsigned)round_up(wide, 8)),
+                       dim3(f32k::THREADS), 0, s, g);
+  else
+    hipLaunchKernelGGL((f32k::f32_logits_kernel<1, GRAD>),
+                       dim3((unsigned)round_up(cdiv<int64_t>(rows, 32) * tiles_m, 8)),
+                       dim3(f32k::THREADS), 0, s, g);
 }
 
 int compact(const Common& c, const Layout& L, uint8_t* ws, const uint8_t* mask,
@@ -705,97 +692,134 @@ int compact(const Common& c, const Layout& L, uint8_t* ws, const uint8_t* mask,
   return AGRL_OK;
 }
 
-template <typename T>
-void fwd_gemm(const Common& c, const Layout& L, uint8_t* ws, const void* W, hipStream_t s) {
-  const int32_t* n_act = (const int32_t*)(ws + L.ctrl);
+void fwd_gemm_bf16(const Common& c, const Layout& L, uint8_t* ws, const void* W, hipStream_t s) {
   const int max_tiles = (int)(L.A_pad / GBM) * L.tiles_v;
   GemmShape g = {};
   g.K = c.d;
   g.group_m = 8;
-  if constexpr (std::is_same<T, __bf16>::value) {
-    // transposed tile (rows: vocabulary, columns: action tokens), so that the
-    // log-sum-exp over the vocabulary reduces mostly inside each lane
-    g.A = W;
-    g.lda = c.d;
-    g.M = c.V;
-    g.B = ws + L.H_act;
-    g.ldb = c.d;
-    g.N = (int32_t)L.A_pad;
-    g.n_dev = n_act;
-    EpiLseCols e;
-    e.y = (const int32_t*)(ws + L.y_act);
-    e.part = (f32x2*)(ws + L.part);
-    e.ld_part = L.A_pad;
-    e.zy = (float*)(ws + L.zy);
-    e.scale = c.inv_temp;
-    launch_gemm<T>(&g, &e, 1, max_tiles, (int32_t*)(ws + L.ctrl + 64), c.o, PH_FWD, -1, s);
-  } else {
-    g.A = ws + L.H_act;
-    g.lda = c.d;
-    g.B = W;
-    g.ldb = c.d;
-    g.m_dev = n_act;
-    g.N = c.V;
-    EpiLsePartial e;
-    e.y = (const int32_t*)(ws + L.y_act);
-    e.part = (f32x2*)(ws + L.part);
-    e.ld_part = L.A_pad;
-    e.zy = (float*)(ws + L.zy);
-    e.scale = c.inv_temp;
-    launch_gemm<T>(&g, &e, 1, max_tiles, (int32_t*)(ws + L.ctrl + 64), c.o, PH_FWD, -1, s);
+  // transposed tile (rows: vocabulary, columns: action tokens), so that the
+  // log-sum-exp over the vocabulary reduces mostly inside each lane
+  g.A = W;
+  g.lda = c.d;
+  g.M = c.V;
+  g.B = ws + L.H_act;
+  g.ldb = c.d;
+  g.N = (int32_t)L.A_pad;
+  g.n_dev = (const int32_t*)(ws + L.ctrl);
+  EpiLseCols e;
+  e.y = (const int32_t*)(ws + L.y_act);
+  e.part = (f32x2*)(ws + L.part);
+  e.ld_part = L.A_pad;
+  e.zy = (float*)(ws + L.zy);
+  e.scale = c.inv_temp;
+  launch_gemm(&g, &e, 1, max_tiles, (int32_t*)(ws + L.ctrl + 64), c.o, PH_FWD, -1, s);
+}
+
+f32k::LogitsArgs logits_args_f32(const Common& c, const Layout& L, uint8_t* ws, const void* W,
+                                 int64_t v0, int32_t nv) {
+  f32k::LogitsArgs g = {};
+  g.W = (const float*)W + v0 * c.d;
+  g.H = (const float*)(ws + L.H_act);
+  g.K = c.d;
+  g.nv = nv;
+  g.n_act = (const int32_t*)(ws + L.ctrl);
+  g.y = (const int32_t*)(ws + L.y_act);
+  g.scale = c.inv_temp;
+  g.col0 = (int32_t)v0;
+  return g;
+}
+
+void fwd_gemm_f32(const Common& c, const Layout& L, uint8_t* ws, const void* W, hipStream_t s) {
+  f32k::LogitsArgs g = logits_args_f32(c, L, ws, W, 0, c.V);
+  g.part = (f32x2*)(ws + L.part);
+  g.ld_part = L.A_pad;
+  g.zy = (float*)(ws + L.zy);
+  record(c.o, 2 * PH_FWD, s);
+  launch_logits_f32<false>(g, L.A_pad, s);
+  record(c.o, 2 * PH_FWD + 1, s);
+}
+
+void fwd_gemm(const Common& c, const Layout& L, uint8_t* ws, const void* W, hipStream_t s) {
+  if (c.dtype == AGRL_BF16)
+    fwd_gemm_bf16(c, L, ws, W, s);
+  else
+    fwd_gemm_f32(c, L, ws, W, s);
+}
+
+void bwd_gemms_f32(const Common& c, const Layout& L, uint8_t* ws, const void* W, float* dH,
+                   float* dW, hipStream_t s) {
+  const int cus = device_cu_count();
+  for (int64_t v0 = 0; v0 < c.V; v0 += L.Vc) {
+    const int32_t nv = (int32_t)((c.V - v0) < L.Vc ? (c.V - v0) : L.Vc);
+    f32k::LogitsArgs g = logits_args_f32(c, L, ws, W, v0, nv);
+    g.lse = (const float*)(ws + L.lse_act);
+    g.gs = (const float*)(ws + L.gs_act);
+    g.G = (float*)(ws + L.G);
+    g.ldg = L.Vc;
+    record(c.o, 2 * PH_RECOMPUTE, s);
+    launch_logits_f32<true>(g, L.A_pad, s);
+    record(c.o, 2 * PH_RECOMPUTE + 1, s);
+    f32k::GradArgs a;
+    a.G = g.G;
+    a.ldg = L.Vc;
+    a.W = g.W;
+    a.H = g.H;
+    a.d = c.d;
+    a.nv = nv;
+    a.n_act = g.n_act;
+    a.dH = dH;
+    a.idx = (const int32_t*)(ws + L.idx);
+    a.dh_add = v0 > 0;
+    a.dW = dW + v0 * c.d;
+    a.dw_add = c.o.dw_accumulate;
+    a.ph = (float*)(ws + L.ph);
+    a.ph_rows = L.A_pad;
+    a.ph_max = L.ph_max;
+    a.pw = (float*)(ws + L.pw);
+    a.pw_max = L.pw_max;
+    a.cus = cus;
+    record(c.o, 2 * PH_DW, s);
+    constexpr int BI = 1, BJ = 1, TM = 64 * BI, TN = 64 * BJ;   // see f32_grad_kernel
+    hipLaunchKernelGGL((f32k::f32_grad_kernel<BI, BJ>),
+                       dim3(f32k::max_blocks((int)L.A_pad, nv, c.d, TM, TN, cus)),
+                       dim3(f32k::THREADS), 0, s, a);
+    record(c.o, 2 * PH_DW + 1, s);
+    record(c.o, 2 * PH_DH, s);
+    record(c.o, 2 * PH_DH + 1, s);
+    if (L.ph_max > 1 || L.pw_max > 1)
+      hipLaunchKernelGGL(f32k::f32_reduce_kernel, dim3(4 * cus), dim3(f32k::THREADS), 0, s, a, TM,
+                         TN);
   }
 }
 
-template <typename T>
-struct Storage {
-  typedef uint16_t type;   // bf16 moved as raw bits
-};
-template <>
-struct Storage<float> {
-  typedef float type;
-};
-
-template <typename T>
-void bwd_gemms(const Common& c, const Layout& L, uint8_t* ws, const void* W, float* dH, float* dW,
-               hipStream_t s) {
-  typedef typename Storage<T>::type S;
+void bwd_gemms_bf16(const Common& c, const Layout& L, uint8_t* ws, const void* W, float* dH,
+                    float* dW, hipStream_t s) {
   const int32_t* ctrl = (const int32_t*)(ws + L.ctrl);
-  T* Ht = (T*)(ws + L.Ht);
-  T* Wt = (T*)(ws + L.Wt);
-  T* G = (T*)(ws + L.G);
-  T* Gt = (T*)(ws + L.Gt);   // fp32 only
+  __bf16* Ht = (__bf16*)(ws + L.Ht);
+  __bf16* Wt = (__bf16*)(ws + L.Wt);
+  __bf16* G = (__bf16*)(ws + L.G);
   // H_act^T [d][A_pad] (zero beyond the action rows) and W^T [d][V_pad] (zero
-  // beyond V); for bf16 both, and G, are stage-tiled: every stage of the two
-  // products below is a contiguous 32 KiB block per operand tile (8 KiB in each
-  // of four blocks for dW's transposed read of G)
-  constexpr int32_t tiled = std::is_same<T, __bf16>::value ? 1 : 0;
+  // beyond V); both, and G, are stage-tiled: every stage of the two products
+  // below is a contiguous 32 KiB block per operand tile (8 KiB in each of four
+  // blocks for dW's transposed read of G)
   const dim3 gh((unsigned)(L.A_pad / 64), (unsigned)cdiv(c.d, 64));
   const dim3 gw((unsigned)(L.V_pad / 64), (unsigned)cdiv(c.d, 64));
-  if constexpr (sizeof(S) == 2) {
-    hipLaunchKernelGGL(transpose16_kernel, gh, dim3(256), 0, s, (const uint16_t*)(ws + L.H_act),
-                       (int64_t)c.d, (uint16_t*)Ht, L.A_pad, (int64_t)0, (int64_t)0,
-                       (int64_t)c.d, ctrl, tiled);
-    hipLaunchKernelGGL(transpose16_kernel, gw, dim3(256), 0, s, (const uint16_t*)W, (int64_t)c.d,
-                       (uint16_t*)Wt, L.V_pad, (int64_t)c.V, L.V_pad, (int64_t)c.d,
-                       (const int32_t*)nullptr, tiled);
-  } else {
-    hipLaunchKernelGGL((transpose_kernel<S>), gh, dim3(256), 0, s, (const S*)(ws + L.H_act),
-                       (int64_t)c.d, (S*)Ht, L.A_pad, (int64_t)0, (int64_t)0, (int64_t)c.d, ctrl,
-                       tiled);
-    hipLaunchKernelGGL((transpose_kernel<S>), gw, dim3(256), 0, s, (const S*)W, (int64_t)c.d,
-                       (S*)Wt, L.V_pad, (int64_t)c.V, L.V_pad, (int64_t)c.d,
-                       (const int32_t*)nullptr, tiled);
-  }
+  hipLaunchKernelGGL(transpose16_kernel, gh, dim3(256), 0, s, (const uint16_t*)(ws + L.H_act),
+                     (int64_t)c.d, (uint16_t*)Ht, L.A_pad, (int64_t)0, (int64_t)0, (int64_t)c.d,
+                     ctrl);
+  hipLaunchKernelGGL(transpose16_kernel, gw, dim3(256), 0, s, (const uint16_t*)W, (int64_t)c.d,
+                     (uint16_t*)Wt, L.V_pad, (int64_t)c.V, L.V_pad, (int64_t)c.d,
+                     (const int32_t*)nullptr);
   const int row_tiles = (int)(L.A_pad / GBM);
   const int d_tiles = cdiv(c.d, GBN);
   for (int64_t v0 = 0; v0 < c.V; v0 += L.Vc) {
     const int32_t nv = (int32_t)((c.V - v0) < L.Vc ? (c.V - v0) : L.Vc);
     const int nv_tiles = cdiv(nv, GBN);
-    {  // logits of the chunk -> G (and G^T for fp32)
+    {  // logits of the chunk -> G
       GemmShape g = {};
       g.A = ws + L.H_act;
       g.lda = c.d;
-      g.B = (const uint8_t*)W + v0 * c.d * (int64_t)sizeof(T);
+      g.B = (const __bf16*)W + v0 * c.d;
       g.ldb = c.d;
       g.m_dev = ctrl;
       g.N = nv;
@@ -805,43 +829,40 @@ void bwd_gemms(const Common& c, const Layout& L, uint8_t* ws, const void* W, flo
       // in the Infinity Cache), not once per group of 8 token tiles
       g.group_m = 8;
       g.group_cols = 1;
-      EpiLogitGrad<T> e;
+      EpiLogitGrad e;
       e.y = (const int32_t*)(ws + L.y_act);
       e.lse = (const float*)(ws + L.lse_act);
       e.gs = (const float*)(ws + L.gs_act);
       e.G = G;
-      e.ldg = tiled ? L.A_pad : L.Vc;
-      e.Gt = tiled ? nullptr : Gt;
-      e.ldgt = L.A_pad;
+      e.ldg = L.A_pad;
       e.scale = c.inv_temp;
       e.col0 = (int32_t)v0;
-      launch_gemm<T>(&g, &e, 1, row_tiles * nv_tiles, (int32_t*)(ws + L.ctrl + 64), c.o,
-                     PH_RECOMPUTE, -1, s);
+      launch_gemm(&g, &e, 1, row_tiles * nv_tiles, (int32_t*)(ws + L.ctrl + 64), c.o,
+                  PH_RECOMPUTE, -1, s);
     }
     {  // dH[idx] (+)= G W[v0 : v0 + nv] (K = the chunk's vocabulary columns) and
        // dW[v0 : v0 + nv] = G^T H_act (K = action tokens), one launch, dH first:
-       // its tiles are the long ones.  bf16 G is column-block stage-tiled; dW
-       // reads it transposed (fp32 reads the separate G^T)
+       // its tiles are the long ones.  G is column-block stage-tiled; dW reads it
+       // transposed
       GemmShape g[2] = {};
       g[0].A = G;
-      g[0].lda = tiled ? L.A_pad : L.Vc;
-      // the chunk's first vocabulary column: a row offset, or whole 64-column blocks
-      g[0].B = tiled ? (const void*)(Wt + v0 * 256) : (const void*)(Wt + v0);
+      g[0].lda = L.A_pad;
+      g[0].B = Wt + v0 * 256;    // the chunk's first column: whole 64-column blocks
       g[0].ldb = L.V_pad;
-      g[0].a_tiled = tiled ? 2 : 0;
-      g[0].b_tiled = tiled;
+      g[0].a_tiled = 2;
+      g[0].b_tiled = 1;
       g[0].m_dev = ctrl;
       g[0].N = c.d;
-      // (bf16: a whole number of stage pairs; G and W^T are zero up to Vc and V_pad)
-      g[0].K = (int32_t)round_up(nv, (tiled ? 2 : 1) * KStage<T>::BK);
+      // (a whole number of stage pairs; G and W^T are zero up to Vc and V_pad)
+      g[0].K = (int32_t)round_up(nv, 2 * bf16k::SK);
       g[0].group_m = 8;
-      g[1].A = tiled ? G : Gt;
+      g[1].A = G;
       g[1].lda = L.A_pad;
       g[1].B = Ht;
       g[1].ldb = L.A_pad;
-      g[1].a_tiled = tiled ? 2 : 0;
-      g[1].a_trans = tiled;
-      g[1].b_tiled = tiled;
+      g[1].a_tiled = 2;
+      g[1].a_trans = 1;
+      g[1].b_tiled = 1;
       g[1].M = nv;
       g[1].N = c.d;
       g[1].k_dev = ctrl;
@@ -855,8 +876,8 @@ void bwd_gemms(const Common& c, const Layout& L, uint8_t* ws, const void* W, flo
       e[1].ldo = c.d;
       e[1].row_map = nullptr;
       e[1].accumulate = c.o.dw_accumulate;
-      launch_gemm<T>(g, e, 2, row_tiles * d_tiles + nv_tiles * d_tiles,
-                     (int32_t*)(ws + L.ctrl + 64), c.o, PH_DW, PH_DH, s);
+      launch_gemm(g, e, 2, row_tiles * d_tiles + nv_tiles * d_tiles,
+                  (int32_t*)(ws + L.ctrl + 64), c.o, PH_DW, PH_DH, s);
     }
   }
 }
@@ -911,10 +932,7 @@ extern "C" int agrl_policy_loss_fwd(int64_t T, int64_t max_act, int32_t d, int32
   uint8_t* ws = (uint8_t*)workspace;
   compact(c, L, ws, action_mask, token_id, adv_tok, old_logp, nullptr, nullptr, 0.0f, n_norm,
           logp, lse, H, err, s);
-  if (dtype == AGRL_BF16)
-    fwd_gemm<__bf16>(c, L, ws, W, s);
-  else
-    fwd_gemm<float>(c, L, ws, W, s);
+  fwd_gemm(c, L, ws, W, s);
   MergeArgs m;
   m.ctrl = (const int32_t*)(ws + L.ctrl);
   m.tiles_v = L.tiles_v;
@@ -976,10 +994,7 @@ extern "C" int agrl_token_logprob(int64_t T, int64_t max_act, int32_t d, int32_t
   uint8_t* ws = (uint8_t*)workspace;
   compact(c, L, ws, action_mask, token_id, nullptr, nullptr, nullptr, nullptr, 0.0f, 0, logp,
           lse, H, err, s);
-  if (dtype == AGRL_BF16)
-    fwd_gemm<__bf16>(c, L, ws, W, s);
-  else
-    fwd_gemm<float>(c, L, ws, W, s);
+  fwd_gemm(c, L, ws, W, s);
   // the loss merge with zero advantages: lse and logp are formed exactly as in
   // the policy-loss forward; its (zero) surrogate partials are not finalised
   MergeArgs m;
@@ -1045,8 +1060,8 @@ extern "C" int agrl_policy_loss_bwd(int64_t T, int64_t max_act, int32_t d, int32
   hipLaunchKernelGGL(zero_masked_rows_kernel, dim3((unsigned)(T < 8192 ? T : 8192)), dim3(256), 0,
                      s, T, d, action_mask, dH);
   if (dtype == AGRL_BF16)
-    bwd_gemms<__bf16>(c, L, ws, W, dH, dW, s);
+    bwd_gemms_bf16(c, L, ws, W, dH, dW, s);
   else
-    bwd_gemms<float>(c, L, ws, W, dH, dW, s);
+    bwd_gemms_f32(c, L, ws, W, dH, dW, s);
   return hip_status(hipGetLastError());
 }

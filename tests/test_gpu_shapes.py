@@ -1,0 +1,62 @@
+"""The policy loss at the sizes where its kernels change tile, split or tail: every
+output of forward and backward against the oracle.
+
+dH and dW, relative Frobenius.  fp32: sums of up to 8192 products (random walk of
+2^-24 roundings: 5e-6) of probabilities whose exponent carries up to 2^-24 * 16
+absolute (1e-6): 1e-5.  bf16: G rounded to 2^-9 relative: 4e-3 (twice the bound, for
+the few elements in which a sum is dominated by one product).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+from helpers import compare_loss, log, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(dtype, V, d, n_act, *, T=None, seed=1, opt=None, max_act=None, dW0=None):
+    import paper_2510_04206_amd as P
+    rng = np.random.default_rng([seed, V, d, n_act])
+    T = T or n_act + n_act // 2 + 3
+    mask = np.zeros(T, np.uint8)
+    mask[np.sort(rng.permutation(T)[:n_act])] = 1
+    g = torch.Generator().manual_seed(seed)
+    H = torch.randn((T, d), generator=g).to(dtype)
+    W = torch.randn((V, d), generator=g).mul_(0.1).to(dtype)
+    y = rng.integers(0, V, T).astype(np.int32)
+    y[:: 7] = V - 1                                  # the last vocabulary row's tile
+    logp = torch.log_softmax(H.float() @ W.float().t(), 1)[torch.arange(T), torch.from_numpy(y).long()]
+    old = (logp.numpy() + 0.2 * rng.standard_normal(T)).astype(np.float32)
+    adv = rng.standard_normal(T).astype(np.float32)
+    log(f"shape {dtype} V={V} d={d} n_act={n_act} T={T} max_act={max_act} {opt}")
+    pl = P.PolicyLoss(T, d, V, dtype, max_act=n_act if max_act is None else max_act, opt=opt)
+    if dW0 is not None:
+        pl.dW.fill_(dW0)
+    t = lambda a: torch.from_numpy(a).cuda()                    # noqa: E731
+    got = run_gpu(pl, dict(H=H.cuda(), W=W.cuda(), token_id=t(y), mask=t(mask), old_logp=t(old)), t(adv))
+    assert P.agrl_get_device_error() == 0
+    ref = oracle.policy_loss(H, W, y, mask, adv, old)
+    if dW0 is not None:
+        ref["dW"] = ref["dW"] + dW0
+    errs = compare_loss(got, ref, mask, adv, old, 0.2, 0.2,
+                        grad_rel=1e-5 if dtype == torch.float32 else 4e-3)
+    log(f"  dH, dW: {errs}")
+
+
+# fp32: logit tiles of 256 x 32 and 256 x 64 (the second from 512 tiles on), gradient
+# tiles of 64 x 64, K stages of 32; dW split (few rows, many tokens), dH split (many
+# rows, few tokens), neither; a hidden size above and below one tile
+@pytest.mark.parametrize("V,d,n_act", [
+    (1, 64, 1), (255, 64, 31), (257, 64, 33), (256, 128, 64), (300, 192, 65), (33, 64, 3000),
+    (256, 64, 8192), (8191, 64, 129), (8193, 64, 1056), (4099, 320, 257), (2049, 1024, 100)])
+def test_fp32_shapes(V, d, n_act):
+    _case(torch.float32, V, d, n_act)
+
+
+def test_fp32_chunks_accumulate_loose_bound():
+    # chunks of 512 columns, the last of 3; dW added to; room for every token
+    _case(torch.float32, 1027, 128, 300, T=1500, opt=dict(g_chunk_bytes=2 * 1536 * 4 * 512, dw_accumulate=1),
+          max_act=0, dW0=0.25)
