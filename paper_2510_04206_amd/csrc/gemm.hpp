@@ -37,15 +37,15 @@ constexpr int GEMM_LDS = 2 * STAGE_BYTES;               // 128 KiB of stage buff
 // bf16 logit-gradient epilogue (two passes of 128 tile rows): G rows staged
 // row-major with 528-byte pitch (the two half-waves of a 16-bit store land in
 // different banks); three 256-entry per-row arrays at EPI_META, above both the
-// stage buffers and the store epilogue's 132 KiB staging of a pass
+// stage buffers and the store epilogue's 130 KiB staging of a pass
 constexpr int EPI_G_ROW = 528;
 constexpr int EPI_GS = 0;
 // fp32 store epilogue of the 16 x 16 layout: a pass of 128 tile rows staged
-// column-major, 132 floats per column (see EpiStore::tile16)
-constexpr int EPI_COL = 132;
-constexpr int EPI_COLS_LDS = 256 * EPI_COL * 4;             // 135168
-constexpr int EPI_META = EPI_COLS_LDS > GEMM_LDS ? EPI_COLS_LDS : GEMM_LDS;
-constexpr int EPI_STAGE_LDS = EPI_META + 3 * 1024;          // 138240 B
+// row-major, 260 floats per row (see EpiStore::tile16)
+constexpr int EPI_F32_ROW = 260;
+constexpr int EPI_ROWS_LDS = 128 * EPI_F32_ROW * 4;         // 133120
+constexpr int EPI_META = EPI_ROWS_LDS > GEMM_LDS ? EPI_ROWS_LDS : GEMM_LDS;
+constexpr int EPI_STAGE_LDS = EPI_META + 3 * 1024;          // 136192 B
 static_assert(EPI_GS + 128 * EPI_G_ROW <= EPI_META, "G staging below the per-row arrays");
 constexpr int BF16_KERNEL_LDS = EPI_STAGE_LDS > GEMM_LDS ? EPI_STAGE_LDS : GEMM_LDS;
 constexpr int GEMM_THREADS = 256;
@@ -67,8 +67,13 @@ struct GemmShape {
   // multiple of 64), 2 in column-block order (tiled_cm_index; lda / ldb = its
   // padded row count, a multiple of 256).  a_trans: A is read transposed out
   // of a column-block tiled matrix whose rows are the product's K and whose
-  // columns are the product's rows (lda = its padded row count).
+  // columns are the product's rows (lda = its padded row count), or (2) out of a
+  // row-major one (lda = its row length; EpiGrad's launches only), whose rows from
+  // stage a_tail_stage on are read from a_tail instead (a copy that is zero-padded
+  // to a whole number of stages).
   int32_t a_tiled, b_tiled, a_trans;
+  const void* a_tail;
+  int32_t a_tail_stage;
   // bf16 kernel only: 1 makes the tile-order groups run over column tiles
   // (group_m column tiles deep, sweeping every row tile) instead of row tiles
   int32_t group_cols;
@@ -299,6 +304,8 @@ struct GemmBatch {
   GemmShape g[2];
   Epi e[2];
   int32_t n;          // number of problems
+  int32_t cus;        // EpiGrad: compute units, and the most parts K of problem 0
+  int32_t split_max;  // may be split into (see dh_split)
   int32_t* queue;     // 8 tile counters, then 8 finished-tile counters, zero at launch
 };
 
@@ -310,6 +317,7 @@ struct GemmBatch {
 // their L2 hit rate dropped).
 struct EpiLseCols;
 struct EpiStore;
+struct EpiGrad;
 template <class Epi>
 struct CopySched {
   static constexpr int spacing = 6;
@@ -331,6 +339,8 @@ struct CopySched<EpiStore> {
   static constexpr bool serpentine = true;
   static constexpr bool round_sync = true;
 };
+template <>
+struct CopySched<EpiGrad> : CopySched<EpiStore> {};
 constexpr int ROUND_SLACK = 2;   // tiles of the earlier rounds that may still run
 constexpr int ROUND_SPIN = 32;   // polls of the finished-tile counter (~0.3 us apart)
 
@@ -376,6 +386,26 @@ __device__ __forceinline__ int queue_tile(int k, const QueueShare& s, int q, int
   return (s.full / 32) * (32 * nq) + (k - s.full) * nq + q;
 }
 
+// Parts of dH's K extent (a vocabulary chunk of nv columns) in an EpiGrad launch.  With
+// few action tokens dH has few tiles, each a chain over the whole chunk (2376 stages at
+// V = 152064, 3 ms, whatever the chip could do beside it): parts of a third of a compute
+// unit's share of the launch let the queues balance them against dW's tiles, whose
+// epilogue (256 KiB written) costs about 12 stages.  dH + dW at V = 152064, d = 3584, 700
+// tokens, dW accumulated: 3250 us in one piece (and 400 us of W^T before it), 2080 us in
+// parts; V = 43776, d = 1088, 2122 tokens: 750 and 415 us.  2 or 5 instead of 3, or 24
+// stages for the epilogue, are within the runs' noise.
+constexpr int DH_PARTS = 3, DW_EPI_STAGES = 12, DH_MIN_STAGES = 16;
+__host__ __device__ inline int dh_split(int n_act, int nv, int d, int cus, int most) {
+  const int td = cdiv(d, GBN);
+  const int64_t th = (int64_t)cdiv(n_act, GBM) * td, tw = (int64_t)cdiv(nv, GBM) * td;
+  const int kh = 2 * cdiv(nv, 2 * bf16k::SK), kw = 2 * cdiv(n_act, 2 * bf16k::SK);
+  const int64_t work = th * kh + tw * (kw + DW_EPI_STAGES);
+  int64_t part = work / ((int64_t)cus * DH_PARTS);
+  if (part < DH_MIN_STAGES) part = DH_MIN_STAGES;
+  const int64_t parts = (kh + part - 1) / part;
+  return (int)(parts < most ? parts : most);
+}
+
 // EVEN: every problem's K is a multiple of 2 stages (a device-read K is rounded
 // up to one, the operands being zero-padded that far); such launches run the
 // 16 x 16 loop (MF16), whose stage pairs know their buffers at compile time, so
@@ -388,6 +418,8 @@ __global__ void __launch_bounds__(GEMM_THREADS)
     __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_bf16_kernel(GemmBatch<Epi> bat) {
   static_assert(MF16 == EVEN, "stage-pair launches run the 16 x 16 loop, the others the 32 x 32 loop");
   static_assert(!ATR || MF16, "transposed A in the 16 x 16 loop only");
+  // both products read A transposed, problem 0 (dH) out of row-major W with K split
+  constexpr bool GRAD = std::is_same<Epi, EpiGrad>::value;
   using namespace bf16k;
   __shared__ __attribute__((aligned(16))) uint8_t smem[BF16_KERNEL_LDS];
   __shared__ int s_tile[2];   // claimed tile (-1: none left) and its queue
@@ -408,6 +440,12 @@ __global__ void __launch_bounds__(GEMM_THREADS)
     tmp[p] = cdiv(Mp[p], GBM);
     tnp[p] = cdiv(Np[p], GBN);
     totp[p] = (p < bat.n && Mp[p] > 0 && Np[p] > 0) ? tmp[p] * tnp[p] : 0;
+  }
+  int parts = 1;
+  if constexpr (GRAD) {
+    parts = __builtin_amdgcn_readfirstlane(
+        dh_split(Np[0], Mp[1], Mp[0], bat.cus, bat.split_max));
+    totp[0] *= parts;
   }
 
   // fragment reads: lane l reads row (l & 31) of each 32-row block, chunk
@@ -483,9 +521,21 @@ __global__ void __launch_bounds__(GEMM_THREADS)
     const Epi epi = p ? bat.e[1] : bat.e[0];
     const int M = p ? Mp[1] : Mp[0];
     const int N = p ? Np[1] : Np[0];
-    const int nk = (p ? Kp[1] : Kp[0]) / SK;
+    int nk = (p ? Kp[1] : Kp[0]) / SK;
     int tm, tn;
-    const int L = p ? queue_tile(t - sh[0].len, sh[1], cq, nq) : queue_tile(t, sh[0], cq, nq);
+    int L = p ? queue_tile(t - sh[0].len, sh[1], cq, nq) : queue_tile(t, sh[0], cq, nq);
+    int k0 = 0, at_part = 0;     // first stage of this item's part of K; the part
+    if constexpr (GRAD) {
+      if (p == 0) {
+        const int tiles = tmp[0] * tnp[0];
+        const int part = __builtin_amdgcn_readfirstlane(L / tiles);
+        const int per = __builtin_amdgcn_readfirstlane(2 * cdiv(nk / 2, parts));
+        L -= part * tiles;
+        k0 = part * per;
+        nk = max(0, min(per, nk - k0));
+        at_part = part;
+      }
+    }
     if (g.group_cols)
       grouped_tile(L, p ? tnp[1] : tnp[0], p ? tmp[1] : tmp[0], g.group_m, tn, tm);
     else
@@ -511,7 +561,11 @@ __global__ void __launch_bounds__(GEMM_THREADS)
       }
     };
     int64_t a_off, a_ks, b_off, b_ks;
-    if (atr) {
+    const bool atr_rows = GRAD && g.a_trans == 2;
+    if (atr_rows) {
+      a_off = (int64_t)m0 * 2;
+      a_ks = SK * lda_b;
+    } else if (atr) {
       a_off = (int64_t)tm * 4 * (g.lda >> 8) * HALF;
       a_ks = SK * ROW;
     } else {
@@ -520,7 +574,18 @@ __global__ void __launch_bounds__(GEMM_THREADS)
     place(g.b_tiled, g.ldb, ldb_b, tn, n0, b_off, b_ks);
     // serpentine K (16 x 16 loop): odd rounds of the problem's tile order copy
     // the stages last to first
-    if (MF16 && CopySched<Epi>::serpentine && ((L / (32 * nq)) & 1)) {
+    // (an item of row-major W goes forwards: its tail is another buffer)
+    if constexpr (GRAD) {
+      a_off += k0 * a_ks;
+      b_off += k0 * b_ks;
+    }
+    int64_t tail_delta = 0;      // from a tail stage's place in W to its copy
+    if constexpr (GRAD) {
+      if (atr_rows)
+        tail_delta = ((const uint8_t*)g.a_tail - (int64_t)g.a_tail_stage * a_ks) -
+                     (const uint8_t*)g.A;
+    }
+    if (MF16 && CopySched<Epi>::serpentine && !atr_rows && ((L / (32 * nq)) & 1)) {
       a_off += (int64_t)(nk - 1) * a_ks;
       b_off += (int64_t)(nk - 1) * b_ks;
       a_ks = -a_ks;
@@ -563,6 +628,13 @@ __global__ void __launch_bounds__(GEMM_THREADS)
         // (lda <= 2^23 rows: at most 3 * 2^15 blocks of 32 KiB, within 32 bits)
         offa[b] = (uint32_t)((w >> 1) * (uint32_t)((g.lda >> 8) * HALF) + kr * ROW +
                              ((c16 ^ ((kr >> 1) & 7)) << 4));
+        // row-major: k-row kr of the stage, the same columns (those past the last
+        // are clamped; the epilogue drops their rows)
+        if constexpr (GRAD) {
+          if (atr_rows)
+            offa[b] = (uint32_t)(kr * (uint32_t)lda_b) +
+                      (uint32_t)(min((w >> 1) * 64 + c16 * 8, M - 8 - m0) * 2);
+        }
       }
     }
 
@@ -576,7 +648,11 @@ __global__ void __launch_bounds__(GEMM_THREADS)
       constexpr uint32_t b = Q % IPW;
       constexpr uint32_t fixed = BUF >= 0 ? (uint32_t)BUF * HALF : 0u;
       const uint32_t base = BUF >= 0 ? lds_w : lds_w + (uint32_t)(buf * HALF);
-      if constexpr (Q < IPW)
+      if constexpr (Q < IPW && GRAD)
+        copy16<fixed + b * RPI * ROW>(
+            a_base + s * a_ks + (atr_rows && k0 + s >= g.a_tail_stage ? tail_delta : 0), offa[b],
+            base);
+      else if constexpr (Q < IPW)
         copy16<fixed + b * RPI * ROW>(a_base + s * a_ks, offa[b], base);
       else
         copy16<NB * HALF + fixed + b * RPI * ROW>(b_base + s * b_ks, offb[b], base);
@@ -609,7 +685,8 @@ __global__ void __launch_bounds__(GEMM_THREADS)
     if constexpr (MF16) {
       // 16 x 16 x 32 loop.  acc[i][j] is the 16 x 16 block (i, j) of the wave's
       // 128 x 128 sub-tile: lane l holds column 16 j + (l & 15), rows 16 i +
-      // 4 (l >> 4) .. + 3.  A stage is two 32-deep slices; the MFMAs of a stage
+      // 4 (l >> 4) .. + 3 (Epi::SWAP: row 16 i + (l & 15), columns 16 j +
+      // 4 (l >> 4) .. + 3).  A stage is two 32-deep slices; the MFMAs of a stage
       // run rows i = 0..7, columns j = 0..7, and the two slices of block (i, j)
       // back to back (the second accumulates onto the first).  The stage's
       // fragments are in registers before it starts: fa[i][kk] (A, replaced in
@@ -730,12 +807,10 @@ __global__ void __launch_bounds__(GEMM_THREADS)
               __builtin_amdgcn_s_barrier();
               __builtin_amdgcn_sched_barrier(0);
             }
-            if constexpr (i == 7 && P == 1)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa7[kk], fb[P][j][kk], acc[i][j],
-                                                                  0, 0, 0);
-            else
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][kk], fb[P][j][kk],
-                                                                  acc[i][j], 0, 0, 0);
+            // (operands swapped: each block transposed, the same sums)
+            const bf16x8 a = i == 7 && P == 1 ? fa7[kk] : fa[i][kk], b = fb[P][j][kk];
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Epi::SWAP ? b : a,
+                                                                Epi::SWAP ? a : b, acc[i][j], 0, 0, 0);
             if constexpr (op >= MF16_COPY && op < MF16_COPY + 16) {
               constexpr int c = op - MF16_COPY;
               copy_q(kc, CopySched<Epi>::a_first ? c : copy_order(c), PC{}, P);
@@ -760,7 +835,9 @@ __global__ void __launch_bounds__(GEMM_THREADS)
       }
       };
       if (nk > 0) {
-        if constexpr (ATR) {
+        if constexpr (GRAD) {
+          loop16(std::true_type{});
+        } else if constexpr (ATR) {
           if (atr)
             loop16(std::true_type{});
           else
@@ -773,6 +850,11 @@ __global__ void __launch_bounds__(GEMM_THREADS)
       __syncthreads();
       {
         const int lane_e = fresh_lane();
+        if constexpr (GRAD) {
+          Epi ep = epi;
+          ep.to_part(at_part);
+          ep.tile16(acc, m0, n0, tn, M, N, smem, wm, wn, lane_e, wave * 64 + lane_e);
+        } else
         epi.tile16(acc, m0, n0, tn, M, N, smem, wm, wn, lane_e, wave * 64 + lane_e);
       }
     } else {
@@ -879,6 +961,7 @@ __global__ void __launch_bounds__(GEMM_THREADS)
 // row waves through LDS: (max, sum exp) per token and vocabulary tile, and the
 // target logit.
 struct EpiLseCols {
+  static constexpr bool SWAP = false;
   const int32_t* y;      // [tokens] target id of each compacted row
   f32x2* part;           // [tiles_v][ld_part] (max, sum exp) per token and vocabulary tile
   int64_t ld_part;
@@ -1060,6 +1143,7 @@ struct EpiLseCols {
 // evaluated in base 2 with the scale folded in:
 // exp(z - lse) = exp2(acc * scale * log2(e) - lse * log2(e)).
 struct EpiLogitGrad {
+  static constexpr bool SWAP = false;
   const int32_t* y;
   const float* lse;
   const float* gs;       // dL/dlogp / temperature, per compacted row
@@ -1233,79 +1317,95 @@ struct EpiLogitGrad {
   }
 };
 
-// Plain fp32 store (or accumulate) of the tile, rows optionally remapped.
+// Plain fp32 store (or accumulate) of the tile, rows optionally remapped.  Swapped
+// accumulators: lane l's f32x4 of block (i, j) is columns 16 j + 4 (l >> 4) .. + 3 of row
+// 16 i + (l & 15).  Pass h stages blocks i = 4 h .. 4 h + 3 of both wave rows row-major,
+// one 16-byte LDS write per accumulator (260 floats a row: the 16 rows of a write are 16
+// distinct bank groups), and a row leaves as one 16-byte access per lane, 1 KiB
+// contiguous.  With few action tokens dW's tiles are mostly this (12 K stages at 700
+// tokens): what bounds them is how many bytes a workgroup has in flight, so 16 rows a
+// wave are read ahead when accumulating (64 KiB per compute unit).
 struct EpiStore {
+  static constexpr bool SWAP = true;
   float* out;
   int64_t ldo;
   const int32_t* row_map;   // nullable: output row of each tile row
   int32_t accumulate;
 
-  // 16 x 16 accumulator layout.  Pass h stages blocks i = 4 h .. 4 h + 3 of both
-  // wave rows (the same tile rows as the 32 x 32 layout's pass h), each block
-  // as whole accumulators: a lane's f32x4 (4 consecutive rows of one column)
-  // is one 16-byte LDS write into a column-major staging area (128 rows per
-  // column, padded to EPI_COL floats so that the 16 columns of a write are 16
-  // distinct bank groups).  (Writing the accumulators element by element
-  // makes the register allocator shuffle them through VGPRs inside the main
-  // loop.)  The write-out takes one staged row per wave at a time, lane l
-  // holding columns l, l + 64, l + 128, l + 192: every store instruction
-  // covers 256 consecutive bytes of an output row.
   __device__ __forceinline__ void tile16(f32x4 (&acc)[8][8], int m0, int n0, int tn, int M, int N,
                                          uint8_t* smem, int wm, int wn, int lane, int tid) const {
     int* sr = (int*)(smem + EPI_META);
-    if (row_map) sr[tid] = (m0 + tid < M) ? row_map[m0 + tid] : 0;
-    float* st = (float*)smem;
+    if (row_map) {
+      sr[tid] = (m0 + tid < M) ? row_map[m0 + tid] : 0;
+      lds_barrier();
+    }
     if (accumulate)
-      out16<true>(acc, m0, n0, M, N, st, sr, wm, wn, lane);
+      out16<true>(acc, m0, n0, M, N, (float*)smem, sr, wm, wn, lane);
     else
-      out16<false>(acc, m0, n0, M, N, st, sr, wm, wn, lane);
+      out16<false>(acc, m0, n0, M, N, (float*)smem, sr, wm, wn, lane);
   }
 
   template <bool ACC>
   __device__ __forceinline__ void out16(const f32x4 (&acc)[8][8], int m0, int n0, int M, int N,
                                         float* st, const int* sr, int wm, int wn, int lane) const {
     const int wave = wm * 2 + wn;
+    const bool col_ok = n0 + 4 * lane < N;         // N is a multiple of 64
+    f32x4 old[16];
+    // staged row pr of pass h is tile row 64 h + pr (pr < 64) or 64 h + pr + 64; wave w
+    // writes rows w, w + 4, ...  (dst is null for a row past M or a column past N)
+    auto dst = [&](int h, int k) {
+      const int pr = wave + 4 * k, tr = 64 * h + (pr < 64 ? pr : pr + 64);
+      const int64_t row = row_map ? (int64_t)sr[tr] : (int64_t)(m0 + tr);
+      return m0 + tr < M && col_ok ? (f32x4*)(out + row * ldo + n0 + 4 * lane) : nullptr;
+    };
+    auto read = [&](int h, int k0) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const f32x4* p = dst(h, k0 + k);
+        old[k] = p ? *p : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+    };
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
+      if constexpr (ACC) read(h, 0);
       if (h) lds_barrier();                        // pass 0's rows have been read
 #pragma unroll
       for (int ii = 0; ii < 4; ++ii)
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          *(f32x4*)(st + (wn * 128 + 16 * j + (lane & 15)) * EPI_COL + wm * 64 + 16 * ii +
+          *(f32x4*)(st + (wm * 64 + 16 * ii + (lane & 15)) * EPI_F32_ROW + wn * 128 + 16 * j +
                     4 * (lane >> 4)) = acc[4 * h + ii][j];
-      lds_barrier();                               // rows staged (and sr written)
-      // staged row pr is tile row 64 h + pr (pr < 64) or 128 + 64 h + (pr - 64);
-      // wave w writes rows w, w + 4, ..., 8 rows at a time
+      lds_barrier();                               // rows staged
 #pragma unroll
-      for (int k0 = 0; k0 < 32; k0 += 8) {
-        float* dst[8];
-        float old[8][4];
+      for (int k0 = 0; k0 < 32; k0 += 16) {
+        f32x4 v[16];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int pr = wave + 4 * (k0 + k);
-          const int tr = 64 * h + (pr < 64 ? pr : pr + 64);
-          const int64_t orow = row_map ? (int64_t)sr[tr] : (int64_t)(m0 + tr);
-          dst[k] = m0 + tr < M ? out + orow * ldo + n0 : nullptr;
-          if constexpr (ACC) {
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-              old[k][m] = dst[k] && n0 + lane + 64 * m < N ? dst[k][lane + 64 * m] : 0.0f;
-          }
+        for (int k = 0; k < 16; ++k) {
+          v[k] = *(const f32x4*)(st + (wave + 4 * (k0 + k)) * EPI_F32_ROW + 4 * lane);
+          if constexpr (ACC) v[k] += old[k];
+        }
+        if constexpr (ACC) {
+          if (k0 == 0) read(h, 16);
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int pr = wave + 4 * (k0 + k);
-#pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            float v = st[(lane + 64 * m) * EPI_COL + pr];
-            if constexpr (ACC) v += old[k][m];
-            if (dst[k] && n0 + lane + 64 * m < N) dst[k][lane + 64 * m] = v;
-          }
+        for (int k = 0; k < 16; ++k) {
+          f32x4* p = dst(h, k0 + k);
+          if (p) *p = v[k];
         }
       }
     }
   }
+};
+
+// The two products of a launch for few action tokens: dW as above; dH computed
+// transposed (rows: hidden units, columns: compacted tokens), so that W is the operand
+// read transposed, as it lies in memory, and no W^T is built.  Its items write their
+// part of K to parts [part][rows][ldo]; the reduce kernel adds the parts in order and
+// turns them into dH's rows.
+struct EpiGrad : EpiStore {
+  int64_t part_stride;
+
+  __device__ __forceinline__ void to_part(int part) { out += part * part_stride; }
 };
 
 }  // namespace agrl

@@ -204,18 +204,30 @@ __global__ __launch_bounds__(kScanThreads) void scan_scatter_kernel(ScatterArgs 
   }
 }
 
-// H_act[n] = H[idx[n]] for n < n_act, zero rows up to the next multiple of 256.
+// The last rows of W padded with zero rows to kTailRows, for a K extent over W's rows.
+constexpr int kTailRows = 2 * bf16k::SK;
+struct TailCopy {
+  const uint8_t* src;      // nullable
+  int64_t rows;            // rows of src
+  uint8_t* dst;
+};
+
+// H_act[n] = H[idx[n]] for n < n_act, zero rows up to the next multiple of 256; then
+// the tail copy.
 __global__ __launch_bounds__(256) void gather_rows_kernel(const uint8_t* __restrict__ H,
                                                           int64_t row_bytes,
                                                           const int32_t* __restrict__ idx,
-                                                          const int32_t* ctrl, uint8_t* H_act) {
+                                                          const int32_t* ctrl, uint8_t* H_act,
+                                                          TailCopy tail) {
   const int n_act = ctrl[0];
   const int64_t rows = round_up(n_act, kRowPad);
   const int64_t chunks = row_bytes / 16;
-  for (int64_t n = blockIdx.x; n < rows; n += gridDim.x) {
-    u32x4* dst = (u32x4*)(H_act + n * row_bytes);
-    if (n < n_act) {
-      const u32x4* src = (const u32x4*)(H + (int64_t)idx[n] * row_bytes);
+  for (int64_t n = blockIdx.x; n < rows + (tail.src ? kTailRows : 0); n += gridDim.x) {
+    const bool t = n >= rows;
+    u32x4* dst = (u32x4*)(t ? tail.dst + (n - rows) * row_bytes : H_act + n * row_bytes);
+    if (t ? n - rows < tail.rows : n < n_act) {
+      const u32x4* src = (const u32x4*)(t ? tail.src + (n - rows) * row_bytes
+                                          : H + (int64_t)idx[n] * row_bytes);
       for (int64_t c = threadIdx.x; c < chunks; c += blockDim.x) dst[c] = src[c];
     } else {
       for (int64_t c = threadIdx.x; c < chunks; c += blockDim.x) dst[c] = u32x4{0, 0, 0, 0};
@@ -407,6 +419,39 @@ __global__ __launch_bounds__(256) void zero_masked_rows_kernel(int64_t T, int32_
   }
 }
 
+// dH[idx[n]][c] (+)= the parts of (c, n) in ascending order: parts [part][d][ld], turned
+// through LDS by 64 x 64 tiles (dh_split says how many there are, as in the launch).
+__global__ __launch_bounds__(256) void dh_reduce_kernel(const float* __restrict__ parts,
+                                                        int64_t ld, const int32_t* ctrl,
+                                                        const int32_t* idx, int32_t nv, int32_t d,
+                                                        int32_t cus, int32_t split_max,
+                                                        int32_t add, float* dH) {
+  __shared__ float tile[64][65];
+  const int n_act = ctrl[0];
+  const int n0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+  if (n0 >= n_act) return;
+  const int n_parts = dh_split(n_act, nv, d, cus, split_max);
+  const int q = threadIdx.x & 15, r = threadIdx.x >> 4;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float* p = parts + (int64_t)(c0 + r + 16 * k) * ld + n0 + 4 * q;
+    f32x4 v = *(const f32x4*)p;
+    for (int i = 1; i < n_parts; ++i) v += *(const f32x4*)(p + i * (int64_t)d * ld);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tile[r + 16 * k][4 * q + e] = v[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int n = r + 16 * k;
+    if (n0 + n >= n_act) continue;
+    f32x4* out = (f32x4*)(dH + (int64_t)idx[n0 + n] * d + c0 + 4 * q);
+    f32x4 v = {tile[4 * q][n], tile[4 * q + 1][n], tile[4 * q + 2][n], tile[4 * q + 3][n]};
+    if (add) v += *out;
+    *out = v;
+  }
+}
+
 __global__ __launch_bounds__(256) void zero_f32_kernel(float* p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
@@ -425,10 +470,19 @@ struct Layout {
   size_t ctrl, blk_cnt, blk_off, idx, y_act, adv_act, old_act, ref_act, w_act, lse_act, gs_act,
       zy, blk_sum,
       blk_clip, H_act, part, Ht, Wt, G, ph, pw, fwd_total, total;
-  int32_t ph_max, pw_max;      // fp32: parts the gradient products' partial buffers hold
+  int32_t ph_max, pw_max;      // parts the gradient products' partial buffers hold
+  bool w_rows;                 // bf16: dH reads W as it lies (no W^T; its place holds W's
+  size_t tail;                 // padded tail rows and dH's parts)
 };
 
 constexpr int64_t kDefaultChunkBytes = (int64_t)4 << 30;
+
+// Up to this many (padded) action tokens dH reads W as it lies, transposing in the LDS
+// read, instead of a W^T built first.  The transpose costs a pass over W whatever the
+// tokens, the transposing reads a share of dH's time.  Backward products and transpose,
+// W^T against W (V = 152064): 7.33 against 6.53 ms at d = 5120 and 2871 tokens, 15.70
+// against 15.57 ms at d = 3584 and 10515, 45.0 against 45.8 ms at d = 5120 and 22793.
+constexpr int64_t kWRowsMax = 8192;
 
 bool make_layout(int64_t T, int64_t max_act, int32_t d, int32_t V, int32_t dtype,
                  const agrl_options& o, Layout* L) {
@@ -486,6 +540,14 @@ bool make_layout(int64_t T, int64_t max_act, int32_t d, int32_t V, int32_t dtype
   L->Ht = take(d_pad * A * L->esize);
   L->Wt = take(d_pad * L->V_pad * L->esize);
   L->G = take(A * (size_t)L->Vc * L->esize);
+  L->w_rows = dtype == AGRL_BF16 && L->A_pad <= kWRowsMax;
+  if (L->w_rows) {
+    L->tail = L->Wt;
+    L->ph = L->Wt + round_up((int64_t)kTailRows * d * 2, 256);
+    const size_t n = L->ph < L->G ? (L->G - L->ph) / (A * d * 4) : 0;
+    L->ph_max = (int32_t)(n > 32 ? 32 : n);
+    L->w_rows = n > 0;        // (a tiny vocabulary's W^T is smaller than dH)
+  }
   if (dtype == AGRL_F32) {
     // The fp32 products read H_act and W as they lie: no H^T and W^T.  G, then half
     // of the rest for the parts of each gradient product (G is budgeted twice)
@@ -586,7 +648,7 @@ void record(const agrl_options& o, int event, hipStream_t s) {
 // slot, when given, is recorded empty).
 template <class Epi>
 void launch_gemm(const GemmShape* g, const Epi* e, int n, int max_tiles, int32_t* queue,
-                 const agrl_options& o, Phase ph, int ph2, hipStream_t s) {
+                 const agrl_options& o, Phase ph, int ph2, hipStream_t s, int split_max = 1) {
   int grid = device_cu_count();
   if (max_tiles < grid) grid = max_tiles < 1 ? 1 : max_tiles;
   GemmBatch<Epi> b;
@@ -596,13 +658,15 @@ void launch_gemm(const GemmShape* g, const Epi* e, int n, int max_tiles, int32_t
   }
   b.n = n;
   b.queue = queue;
+  b.cus = device_cu_count();
+  b.split_max = split_max;
   hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(64), 0, s, queue);
   record(o, 2 * ph, s);
   // The bf16 store launch is the backward's dH + dW: its operands are
   // stage-tiled, dW reads G transposed, and both K extents are whole stage
   // pairs (the vocabulary chunk rounded up to 128, the device-read token count
   // rounded up in the kernel), so it always runs the 16 x 16 loop.
-  if constexpr (std::is_same<Epi, EpiStore>::value) {
+  if constexpr (std::is_base_of<EpiStore, Epi>::value) {
     hipLaunchKernelGGL((gemm_bf16_kernel<Epi, true, true, true>), dim3(grid), dim3(GEMM_THREADS),
                        0, s, b);
   } else {
@@ -642,7 +706,7 @@ void launch_logits_f32(const f32k::LogitsArgs& g, int64_t rows, hipStream_t s) {
 int compact(const Common& c, const Layout& L, uint8_t* ws, const uint8_t* mask,
             const int32_t* token_id, const float* adv, const float* old, const float* lse_in,
             const float* logp_in, float grad_loss, int64_t n_norm, float* logp_out,
-            float* lse_out, const void* H, int* err, hipStream_t s) {
+            float* lse_out, const void* H, int* err, hipStream_t s, TailCopy tail = {}) {
   int32_t* ctrl = (int32_t*)(ws + L.ctrl);
   hipLaunchKernelGGL(scan_count_kernel, dim3(L.nblk), dim3(kScanThreads), 0, s, c.T, mask,
                      (int32_t*)(ws + L.blk_cnt));
@@ -684,11 +748,11 @@ int compact(const Common& c, const Layout& L, uint8_t* ws, const uint8_t* mask,
   a.inv_temp = c.inv_temp;
   a.err = err;
   hipLaunchKernelGGL(scan_scatter_kernel, dim3(L.nblk), dim3(kScanThreads), 0, s, a);
-  const int64_t rows = L.A_pad;
+  const int64_t rows = L.A_pad + (tail.src ? kTailRows : 0);
   const int grid = (int)(rows < 4096 ? rows : 4096);
   hipLaunchKernelGGL(gather_rows_kernel, dim3(grid), dim3(256), 0, s, (const uint8_t*)H,
                      (int64_t)c.d * L.esize, (const int32_t*)(ws + L.idx), (const int32_t*)ctrl,
-                     ws + L.H_act);
+                     ws + L.H_act, tail);
   return AGRL_OK;
 }
 
@@ -807,9 +871,10 @@ void bwd_gemms_bf16(const Common& c, const Layout& L, uint8_t* ws, const void* W
   hipLaunchKernelGGL(transpose16_kernel, gh, dim3(256), 0, s, (const uint16_t*)(ws + L.H_act),
                      (int64_t)c.d, (uint16_t*)Ht, L.A_pad, (int64_t)0, (int64_t)0, (int64_t)c.d,
                      ctrl);
-  hipLaunchKernelGGL(transpose16_kernel, gw, dim3(256), 0, s, (const uint16_t*)W, (int64_t)c.d,
-                     (uint16_t*)Wt, L.V_pad, (int64_t)c.V, L.V_pad, (int64_t)c.d,
-                     (const int32_t*)nullptr);
+  if (!L.w_rows)
+    hipLaunchKernelGGL(transpose16_kernel, gw, dim3(256), 0, s, (const uint16_t*)W, (int64_t)c.d,
+                       (uint16_t*)Wt, L.V_pad, (int64_t)c.V, L.V_pad, (int64_t)c.d,
+                       (const int32_t*)nullptr);
   const int row_tiles = (int)(L.A_pad / GBM);
   const int d_tiles = cdiv(c.d, GBN);
   for (int64_t v0 = 0; v0 < c.V; v0 += L.Vc) {
@@ -867,7 +932,7 @@ void bwd_gemms_bf16(const Common& c, const Layout& L, uint8_t* ws, const void* W
       g[1].N = c.d;
       g[1].k_dev = ctrl;
       g[1].group_m = 8;
-      EpiStore e[2];
+      EpiGrad e[2] = {};
       e[0].out = dH;
       e[0].ldo = c.d;
       e[0].row_map = (const int32_t*)(ws + L.idx);
@@ -876,8 +941,39 @@ void bwd_gemms_bf16(const Common& c, const Layout& L, uint8_t* ws, const void* W
       e[1].ldo = c.d;
       e[1].row_map = nullptr;
       e[1].accumulate = c.o.dw_accumulate;
-      launch_gemm(g, e, 2, row_tiles * d_tiles + nv_tiles * d_tiles,
-                  (int32_t*)(ws + L.ctrl + 64), c.o, PH_DW, PH_DH, s);
+      int32_t* queue = (int32_t*)(ws + L.ctrl + 64);
+      if (!L.w_rows) {
+        const EpiStore es[2] = {e[0], e[1]};
+        launch_gemm(g, es, 2, row_tiles * d_tiles + nv_tiles * d_tiles, queue, c.o, PH_DW, PH_DH,
+                    s);
+        continue;
+      }
+      // dH^T = W^T G^T: W's rows are K as they lie, the last ones from the padded copy
+      GemmShape& h = g[0];
+      h.B = h.A;
+      h.ldb = h.lda;
+      h.b_tiled = 2;
+      h.N = (int32_t)L.A_pad;
+      h.n_dev = ctrl;
+      h.A = (const __bf16*)W + v0 * c.d;
+      h.lda = c.d;
+      h.a_tiled = 0;
+      h.a_trans = 2;
+      h.M = c.d;
+      h.m_dev = nullptr;
+      h.a_tail = ws + L.tail;
+      h.a_tail_stage = (int32_t)((c.V / kTailRows * kTailRows - v0) / bf16k::SK);
+      const bool add = e[0].accumulate;
+      e[0].out = (float*)(ws + L.ph);
+      e[0].ldo = L.A_pad;
+      e[0].row_map = nullptr;
+      e[0].accumulate = 0;
+      e[0].part_stride = c.d * L.A_pad;
+      launch_gemm(g, e, 2, row_tiles * d_tiles * L.ph_max + nv_tiles * d_tiles, queue, c.o, PH_DW,
+                  PH_DH, s, L.ph_max);
+      hipLaunchKernelGGL(dh_reduce_kernel, gh, dim3(256), 0, s, (const float*)(ws + L.ph), L.A_pad,
+                         ctrl, (const int32_t*)(ws + L.idx), nv, c.d, device_cu_count(), L.ph_max,
+                         (int32_t)add, dH);
     }
   }
 }
@@ -1055,8 +1151,12 @@ extern "C" int agrl_policy_loss_bwd(int64_t T, int64_t max_act, int32_t d, int32
   Layout L;
   make_layout(T, c.max_act, d, V, dtype, c.o, &L);
   uint8_t* ws = (uint8_t*)workspace;
+  TailCopy tail = {};
+  const int64_t tail0 = V / kTailRows * kTailRows;
+  if (L.w_rows && tail0 < V)
+    tail = TailCopy{(const uint8_t*)W + tail0 * d * 2, V - tail0, ws + L.tail};
   compact(c, L, ws, action_mask, token_id, adv_tok, old_logp, lse, logp, grad_loss, n_norm,
-          nullptr, nullptr, H, err, s);
+          nullptr, nullptr, H, err, s, tail);
   hipLaunchKernelGGL(zero_masked_rows_kernel, dim3((unsigned)(T < 8192 ? T : 8192)), dim3(256), 0,
                      s, T, d, action_mask, dH);
   if (dtype == AGRL_BF16)

@@ -60,3 +60,19 @@ def test_fp32_chunks_accumulate_loose_bound():
     # chunks of 512 columns, the last of 3; dW added to; room for every token
     _case(torch.float32, 1027, 128, 300, T=1500, opt=dict(g_chunk_bytes=2 * 1536 * 4 * 512, dw_accumulate=1),
           max_act=0, dW0=0.25)
+
+
+# bf16 with few action tokens (dH reads W as it lies): one, several and many parts of
+# dH's K; W's last rows a whole stage pair or a remainder of 1, 63, 64, 127; a hidden
+# size that leaves a partial 256-tile; one row of tokens more and less than a tile
+@pytest.mark.parametrize("V,d,n_act", [
+    (1, 64, 1), (127, 64, 255), (129, 128, 256), (2048, 192, 257), (8191, 320, 100),
+    (20031, 128, 300), (50240, 256, 70), (33, 512, 2000)])
+def test_bf16_few_tokens(V, d, n_act):
+    _case(torch.bfloat16, V, d, n_act)
+
+
+def test_bf16_few_tokens_chunks_accumulate_loose_bound():
+    # chunks of 4096 columns, the last of 1; dW added to; room for every token
+    _case(torch.bfloat16, 8193, 320, 130, T=700, opt=dict(g_chunk_bytes=768 * 2 * 4096, dw_accumulate=1),
+          max_act=0, dW0=0.25)
