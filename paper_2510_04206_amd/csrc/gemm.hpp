@@ -307,6 +307,7 @@ struct GemmBatch {
   int32_t cus;        // EpiGrad: compute units, and the most parts K of problem 0
   int32_t split_max;  // may be split into (see dh_split)
   int32_t* queue;     // 8 tile counters, then 8 finished-tile counters, zero at launch
+  int32_t* queue_next;  // the next launch's: zeroed by this one
 };
 
 // Copy schedule of the 16 x 16 loop, per epilogue (measured on the 32B-shaped
@@ -426,6 +427,7 @@ __global__ void __launch_bounds__(GEMM_THREADS)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
+  if (blockIdx.x == 0 && tid < 16) bat.queue_next[tid] = 0;
   const int nq = min(8, (int)gridDim.x);
   const int qi = blockIdx.x % nq;
   int Mp[2], Np[2], Kp[2], tmp[2], tnp[2], totp[2];

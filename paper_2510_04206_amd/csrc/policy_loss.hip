@@ -26,6 +26,12 @@ constexpr int kScanThreads = 256;
 constexpr int kScanPer = kScanTile / kScanThreads;   // 16 tokens per thread
 constexpr int kRowPad = 256;             // compacted rows are padded to the GEMM tile
 constexpr int kMergeRows = 64;         // action tokens per merge block
+constexpr int kMergeWaves = 16;        // waves per merge block
+constexpr int kCompactRows = 256;      // tokens per compaction block
+// words of the control block: action tokens the launches work on (0 when there are more
+// than max_act), that fault's flag, action tokens counted, merge blocks finished; from
+// byte 64 two tile queues of 16 words, which the matrix-core launches use in turn
+enum : int { CTRL_N = 0, CTRL_OVER = 1, CTRL_COUNT = 2, CTRL_MERGED = 3, CTRL_QUEUE = 16 };
 
 __host__ __device__ inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
@@ -50,8 +56,17 @@ __global__ __launch_bounds__(kScanThreads) void scan_count_kernel(int64_t T,
   }
 }
 
-// Single block: exclusive offsets of the scan blocks, the action count, and
-// the max_act check (an overflow zeroes the count and flags the call).
+__device__ __forceinline__ void set_ctrl(int32_t* ctrl, int total, int64_t max_act, int* err) {
+  const bool over = (int64_t)total > max_act;
+  if (over) set_error(err, ERR_MAX_ACT);
+  ctrl[CTRL_N] = over ? 0 : total;
+  ctrl[CTRL_OVER] = over;      // the loss becomes NaN
+  ctrl[CTRL_COUNT] = total;
+  ctrl[CTRL_MERGED] = 0;
+  for (int i = 0; i < 32; ++i) ctrl[CTRL_QUEUE + i] = 0;
+}
+
+// Single block: exclusive offsets of the scan blocks and the control words.
 __global__ __launch_bounds__(1024) void scan_offsets_kernel(int32_t nblk,
                                                             const int32_t* __restrict__ blk_cnt,
                                                             int32_t* blk_off, int32_t* ctrl,
@@ -78,35 +93,29 @@ __global__ __launch_bounds__(1024) void scan_offsets_kernel(int32_t nblk,
     if (threadIdx.x == 1023) carry = before + incl;
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    const int total = carry;
-    if ((int64_t)total > max_act) {
-      set_error(err, ERR_MAX_ACT);
-      ctrl[0] = 0;
-      ctrl[1] = 1;      // loss becomes NaN
-    } else {
-      ctrl[0] = total;
-      ctrl[1] = 0;
-    }
-    ctrl[2] = total;
-    ctrl[3] = 0;        // set by the scatter when an action token's id is out of range
-  }
+  if (threadIdx.x == 0) set_ctrl(ctrl, carry, max_act, err);
 }
 
-struct ScatterArgs {
+// The last rows of W padded with zero rows to kTailRows, for a K extent over W's rows.
+constexpr int kTailRows = 2 * bf16k::SK;
+struct TailCopy {
+  const uint8_t* src;      // nullable
+  int64_t rows;            // rows of src
+  uint8_t* dst;
+};
+
+struct CompactArgs {
   int64_t T;
-  int32_t V;
-  int32_t nblk;
+  int32_t V, d;
   const uint8_t* mask;
   const int32_t* token_id;
   const float* adv_tok;
   const float* old_logp;
   const float* lse_in;      // backward only
   const float* logp_in;     // backward only
-  const int32_t* blk_off;
-  const int32_t* ctrl;
-  int32_t* bad_id;          // ctrl[3]: 1 once an action token's id is out of range
-  int64_t cap;              // rows allocated for compacted arrays
+  const int32_t* blk_off;   // nullable: action tokens before each scan tile, ctrl then set
+  int32_t* ctrl;
+  int64_t max_act;
   int32_t* idx;
   int32_t* y_act;
   float* adv_act;
@@ -126,113 +135,176 @@ struct ScatterArgs {
   int64_t n_norm;
   float inv_temp;
   int* err;
+  const uint8_t* H;
+  uint8_t* H_act;
+  int64_t row_bytes;        // of H
+  float* dH;                // backward only: masked rows zeroed
+  TailCopy tail;
 };
 
-__global__ __launch_bounds__(kScanThreads) void scan_scatter_kernel(ScatterArgs a) {
-  __shared__ int wsum[kScanThreads / 64];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + threadIdx.x * kScanPer;
-  uint8_t m[kScanPer];
-  int c = 0;
-  for (int i = 0; i < kScanPer; ++i) {
-    const int64_t t = base + i;
-    m[i] = (t < a.T) ? (a.mask[t] != 0) : 0;
-    c += m[i];
+// one wave: dst[0, bytes) = src (nullptr: zeros), 16 bytes a lane
+__device__ __forceinline__ void copy_row(u32x4* dst, const u32x4* src, int64_t chunks, int lane) {
+  for (int64_t c = lane; c < chunks; c += 4 * 64) {
+    u32x4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (c + 64 * k < chunks) v[k] = src ? src[c + 64 * k] : u32x4{0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (c + 64 * k < chunks) dst[c + 64 * k] = v[k];
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int incl = c;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(incl, o);
-    if (lane >= o) incl += u;
+}
+
+// nonzero bytes of a word
+__device__ __forceinline__ int nonzero_bytes(uint32_t x) {
+  return __popc((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u);
+}
+
+// Everything the products need of the action tokens, in one launch: their positions,
+// their scalars and H rows compacted (zero rows up to the next multiple of 256), and what
+// masked tokens get (logp = lse = 0; dH row +0).  Block (b, r) covers the tokens
+// [256 b, 256 b + 256); the blocks of one b share its rows out, the first writes the
+// scalars.  Every block counts the action tokens before its own, and all of them, from
+// the mask itself: for a mask of up to 256 KiB (kOneLaunchTokens) that is a few loads of
+// 16 bytes in flight per thread, cheaper than the two launches (5 us each) that it
+// replaces; beyond, scan_count / scan_offsets come first and blk_off is given.  Against
+// the scan, scatter, gather and zero kernels it replaces (forward + backward): 79 and 22 us
+// at T = 2304, d = 3584, 170 and 128 at T = 32768, 370 and 378 at T = 65536, d = 5120, where
+// all that counts is the 1.8 GB of rows.
+__global__ __launch_bounds__(kCompactRows) void compact_kernel(CompactArgs a) {
+  __shared__ int wsum[kCompactRows / 64][3];
+  __shared__ int16_t row_of[kCompactRows];     // action tokens from 0 up, masked from 255 down
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t base = (int64_t)blockIdx.x * kCompactRows, t = base + tid;
+  const bool first = blockIdx.y == 0;
+  const bool in = t < a.T, m = in && a.mask[t] != 0;
+  int before = 0, total = 0;
+  const int64_t from = a.blk_off ? base / kScanTile * kScanTile : 0;
+  const int64_t to = a.blk_off ? base : a.T;
+  if (((uintptr_t)a.mask & 15) == 0) {         // base and from are multiples of 256
+    const int64_t whole = from + (to - from) / 16 * 16;
+#pragma unroll 4
+    for (int64_t c = from + 16 * tid; c < whole; c += 16 * kCompactRows) {
+      const u32x4 v = *(const u32x4*)(a.mask + c);
+      const int n = nonzero_bytes(v[0]) + nonzero_bytes(v[1]) + nonzero_bytes(v[2]) +
+                    nonzero_bytes(v[3]);
+      total += n;
+      before += c < base ? n : 0;
+    }
+    if (whole + tid < to) total += a.mask[whole + tid] != 0;
+  } else {
+#pragma unroll 8
+    for (int64_t c = from + tid; c < to; c += kCompactRows) {
+      const int n = a.mask[c] != 0;
+      total += n;
+      before += c < base ? n : 0;
+    }
   }
-  if (lane == 63) wsum[wave] = incl;
+  for (int o = 32; o >= 1; o >>= 1) {
+    before += __shfl_xor(before, o);
+    total += __shfl_xor(total, o);
+  }
+  const uint64_t act = __ballot(m);
+  const int below = __popcll(act & (((uint64_t)1 << lane) - 1));
+  if (lane == 0) {
+    wsum[wave][0] = before;
+    wsum[wave][1] = total;
+    wsum[wave][2] = __popcll(act);
+  }
   __syncthreads();
-  int pos = a.blk_off[blockIdx.x] + incl - c;
-  for (int w = 0; w < wave; ++w) pos += wsum[w];
-  const bool ok = a.ctrl[1] == 0;
-  const int n_act = a.ctrl[2];
-  const float N = a.n_norm > 0 ? (float)a.n_norm : (float)n_act;
-  for (int i = 0; i < kScanPer; ++i) {
-    const int64_t t = base + i;
-    if (t >= a.T) break;
-    if (!m[i]) {
+  before = total = 0;
+  int rank = below, mine = 0;                  // action tokens of the block
+  for (int w = 0; w < kCompactRows / 64; ++w) {
+    before += wsum[w][0];
+    total += wsum[w][1];
+    rank += w < wave ? wsum[w][2] : 0;
+    mine += wsum[w][2];
+  }
+  if (a.blk_off) {
+    before += a.blk_off[base / kScanTile];
+    total = a.ctrl[CTRL_COUNT];
+  } else if (first && blockIdx.x == 0 && tid == 0) {
+    set_ctrl(a.ctrl, total, a.max_act, a.err);
+  }
+  const bool ok = total <= a.max_act;
+  if (m)
+    row_of[rank] = (int16_t)tid;
+  else
+    row_of[kCompactRows - 1 - (tid - rank)] = (int16_t)tid;
+  __syncthreads();
+
+  if (first && in) {
+    if (!m) {
       if (a.logp_out) {
         a.logp_out[t] = 0.0f;
         a.lse_out[t] = 0.0f;
       }
-      continue;
-    }
-    const int y_in = a.token_id[t];
-    // an id outside the vocabulary poisons the call: the token is kept with
-    // id -1 (it matches no logit), its logp / lse become NaN in the merge, its
-    // logit-gradient row NaN in the backward, and the loss NaN
-    const bool bad = y_in < 0 || y_in >= a.V;
-    const int y = bad ? -1 : y_in;
-    if (bad) {
-      set_error(a.err, ERR_TOKEN_ID);
-      *a.bad_id = 1;
-    }
-    if (ok && pos < a.cap) {
-      a.idx[pos] = (int32_t)t;
-      a.y_act[pos] = y;
-      // the forward-only log-prob pass has neither (its merge then forms a zero surrogate)
-      const float adv = a.adv_tok ? a.adv_tok[t] : 0.0f;
-      const float old = a.old_logp ? a.old_logp[t] : 0.0f;
-      a.adv_act[pos] = adv;
-      a.old_act[pos] = old;
-      if (a.gs_act) {
-        // dL/dlogp of -w (min(rho A, clip(rho) A) - beta KL), w = 1/N or the
-        // token's weight: the unclipped branch's derivative, or 0 where the
-        // clipped branch is the active minimum, plus w beta dKL/dlogp.
-        const float lp = a.logp_in[t];
-        const float rho = expf(lp - old);
-        const bool cut = (adv > 0.0f && rho > 1.0f + a.eps_hi) || (adv < 0.0f && rho < 1.0f - a.eps_lo);
-        const float scale = a.token_weight ? a.grad_loss * a.token_weight[t] : a.grad_loss / N;
-        float g = cut ? 0.0f : -scale * adv * rho;
-        if (a.kl_beta != 0.0f) {
-          // k3: dKL/dl = 1 - exp(r - l) = -expm1(r - l); k1: 1
-          const float dkl = a.kl_est == 1 ? 1.0f : -expm1f(a.ref_logp[t] - lp);
-          g += scale * a.kl_beta * dkl;
+    } else {
+      const int y_in = a.token_id[t];
+      // an id outside the vocabulary poisons the call: the token is kept with
+      // id -1 (it matches no logit), its logp / lse and the loss become NaN in the
+      // merge, its logit-gradient row NaN in the backward
+      const bool bad = y_in < 0 || y_in >= a.V;
+      if (bad) set_error(a.err, ERR_TOKEN_ID);
+      if (ok) {
+        const int pos = before + rank;
+        a.idx[pos] = (int32_t)t;
+        a.y_act[pos] = bad ? -1 : y_in;
+        // the forward-only log-prob pass has neither (its merge then forms a zero surrogate)
+        const float adv = a.adv_tok ? a.adv_tok[t] : 0.0f;
+        const float old = a.old_logp ? a.old_logp[t] : 0.0f;
+        a.adv_act[pos] = adv;
+        a.old_act[pos] = old;
+        if (a.gs_act) {
+          // dL/dlogp of -w (min(rho A, clip(rho) A) - beta KL), w = 1/N or the
+          // token's weight: the unclipped branch's derivative, or 0 where the
+          // clipped branch is the active minimum, plus w beta dKL/dlogp.
+          const float lp = a.logp_in[t];
+          const float rho = expf(lp - old);
+          const bool cut = (adv > 0.0f && rho > 1.0f + a.eps_hi) || (adv < 0.0f && rho < 1.0f - a.eps_lo);
+          const float N = a.n_norm > 0 ? (float)a.n_norm : (float)total;
+          const float scale = a.token_weight ? a.grad_loss * a.token_weight[t] : a.grad_loss / N;
+          float g = cut ? 0.0f : -scale * adv * rho;
+          if (a.kl_beta != 0.0f) {
+            // k3: dKL/dl = 1 - exp(r - l) = -expm1(r - l); k1: 1
+            const float dkl = a.kl_est == 1 ? 1.0f : -expm1f(a.ref_logp[t] - lp);
+            g += scale * a.kl_beta * dkl;
+          }
+          a.lse_act[pos] = a.lse_in[t];
+          a.gs_act[pos] = bad ? NAN : g * a.inv_temp;
+        } else {
+          a.ref_act[pos] = a.ref_logp ? a.ref_logp[t] : 0.0f;
+          a.w_act[pos] = a.token_weight ? a.token_weight[t] : 0.0f;
         }
-        a.lse_act[pos] = a.lse_in[t];
-        a.gs_act[pos] = bad ? NAN : g * a.inv_temp;
-      } else {
-        a.ref_act[pos] = a.ref_logp ? a.ref_logp[t] : 0.0f;
-        a.w_act[pos] = a.token_weight ? a.token_weight[t] : 0.0f;
       }
     }
-    ++pos;
   }
-}
 
-// The last rows of W padded with zero rows to kTailRows, for a K extent over W's rows.
-constexpr int kTailRows = 2 * bf16k::SK;
-struct TailCopy {
-  const uint8_t* src;      // nullable
-  int64_t rows;            // rows of src
-  uint8_t* dst;
-};
-
-// H_act[n] = H[idx[n]] for n < n_act, zero rows up to the next multiple of 256; then
-// the tail copy.
-__global__ __launch_bounds__(256) void gather_rows_kernel(const uint8_t* __restrict__ H,
-                                                          int64_t row_bytes,
-                                                          const int32_t* __restrict__ idx,
-                                                          const int32_t* ctrl, uint8_t* H_act,
-                                                          TailCopy tail) {
-  const int n_act = ctrl[0];
-  const int64_t rows = round_up(n_act, kRowPad);
-  const int64_t chunks = row_bytes / 16;
-  for (int64_t n = blockIdx.x; n < rows + (tail.src ? kTailRows : 0); n += gridDim.x) {
-    const bool t = n >= rows;
-    u32x4* dst = (u32x4*)(t ? tail.dst + (n - rows) * row_bytes : H_act + n * row_bytes);
-    if (t ? n - rows < tail.rows : n < n_act) {
-      const u32x4* src = (const u32x4*)(t ? tail.src + (n - rows) * row_bytes
-                                          : H + (int64_t)idx[n] * row_bytes);
-      for (int64_t c = threadIdx.x; c < chunks; c += blockDim.x) dst[c] = src[c];
-    } else {
-      for (int64_t c = threadIdx.x; c < chunks; c += blockDim.x) dst[c] = u32x4{0, 0, 0, 0};
-    }
+  // rows, one wave each
+  const int R = gridDim.y * (kCompactRows / 64), r = blockIdx.y * (kCompactRows / 64) + wave;
+  const int64_t chunks = a.row_bytes / 16;
+  if (ok)
+    for (int i = r; i < mine; i += R)
+      copy_row((u32x4*)(a.H_act + (before + i) * a.row_bytes),
+               (const u32x4*)(a.H + (base + row_of[i]) * a.row_bytes), chunks, lane);
+  if (a.dH) {
+    const int masked = (int)min((int64_t)kCompactRows, a.T - base) - mine;
+    // (the threads past T come last in the masked list)
+    for (int i = r; i < masked; i += R)
+      copy_row((u32x4*)(a.dH + (base + row_of[kCompactRows - 1 - i]) * a.d), nullptr, a.d / 4,
+               lane);
   }
+  // zero rows after the last action token, and the tail copy
+  const int64_t waves = (int64_t)gridDim.x * R, w = (int64_t)blockIdx.x * R + r;
+  const int n_act = ok ? total : 0;
+  const int64_t pad = round_up(n_act, kRowPad) - n_act;
+  for (int64_t i = w; i < pad; i += waves)
+    copy_row((u32x4*)(a.H_act + (n_act + i) * a.row_bytes), nullptr, chunks, lane);
+  if (a.tail.src)
+    for (int64_t i = w; i < kTailRows; i += waves)
+      copy_row((u32x4*)(a.tail.dst + i * a.row_bytes),
+               i < a.tail.rows ? (const u32x4*)(a.tail.src + i * a.row_bytes) : nullptr, chunks,
+               lane);
 }
 
 // dst = src^T, stage-tiled (tiled_index, K = r padded to ld_dst); rows r in
@@ -281,7 +353,7 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
 
 // ------------------------------------------------------------------ forward epilogue
 struct MergeArgs {
-  const int32_t* ctrl;
+  int32_t* ctrl;
   int32_t tiles_v;
   const f32x2* part;
   int64_t ld_part;
@@ -296,27 +368,47 @@ struct MergeArgs {
   float kl_beta;
   int32_t kl_est;
   int32_t weighted;        // loss partials are w_n f_n (else f_n, divided by N at the end)
+  int64_t n_norm;
   float* logp_out;
   float* lse_out;
   double* blk_sum;
-  long long* blk_clip;     // [2 * blocks]
+  unsigned long long* blk_clip;     // [2 * blocks]
+  float* loss;             // nullptr: log-probs only
+  int64_t* n_clip;
 };
 
-// 64 action tokens per block.  Each of the 4 waves folds a quarter of the
-// vocabulary-tile partials of its lane's token with the online log-sum-exp
-// update; wave 0 combines the four, then forms logp, rho and the clipped
-// surrogate and writes the block's fixed-order partial sums.
-__global__ __launch_bounds__(256) void merge_loss_kernel(MergeArgs a) {
-  __shared__ f32x2 wpart[4][kMergeRows];
-  const int n_act = a.ctrl[0];
+// (max, sum of exp) joined by another; an empty sum carries no weight whatever its max
+__device__ __forceinline__ float mass(float sum, float at, float to) {
+  return sum == 0.0f ? 0.0f : sum * expf(at - to);
+}
+
+// 64 action tokens per block.  Each of the 16 waves folds a sixteenth of the
+// vocabulary-tile partials of its lane's token, eight loads in flight (what bounds the
+// kernel is their latency: at V = 152064, with 4 waves and one load at a time, 74 us at 150
+// tokens and 86 at 22793; now 14 and 41); wave 0
+// combines them, then forms logp, rho and the clipped surrogate and writes the block's
+// fixed-order partial sums.  The block that finishes last adds those in block order.
+__global__ __launch_bounds__(64 * kMergeWaves) void merge_loss_kernel(MergeArgs a) {
+  constexpr int U = 8;
+  __shared__ f32x2 wpart[kMergeWaves][kMergeRows];
+  const int n_act = a.ctrl[CTRL_N];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = blockIdx.x * kMergeRows + lane;
   float m = -INFINITY, s = 0.0f;
   if (n < n_act) {
-    for (int t = wave; t < a.tiles_v; t += 4) {
-      const f32x2 p = a.part[(int64_t)t * a.ld_part + n];
-      const float mn = fmaxf(m, p.x);
-      s = s * expf(m - mn) + p.y * expf(p.x - mn);
+    for (int t = wave; t < a.tiles_v; t += U * kMergeWaves) {
+      f32x2 p[U];
+      float mn = m;
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int tk = t + k * kMergeWaves;
+        p[k] = tk < a.tiles_v ? a.part[(int64_t)tk * a.ld_part + n] : f32x2{-INFINITY, 0.0f};
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) mn = fmaxf(mn, p[k].x);
+      s = mass(s, m, mn);
+#pragma unroll
+      for (int k = 0; k < U; ++k) s += mass(p[k].y, p[k].x, mn);
       m = mn;
     }
   }
@@ -327,10 +419,9 @@ __global__ __launch_bounds__(256) void merge_loss_kernel(MergeArgs a) {
   long long hi = 0, lo = 0;
   if (n < n_act) {
     float mm = -INFINITY;
-    for (int w = 0; w < 4; ++w) mm = fmaxf(mm, wpart[w][lane].x);
+    for (int w = 0; w < kMergeWaves; ++w) mm = fmaxf(mm, wpart[w][lane].x);
     float sum = 0.0f;
-    for (int w = 0; w < 4; ++w)
-      if (wpart[w][lane].y > 0.0f) sum += wpart[w][lane].y * expf(wpart[w][lane].x - mm);
+    for (int w = 0; w < kMergeWaves; ++w) sum += mass(wpart[w][lane].y, wpart[w][lane].x, mm);
     const bool bad = a.y_act[n] < 0;
     const float lse = bad ? NAN : mm + logf(sum);
     const float logp = bad ? NAN : a.zy[n] - lse;
@@ -344,11 +435,45 @@ __global__ __launch_bounds__(256) void merge_loss_kernel(MergeArgs a) {
       f -= a.kl_beta * (a.kl_est == 1 ? -u : expm1f(u) - u);
     }
     sv = a.weighted ? (double)a.w_act[n] * (double)f : (double)f;
+    if (bad) sv = NAN;
     hi = (A > 0.0f && rho > 1.0f + a.eps_hi);
     lo = (A < 0.0f && rho < 1.0f - a.eps_lo);
     const int t = a.idx[n];
     a.logp_out[t] = logp;
     a.lse_out[t] = lse;
+  }
+  if (!a.loss) return;
+  for (int o = 32; o >= 1; o >>= 1) {
+    sv += __shfl_xor(sv, o);
+    hi += __shfl_xor(hi, o);
+    lo += __shfl_xor(lo, o);
+  }
+  // blocks run on XCDs whose L2 caches are not coherent: sums are written and read at
+  // device scope, the counter orders them
+  unsigned long long* sums = (unsigned long long*)a.blk_sum;
+  int done = 0;
+  if (lane == 0) {
+    const int b = blockIdx.x;
+    __hip_atomic_store(sums + b, __builtin_bit_cast(unsigned long long, sv), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.blk_clip + 2 * b, (unsigned long long)hi, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.blk_clip + 2 * b + 1, (unsigned long long)lo, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    done = __hip_atomic_fetch_add(a.ctrl + CTRL_MERGED, 1, __ATOMIC_ACQ_REL,
+                                  __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (__shfl(done, 0) != (int)gridDim.x - 1) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  sv = 0.0;
+  hi = lo = 0;
+  for (int b = lane; b < (int)gridDim.x; b += 64) {
+    sv += __builtin_bit_cast(double, __hip_atomic_load(sums + b, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT));
+    hi += (long long)__hip_atomic_load(a.blk_clip + 2 * b, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+    lo += (long long)__hip_atomic_load(a.blk_clip + 2 * b + 1, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
   }
   for (int o = 32; o >= 1; o >>= 1) {
     sv += __shfl_xor(sv, o);
@@ -356,47 +481,12 @@ __global__ __launch_bounds__(256) void merge_loss_kernel(MergeArgs a) {
     lo += __shfl_xor(lo, o);
   }
   if (lane == 0) {
-    a.blk_sum[blockIdx.x] = sv;
-    a.blk_clip[2 * blockIdx.x] = hi;
-    a.blk_clip[2 * blockIdx.x + 1] = lo;
-  }
-}
-
-__global__ __launch_bounds__(256) void finalize_loss_kernel(int32_t nblk, const double* blk_sum,
-                                                            const long long* blk_clip,
-                                                            const int32_t* ctrl, int64_t n_norm,
-                                                            int32_t weighted, float* loss,
-                                                            int64_t* n_clip) {
-  __shared__ double ssum[256];
-  __shared__ long long shi[256], slo[256];
-  double s = 0.0;
-  long long hi = 0, lo = 0;
-  for (int b = threadIdx.x; b < nblk; b += 256) {
-    s += blk_sum[b];
-    hi += blk_clip[2 * b];
-    lo += blk_clip[2 * b + 1];
-  }
-  ssum[threadIdx.x] = s;
-  shi[threadIdx.x] = hi;
-  slo[threadIdx.x] = lo;
-  __syncthreads();
-  for (int w = 128; w >= 1; w >>= 1) {
-    if (threadIdx.x < w) {
-      ssum[threadIdx.x] += ssum[threadIdx.x + w];
-      shi[threadIdx.x] += shi[threadIdx.x + w];
-      slo[threadIdx.x] += slo[threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const int n_act = ctrl[0];
-    const double N = n_norm > 0 ? (double)n_norm : (double)n_act;
-    float L = weighted ? (float)(-ssum[0]) : (N > 0 ? (float)(-ssum[0] / N) : 0.0f);
-    if (ctrl[1] || ctrl[3]) L = NAN;
-    *loss = L;
-    if (n_clip) {
-      n_clip[0] = shi[0];
-      n_clip[1] = slo[0];
+    const double N = a.n_norm > 0 ? (double)a.n_norm : (double)n_act;
+    const float L = a.weighted ? (float)(-sv) : (N > 0 ? (float)(-sv / N) : 0.0f);
+    *a.loss = a.ctrl[CTRL_OVER] ? NAN : L;
+    if (a.n_clip) {
+      a.n_clip[0] = hi;
+      a.n_clip[1] = lo;
     }
   }
 }
@@ -406,16 +496,6 @@ __global__ void zero_loss_kernel(float* loss, int64_t* n_clip) {
   if (n_clip) {
     n_clip[0] = 0;
     n_clip[1] = 0;
-  }
-}
-
-__global__ __launch_bounds__(256) void zero_masked_rows_kernel(int64_t T, int32_t d,
-                                                               const uint8_t* __restrict__ mask,
-                                                               float* dH) {
-  for (int64_t t = blockIdx.x; t < T; t += gridDim.x) {
-    if (mask[t]) continue;
-    f32x4* row = (f32x4*)(dH + t * d);
-    for (int c = threadIdx.x; c < d / 4; c += blockDim.x) row[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 }
 
@@ -635,19 +715,16 @@ int validate(const char* fn, int64_t T, int64_t max_act, int32_t d, int32_t V, i
 
 enum Phase { PH_FWD = 0, PH_RECOMPUTE = 1, PH_DW = 2, PH_DH = 3 };
 
-__global__ void zero_queue_kernel(int32_t* q) {
-  if (threadIdx.x < 16) q[threadIdx.x] = 0;
-}
-
 void record(const agrl_options& o, int event, hipStream_t s) {
   if (o.phase_events) hipEventRecord(((hipEvent_t*)o.phase_events)[event], s);
 }
 
-// Launch n (1 or 2) independent bf16 products: one persistent launch with its tile
-// queues reset first.  The phase's events bracket the whole launch (a second phase
+// Launch n (1 or 2) independent bf16 products: one persistent launch.  `launch` counts
+// the call's launches: they use the control block's two tile queues in turn, each
+// clearing the next one's (the first is clear).  The phase's events bracket the whole launch (a second phase
 // slot, when given, is recorded empty).
 template <class Epi>
-void launch_gemm(const GemmShape* g, const Epi* e, int n, int max_tiles, int32_t* queue,
+void launch_gemm(const GemmShape* g, const Epi* e, int n, int max_tiles, int32_t* ctrl, int launch,
                  const agrl_options& o, Phase ph, int ph2, hipStream_t s, int split_max = 1) {
   int grid = device_cu_count();
   if (max_tiles < grid) grid = max_tiles < 1 ? 1 : max_tiles;
@@ -657,10 +734,10 @@ void launch_gemm(const GemmShape* g, const Epi* e, int n, int max_tiles, int32_t
     b.e[i] = e[i < n ? i : 0];
   }
   b.n = n;
-  b.queue = queue;
+  b.queue = ctrl + CTRL_QUEUE + 16 * (launch & 1);
+  b.queue_next = ctrl + CTRL_QUEUE + 16 * (~launch & 1);
   b.cus = device_cu_count();
   b.split_max = split_max;
-  hipLaunchKernelGGL(zero_queue_kernel, dim3(1), dim3(64), 0, s, queue);
   record(o, 2 * ph, s);
   // The bf16 store launch is the backward's dH + dW: its operands are
   // stage-tiled, dW reads G transposed, and both K extents are whole stage
@@ -703,30 +780,28 @@ void launch_logits_f32(const f32k::LogitsArgs& g, int64_t rows, hipStream_t s) {
                        dim3(f32k::THREADS), 0, s, g);
 }
 
-int compact(const Common& c, const Layout& L, uint8_t* ws, const uint8_t* mask,
-            const int32_t* token_id, const float* adv, const float* old, const float* lse_in,
-            const float* logp_in, float grad_loss, int64_t n_norm, float* logp_out,
-            float* lse_out, const void* H, int* err, hipStream_t s, TailCopy tail = {}) {
+// Up to this many tokens the compaction is one launch.
+constexpr int64_t kOneLaunchTokens = (int64_t)1 << 18;
+
+void compact(const Common& c, const Layout& L, uint8_t* ws, const uint8_t* mask,
+             const int32_t* token_id, const float* adv, const float* old, const float* lse_in,
+             const float* logp_in, float grad_loss, int64_t n_norm, float* logp_out,
+             float* lse_out, const void* H, int* err, hipStream_t s, float* dH = nullptr,
+             TailCopy tail = {}) {
   int32_t* ctrl = (int32_t*)(ws + L.ctrl);
-  hipLaunchKernelGGL(scan_count_kernel, dim3(L.nblk), dim3(kScanThreads), 0, s, c.T, mask,
-                     (int32_t*)(ws + L.blk_cnt));
-  hipLaunchKernelGGL(scan_offsets_kernel, dim3(1), dim3(1024), 0, s, L.nblk,
-                     (const int32_t*)(ws + L.blk_cnt), (int32_t*)(ws + L.blk_off), ctrl,
-                     c.max_act, err);
-  ScatterArgs a;
+  CompactArgs a;
   a.T = c.T;
   a.V = c.V;
-  a.nblk = L.nblk;
+  a.d = c.d;
   a.mask = mask;
   a.token_id = token_id;
   a.adv_tok = adv;
   a.old_logp = old;
   a.lse_in = lse_in;
   a.logp_in = logp_in;
-  a.blk_off = (const int32_t*)(ws + L.blk_off);
+  a.blk_off = nullptr;
   a.ctrl = ctrl;
-  a.bad_id = ctrl + 3;
-  a.cap = L.A_pad;
+  a.max_act = c.max_act;
   a.idx = (int32_t*)(ws + L.idx);
   a.y_act = (int32_t*)(ws + L.y_act);
   a.adv_act = (float*)(ws + L.adv_act);
@@ -747,13 +822,25 @@ int compact(const Common& c, const Layout& L, uint8_t* ws, const uint8_t* mask,
   a.n_norm = n_norm;
   a.inv_temp = c.inv_temp;
   a.err = err;
-  hipLaunchKernelGGL(scan_scatter_kernel, dim3(L.nblk), dim3(kScanThreads), 0, s, a);
-  const int64_t rows = L.A_pad + (tail.src ? kTailRows : 0);
-  const int grid = (int)(rows < 4096 ? rows : 4096);
-  hipLaunchKernelGGL(gather_rows_kernel, dim3(grid), dim3(256), 0, s, (const uint8_t*)H,
-                     (int64_t)c.d * L.esize, (const int32_t*)(ws + L.idx), (const int32_t*)ctrl,
-                     ws + L.H_act, tail);
-  return AGRL_OK;
+  a.H = (const uint8_t*)H;
+  a.H_act = ws + L.H_act;
+  a.row_bytes = (int64_t)c.d * L.esize;
+  a.dH = dH;
+  a.tail = tail;
+  if (c.T > kOneLaunchTokens) {
+    hipLaunchKernelGGL(scan_count_kernel, dim3(L.nblk), dim3(kScanThreads), 0, s, c.T, mask,
+                       (int32_t*)(ws + L.blk_cnt));
+    hipLaunchKernelGGL(scan_offsets_kernel, dim3(1), dim3(1024), 0, s, L.nblk,
+                       (const int32_t*)(ws + L.blk_cnt), (int32_t*)(ws + L.blk_off), ctrl,
+                       c.max_act, err);
+    a.blk_off = (const int32_t*)(ws + L.blk_off);
+  }
+  // about eight blocks a compute unit, up to 64 for the same tokens
+  const int64_t blocks = cdiv<int64_t>(c.T, kCompactRows);
+  const int64_t share = 8 * device_cu_count() / blocks;
+  hipLaunchKernelGGL(compact_kernel,
+                     dim3((unsigned)blocks, (unsigned)(share < 1 ? 1 : share > 64 ? 64 : share)),
+                     dim3(kCompactRows), 0, s, a);
 }
 
 void fwd_gemm_bf16(const Common& c, const Layout& L, uint8_t* ws, const void* W, hipStream_t s) {
@@ -776,7 +863,37 @@ void fwd_gemm_bf16(const Common& c, const Layout& L, uint8_t* ws, const void* W,
   e.ld_part = L.A_pad;
   e.zy = (float*)(ws + L.zy);
   e.scale = c.inv_temp;
-  launch_gemm(&g, &e, 1, max_tiles, (int32_t*)(ws + L.ctrl + 64), c.o, PH_FWD, -1, s);
+  launch_gemm(&g, &e, 1, max_tiles, (int32_t*)(ws + L.ctrl), 0, c.o, PH_FWD, -1, s);
+}
+
+// loss == nullptr: lse and logp, formed exactly as in the policy-loss forward
+void merge(const Common& c, const Layout& L, uint8_t* ws, int64_t n_norm, float* loss, float* logp,
+           float* lse, int64_t* n_clip, hipStream_t s) {
+  MergeArgs m;
+  m.ctrl = (int32_t*)(ws + L.ctrl);
+  m.tiles_v = L.tiles_v;
+  m.part = (const f32x2*)(ws + L.part);
+  m.ld_part = L.A_pad;
+  m.zy = (const float*)(ws + L.zy);
+  m.y_act = (const int32_t*)(ws + L.y_act);
+  m.old_act = (const float*)(ws + L.old_act);
+  m.adv_act = (const float*)(ws + L.adv_act);
+  m.idx = (const int32_t*)(ws + L.idx);
+  m.eps_lo = c.eps_lo;
+  m.eps_hi = c.eps_hi;
+  m.ref_act = (const float*)(ws + L.ref_act);
+  m.w_act = (const float*)(ws + L.w_act);
+  m.kl_beta = c.o.kl_beta;
+  m.kl_est = c.o.kl_estimator;
+  m.weighted = c.o.token_weight != nullptr;
+  m.n_norm = n_norm;
+  m.logp_out = logp;
+  m.lse_out = lse;
+  m.blk_sum = (double*)(ws + L.blk_sum);
+  m.blk_clip = (unsigned long long*)(ws + L.blk_clip);
+  m.loss = loss;
+  m.n_clip = n_clip;
+  hipLaunchKernelGGL(merge_loss_kernel, dim3(L.merge_blocks), dim3(64 * kMergeWaves), 0, s, m);
 }
 
 f32k::LogitsArgs logits_args_f32(const Common& c, const Layout& L, uint8_t* ws, const void* W,
@@ -902,8 +1019,8 @@ void bwd_gemms_bf16(const Common& c, const Layout& L, uint8_t* ws, const void* W
       e.ldg = L.A_pad;
       e.scale = c.inv_temp;
       e.col0 = (int32_t)v0;
-      launch_gemm(&g, &e, 1, row_tiles * nv_tiles, (int32_t*)(ws + L.ctrl + 64), c.o,
-                  PH_RECOMPUTE, -1, s);
+      launch_gemm(&g, &e, 1, row_tiles * nv_tiles, (int32_t*)(ws + L.ctrl), 0, c.o, PH_RECOMPUTE,
+                  -1, s);
     }
     {  // dH[idx] (+)= G W[v0 : v0 + nv] (K = the chunk's vocabulary columns) and
        // dW[v0 : v0 + nv] = G^T H_act (K = action tokens), one launch, dH first:
@@ -941,10 +1058,10 @@ void bwd_gemms_bf16(const Common& c, const Layout& L, uint8_t* ws, const void* W
       e[1].ldo = c.d;
       e[1].row_map = nullptr;
       e[1].accumulate = c.o.dw_accumulate;
-      int32_t* queue = (int32_t*)(ws + L.ctrl + 64);
+      int32_t* queue = (int32_t*)(ws + L.ctrl);
       if (!L.w_rows) {
         const EpiStore es[2] = {e[0], e[1]};
-        launch_gemm(g, es, 2, row_tiles * d_tiles + nv_tiles * d_tiles, queue, c.o, PH_DW, PH_DH,
+        launch_gemm(g, es, 2, row_tiles * d_tiles + nv_tiles * d_tiles, queue, 1, c.o, PH_DW, PH_DH,
                     s);
         continue;
       }
@@ -969,7 +1086,7 @@ void bwd_gemms_bf16(const Common& c, const Layout& L, uint8_t* ws, const void* W
       e[0].row_map = nullptr;
       e[0].accumulate = 0;
       e[0].part_stride = c.d * L.A_pad;
-      launch_gemm(g, e, 2, row_tiles * d_tiles * L.ph_max + nv_tiles * d_tiles, queue, c.o, PH_DW,
+      launch_gemm(g, e, 2, row_tiles * d_tiles * L.ph_max + nv_tiles * d_tiles, queue, 1, c.o, PH_DW,
                   PH_DH, s, L.ph_max);
       hipLaunchKernelGGL(dh_reduce_kernel, gh, dim3(256), 0, s, (const float*)(ws + L.ph), L.A_pad,
                          ctrl, (const int32_t*)(ws + L.idx), nv, c.d, device_cu_count(), L.ph_max,
@@ -1029,32 +1146,7 @@ extern "C" int agrl_policy_loss_fwd(int64_t T, int64_t max_act, int32_t d, int32
   compact(c, L, ws, action_mask, token_id, adv_tok, old_logp, nullptr, nullptr, 0.0f, n_norm,
           logp, lse, H, err, s);
   fwd_gemm(c, L, ws, W, s);
-  MergeArgs m;
-  m.ctrl = (const int32_t*)(ws + L.ctrl);
-  m.tiles_v = L.tiles_v;
-  m.part = (const f32x2*)(ws + L.part);
-  m.ld_part = L.A_pad;
-  m.zy = (const float*)(ws + L.zy);
-  m.y_act = (const int32_t*)(ws + L.y_act);
-  m.old_act = (const float*)(ws + L.old_act);
-  m.adv_act = (const float*)(ws + L.adv_act);
-  m.idx = (const int32_t*)(ws + L.idx);
-  m.eps_lo = c.eps_lo;
-  m.eps_hi = c.eps_hi;
-  m.ref_act = (const float*)(ws + L.ref_act);
-  m.w_act = (const float*)(ws + L.w_act);
-  m.kl_beta = c.o.kl_beta;
-  m.kl_est = c.o.kl_estimator;
-  m.weighted = c.o.token_weight != nullptr;
-  m.logp_out = logp;
-  m.lse_out = lse;
-  m.blk_sum = (double*)(ws + L.blk_sum);
-  m.blk_clip = (long long*)(ws + L.blk_clip);
-  hipLaunchKernelGGL(merge_loss_kernel, dim3(L.merge_blocks), dim3(256), 0, s, m);
-  hipLaunchKernelGGL(finalize_loss_kernel, dim3(1), dim3(256), 0, s, L.merge_blocks,
-                     (const double*)(ws + L.blk_sum), (const long long*)(ws + L.blk_clip),
-                     (const int32_t*)(ws + L.ctrl), n_norm, (int32_t)(c.o.token_weight != nullptr),
-                     loss, n_clip);
+  merge(c, L, ws, n_norm, loss, logp, lse, n_clip, s);
   return hip_status(hipGetLastError());
 }
 
@@ -1091,30 +1183,7 @@ extern "C" int agrl_token_logprob(int64_t T, int64_t max_act, int32_t d, int32_t
   compact(c, L, ws, action_mask, token_id, nullptr, nullptr, nullptr, nullptr, 0.0f, 0, logp,
           lse, H, err, s);
   fwd_gemm(c, L, ws, W, s);
-  // the loss merge with zero advantages: lse and logp are formed exactly as in
-  // the policy-loss forward; its (zero) surrogate partials are not finalised
-  MergeArgs m;
-  m.ctrl = (const int32_t*)(ws + L.ctrl);
-  m.tiles_v = L.tiles_v;
-  m.part = (const f32x2*)(ws + L.part);
-  m.ld_part = L.A_pad;
-  m.zy = (const float*)(ws + L.zy);
-  m.y_act = (const int32_t*)(ws + L.y_act);
-  m.old_act = (const float*)(ws + L.old_act);
-  m.adv_act = (const float*)(ws + L.adv_act);
-  m.idx = (const int32_t*)(ws + L.idx);
-  m.eps_lo = 0.0f;
-  m.eps_hi = 0.0f;
-  m.ref_act = (const float*)(ws + L.ref_act);
-  m.w_act = (const float*)(ws + L.w_act);
-  m.kl_beta = 0.0f;
-  m.kl_est = 0;
-  m.weighted = 0;
-  m.logp_out = logp;
-  m.lse_out = lse;
-  m.blk_sum = (double*)(ws + L.blk_sum);
-  m.blk_clip = (long long*)(ws + L.blk_clip);
-  hipLaunchKernelGGL(merge_loss_kernel, dim3(L.merge_blocks), dim3(256), 0, s, m);
+  merge(c, L, ws, 0, nullptr, logp, lse, nullptr, s);
   return hip_status(hipGetLastError());
 }
 
@@ -1156,9 +1225,7 @@ extern "C" int agrl_policy_loss_bwd(int64_t T, int64_t max_act, int32_t d, int32
   if (L.w_rows && tail0 < V)
     tail = TailCopy{(const uint8_t*)W + tail0 * d * 2, V - tail0, ws + L.tail};
   compact(c, L, ws, action_mask, token_id, adv_tok, old_logp, lse, logp, grad_loss, n_norm,
-          nullptr, nullptr, H, err, s, tail);
-  hipLaunchKernelGGL(zero_masked_rows_kernel, dim3((unsigned)(T < 8192 ? T : 8192)), dim3(256), 0,
-                     s, T, d, action_mask, dH);
+          nullptr, nullptr, H, err, s, dH, tail);
   if (dtype == AGRL_BF16)
     bwd_gemms_bf16(c, L, ws, W, dH, dW, s);
   else

@@ -76,3 +76,42 @@ def test_bf16_few_tokens_chunks_accumulate_loose_bound():
     # chunks of 4096 columns, the last of 1; dW added to; room for every token
     _case(torch.bfloat16, 8193, 320, 130, T=700, opt=dict(g_chunk_bytes=768 * 2 * 4096, dw_accumulate=1),
           max_act=0, dW0=0.25)
+
+
+# compaction: tokens before, at and after a block of 256, a mask that starts off a 16-byte
+# boundary, more tokens than one launch handles (2^18)
+@pytest.mark.parametrize("T,offset", [(1, 0), (255, 3), (256, 0), (257, 1), (4097, 16), (5000, 7),
+                                      ((1 << 18) + 333, 0), ((1 << 18) + 77, 5)])
+def test_compaction(T, offset):
+    import paper_2510_04206_amd as P
+    rng = np.random.default_rng(T)
+    d, V = 64, 300
+    m = np.zeros(T + offset, np.uint8)
+    m[offset:] = rng.random(T) < (0.4 if T < 10000 else 0.004)
+    m[-1] = 1
+    m[offset:] *= rng.integers(1, 256, T).astype(np.uint8)      # any nonzero byte is an action
+    log(f"compaction T={T} offset={offset}")
+    mask = torch.from_numpy(m).cuda()[offset:]
+    g = torch.Generator(device="cuda").manual_seed(T)
+    H = torch.randn((T, d), generator=g, device="cuda").bfloat16()
+    W = torch.randn((V, d), generator=g, device="cuda").bfloat16()
+    y = torch.randint(0, V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    act = mask != 0
+    lp = P.TokenLogprob(T, d, V, H.dtype, max_act=int(act.sum()))
+    logp, lse = lp(H, W, y, mask)
+    assert P.agrl_get_device_error() == 0
+    z = H[act].double() @ W.double().t()
+    want = torch.zeros(2, T, dtype=torch.float64, device="cuda")
+    want[0, act] = torch.log_softmax(z, 1).gather(1, y[act].long()[:, None])[:, 0]
+    want[1, act] = z.logsumexp(1)
+    assert (logp.double() - want[0]).abs().max() < 5e-5 and (lse.double() - want[1]).abs().max() < 2e-5
+    adv = torch.randn(T, generator=g, device="cuda")
+    pl = P.PolicyLoss(T, d, V, H.dtype, max_act=int(act.sum()))
+    pl.dH.fill_(float("nan"))
+    pl.forward(H, W, y, mask, adv, want[0].float())
+    dH, _ = pl.backward(H, W, y, mask, adv, want[0].float())
+    assert (dH[~act] == 0).all() and not torch.signbit(dH[~act]).any()
+    p = torch.softmax(z, 1)
+    p.scatter_add_(1, y[act].long()[:, None], torch.full((int(act.sum()), 1), -1.0, device="cuda").double())
+    ref = (adv[act].double() / act.sum())[:, None] * p @ W.double()
+    assert ((dH[act].double() - ref).norm() / ref.norm()) < 4e-3
