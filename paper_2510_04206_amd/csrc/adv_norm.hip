@@ -19,58 +19,99 @@ __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
   if (i < n) p[i] = v;
 }
 
-// n_tau: each lane walks kCountPerLane consecutive tokens, adding runs of the
-// same trajectory; the wave then merges lanes that end on the same trajectory.
-// Integer atomics are exact, so the counts do not depend on the order.
-// VEC: traj_id and mask are 16-byte aligned, and a lane's whole run of tokens
-// is read with four 16-byte id loads and one 16-byte mask load.
-template <bool VEC>
-__global__ __launch_bounds__(256) void count_kernel(int64_t T_g, int32_t n_traj,
-                                                    const int32_t* __restrict__ traj_id,
-                                                    const uint8_t* __restrict__ mask,
-                                                    int32_t* act_count, int* err) {
-  static_assert(kCountPerLane == 16, "one 16-byte mask load per lane");
-  const int64_t t0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * kCountPerLane;
+// n_tau: a lane walks kCountPerLane consecutive tokens, adding each run of one
+// trajectory's action tokens at its end; the last run is left in (cur, cnt).  Integer
+// atomics are exact, so the counts do not depend on the order.
+struct Run {
   int cur = -1, cnt = 0;
-  auto token = [&](int id, bool m) {
+  __device__ __forceinline__ void token(int id, bool m, int32_t n_traj, int32_t* count, int* err) {
     if (id >= n_traj) {
       set_error(err, ERR_TRAJ_ID);
       return;
     }
     if (id < 0 || !m) return;
     if (id != cur) {
-      if (cnt) atomicAdd(&act_count[cur], cnt);
+      if (cnt) atomicAdd(&count[cur], cnt);
       cur = id;
       cnt = 0;
     }
     ++cnt;
-  };
-  if (VEC && t0 + kCountPerLane <= T_g) {
-    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    i32x4 ids[4];
+  }
+};
+
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+
+// The ids and mask bytes of a lane's tokens [t0, t0 + 16): VEC (both arrays 16-byte
+// aligned) with four 16-byte id loads and one 16-byte mask load.  Tokens past T_g are
+// padding.
+template <bool VEC>
+struct Tokens {
+  i32x4 ids[4];
+  u32x4 m;
+  __device__ __forceinline__ void load(int64_t t0, int64_t T_g, const int32_t* __restrict__ traj_id,
+                                       const uint8_t* __restrict__ mask) {
+    static_assert(kCountPerLane == 16, "one 16-byte mask load per lane");
+    if (VEC && t0 + kCountPerLane <= T_g) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) ids[k] = *(const i32x4*)(traj_id + t0 + 4 * k);
-    const u32x4 mw = *(const u32x4*)(mask + t0);
+      for (int k = 0; k < 4; ++k) ids[k] = *(const i32x4*)(traj_id + t0 + 4 * k);
+      m = *(const u32x4*)(mask + t0);
+      return;
+    }
+    m = u32x4{0, 0, 0, 0};
 #pragma unroll
-    for (int i = 0; i < kCountPerLane; ++i)
-      token(ids[i >> 2][i & 3], (mw[i >> 2] >> (8 * (i & 3))) & 0xFFu);
-  } else {
     for (int i = 0; i < kCountPerLane; ++i) {
-      const int64_t t = t0 + i;
-      if (t >= T_g) break;
-      token(traj_id[t], mask[t] != 0);
+      const bool in = t0 + i < T_g;
+      ids[i >> 2][i & 3] = in ? traj_id[t0 + i] : -1;
+      m[i >> 2] |= (in && mask[t0 + i] ? 1u : 0u) << (8 * (i & 3));
     }
   }
+  __device__ __forceinline__ Run count(int32_t n_traj, int32_t* count, int* err) const {
+    Run r;
+#pragma unroll
+    for (int i = 0; i < kCountPerLane; ++i)
+      r.token(ids[i >> 2][i & 3], (m[i >> 2] >> (8 * (i & 3))) & 0xFFu, n_traj, count, err);
+    return r;
+  }
+};
+
+// A wave's tokens from t0 (each lane's first) into counters in memory: lanes that end on
+// the same trajectory are merged into one atomic.
+template <bool VEC>
+__device__ __forceinline__ void count_tokens(int64_t t0, int64_t T_g, int32_t n_traj,
+                                             const int32_t* traj_id, const uint8_t* mask,
+                                             int32_t* count, int* err) {
+  Tokens<VEC> tok;
+  tok.load(t0, T_g, traj_id, mask);
+  Run r = tok.count(n_traj, count, err);
   const int lane = threadIdx.x & 63;
   for (;;) {
-    const uint64_t pend = __ballot(cnt > 0);
+    const uint64_t pend = __ballot(r.cnt > 0);
     if (!pend) break;
     const int leader = __ffsll((unsigned long long)pend) - 1;
-    const int lid = __shfl(cur, leader);
-    int mine = (cnt > 0 && cur == lid) ? cnt : 0;
+    const int lid = __shfl(r.cur, leader);
+    int mine = (r.cnt > 0 && r.cur == lid) ? r.cnt : 0;
     for (int o = 32; o >= 1; o >>= 1) mine += __shfl_xor(mine, o);
-    if (lane == leader) atomicAdd(&act_count[lid], mine);
-    if (cnt > 0 && cur == lid) cnt = 0;
+    if (lane == leader) atomicAdd(&count[lid], mine);
+    if (r.cnt > 0 && r.cur == lid) r.cnt = 0;
+  }
+}
+
+// All T_g tokens by one workgroup of 1024 threads into counters in LDS, two batches of
+// loads in flight.
+template <bool VEC>
+__device__ __forceinline__ void count_in_lds(int64_t T_g, int32_t n_traj, const int32_t* traj_id,
+                                             const uint8_t* mask, int32_t* count, int* err) {
+  constexpr int B = 2;
+  constexpr int64_t step = 1024 * kCountPerLane;
+  for (int64_t t0 = (int64_t)threadIdx.x * kCountPerLane; t0 < T_g; t0 += B * step) {
+    Tokens<VEC> tok[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) tok[b].load(t0 + b * step, T_g, traj_id, mask);
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const Run r = tok[b].count(n_traj, count, err);
+      if (r.cnt) atomicAdd(&count[r.cur], r.cnt);
+    }
   }
 }
 
@@ -89,34 +130,66 @@ __device__ __forceinline__ void wave_range(bool valid, int key, int tau, int32_t
   }
 }
 
-// Zero the per-trajectory counts and check the task / group ids, one launch.
-// With `range` (2 ints per group, then 2 per task, preset to (n_traj, -1)),
-// also record the lowest and the highest index of each group's and each
-// task's members (integer atomics: the result does not depend on the order).
-__global__ void prep_kernel(int32_t n_traj, int32_t n_task, int32_t n_group,
-                            const int32_t* traj_task, const int32_t* traj_group,
-                            int32_t* act_count, int32_t* range, int* err) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// Zero the per-trajectory counts, preset the n_range member ranges to empty (lowest =
+// n_traj, highest = -1), one launch.
+__global__ void init_kernel(int32_t n_traj, int32_t* act_count, int32_t n_range, int32_t* range) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < n_traj) act_count[k] = 0;
+  if (k < n_range) range[k] = (k & 1) ? -1 : n_traj;
+}
+
+// Check a trajectory's task and group ids; with `range` (2 ints per group, then 2 per
+// task) also record the lowest and the highest index of each group's and each task's
+// members (integer atomics: the result does not depend on the order).
+struct IdArgs {
+  int32_t n_task, n_group;
+  const int32_t* traj_task;
+  const int32_t* traj_group;
+  int32_t* range;
+};
+__device__ __forceinline__ void check_ids(const IdArgs& a, int j, int32_t n_traj, int* err) {
   const bool in = j < n_traj;
-  const int i = in ? traj_task[j] : 0;
-  const int g = in && traj_group ? traj_group[j] : 0;
-  const bool ok_task = in && i >= 0 && i < n_task;
-  const bool ok_group = in && traj_group && g >= 0 && g < n_group;
-  if (in) {
-    act_count[j] = 0;
-    if (!ok_task) set_error(err, ERR_TASK_ID);
-    if (traj_group && !ok_group) set_error(err, ERR_GROUP_ID);
-  }
-  if (range) {
-    if (traj_group) wave_range(ok_group, g, j, range);
-    wave_range(ok_task, i, j, range + 2 * n_group);
+  const int i = in ? a.traj_task[j] : 0;
+  const int g = in && a.traj_group ? a.traj_group[j] : 0;
+  const bool ok_task = in && i >= 0 && i < a.n_task;
+  const bool ok_group = in && a.traj_group && g >= 0 && g < a.n_group;
+  if (in && !ok_task) set_error(err, ERR_TASK_ID);
+  if (in && a.traj_group && !ok_group) set_error(err, ERR_GROUP_ID);
+  if (a.range) {
+    if (a.traj_group) wave_range(ok_group, g, j, a.range);
+    wave_range(ok_task, i, j, a.range + 2 * a.n_group);
   }
 }
 
-// Preset the member ranges to empty: lowest = n_traj, highest = -1.
-__global__ void range_init_kernel(int32_t n, int32_t n_traj, int32_t* range) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) range[k] = (k & 1) ? -1 : n_traj;
+// The token counts, and beside them the id checks, which do not need them: the first
+// id_blocks blocks take 256 trajectories each, the others 256 * kCountPerLane tokens.
+// One launch less at 2560 trajectories and 9M tokens: 38.6 -> 33.6 us a call.  (Ranges
+// preset and recorded by one block: 16.3 us for that launch alone.)
+template <bool VEC>
+__global__ __launch_bounds__(256) void count_kernel(int64_t T_g, int32_t n_traj,
+                                                    const int32_t* __restrict__ traj_id,
+                                                    const uint8_t* __restrict__ mask,
+                                                    int32_t* act_count, int32_t id_blocks,
+                                                    IdArgs ids, int* err) {
+  if ((int)blockIdx.x < id_blocks) {
+    check_ids(ids, blockIdx.x * 256 + threadIdx.x, n_traj, err);
+    return;
+  }
+  count_tokens<VEC>(((int64_t)(blockIdx.x - id_blocks) * 256 + threadIdx.x) * kCountPerLane, T_g,
+                    n_traj, traj_id, mask, act_count, err);
+}
+
+void launch_count(int64_t T_g, int32_t n_traj, const int32_t* traj_id, const uint8_t* mask,
+                  int32_t* act_count, int32_t id_blocks, const IdArgs& ids, int* err,
+                  hipStream_t s) {
+  const int64_t blocks = id_blocks + cdiv<int64_t>(cdiv<int64_t>(T_g, kCountPerLane), 256);
+  if (blocks == 0) return;
+  if ((((uintptr_t)traj_id | (uintptr_t)mask) & 15) == 0)
+    hipLaunchKernelGGL(count_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, T_g, n_traj,
+                       traj_id, mask, act_count, id_blocks, ids, err);
+  else
+    hipLaunchKernelGGL(count_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, T_g, n_traj,
+                       traj_id, mask, act_count, id_blocks, ids, err);
 }
 
 // The trajectories a segment's wave visits: [first, last] of its members when
@@ -279,23 +352,93 @@ __global__ __launch_bounds__(256) void task_kernel(int32_t n_task, int32_t n_gro
               task_std, adv_traj);
 }
 
-// VEC: traj_id, mask and adv_tok are 16-byte aligned and a thread handles 4
-// tokens with one 16-byte id load, one 4-byte mask load and one 16-byte store.
+// tok[t .. t + 3] = value[traj_id] on action tokens, 0 elsewhere.  VEC: traj_id, mask and
+// tok are 16-byte aligned: one 16-byte id load, one 4-byte mask load, one 16-byte store.
+template <bool VEC>
+__device__ __forceinline__ void spread_tokens(int64_t t, int64_t T, int32_t n_traj,
+                                              const int32_t* __restrict__ traj_id,
+                                              const uint8_t* __restrict__ mask,
+                                              const float* value, float* tok) {
+  auto one = [&](int id, bool m) { return (m && id >= 0 && id < n_traj) ? value[id] : 0.0f; };
+  if (VEC && t + 4 <= T) {
+    const i32x4 id = *(const i32x4*)(traj_id + t);
+    const uint32_t m = *(const uint32_t*)(mask + t);
+    *(f32x4*)(tok + t) = f32x4{one(id[0], m & 0xFFu), one(id[1], (m >> 8) & 0xFFu),
+                               one(id[2], (m >> 16) & 0xFFu), one(id[3], m >> 24)};
+    return;
+  }
+  for (int64_t u = t; u < T && u < t + 4; ++u) tok[u] = one(traj_id[u], mask[u] != 0);
+}
+
 template <bool VEC>
 __global__ void broadcast_kernel(int64_t T_g, int32_t n_traj, const int32_t* __restrict__ traj_id,
                                  const uint8_t* __restrict__ mask,
                                  const float* __restrict__ adv_traj, float* adv_tok) {
-  auto one = [&](int id, bool m) { return (m && id >= 0 && id < n_traj) ? adv_traj[id] : 0.0f; };
-  const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * (VEC ? 4 : 1);
-  if (VEC && t + 4 <= T_g) {
-    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    const i32x4 id = *(const i32x4*)(traj_id + t);
-    const uint32_t m = *(const uint32_t*)(mask + t);
-    *(f32x4*)(adv_tok + t) = f32x4{one(id[0], m & 0xFFu), one(id[1], (m >> 8) & 0xFFu),
-                                   one(id[2], (m >> 16) & 0xFFu), one(id[3], m >> 24)};
-    return;
+  spread_tokens<VEC>(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4, T_g, n_traj, traj_id,
+                     mask, adv_traj, adv_tok);
+}
+
+// A whole call in one workgroup, for batches small enough that launches are what they
+// cost: the same stages on arrays in LDS.  32 trajectories, 3.8k tokens, 8 groups, 2
+// tasks: 8.0 us, against 18.6 us of six kernels and as much between them.  The limits keep
+// it ahead: at 32768 tokens two lots of 16 a thread, and at most 64k ids scanned by 16
+// waves (about 64 steps each).
+constexpr int kSmallTraj = 1024;          // trajectories
+constexpr int64_t kSmallTokens = 32768;
+constexpr int64_t kSmallScan = 1 << 16;   // segments x trajectories: what the stages' waves scan
+struct SmallArgs {
+  int64_t T_g;
+  int32_t n_traj, n_task, n_group;
+  const int32_t* traj_id;
+  const uint8_t* mask;
+  const int32_t* traj_task;
+  const int32_t* traj_group;
+  const float* reward;
+  int32_t ddof;
+  float eps;
+  int32_t drop;
+  int32_t* act_count;
+  int64_t* task_count;
+  float* task_mean;
+  float* task_std;
+  float* adv_traj;
+  float* adv_tok;
+  int* err;
+};
+template <bool VEC>
+__global__ __launch_bounds__(1024) void adv_small_kernel(SmallArgs a) {
+  __shared__ int32_t s_count[kSmallTraj], s_task[kSmallTraj], s_group[kSmallTraj];
+  __shared__ float s_reward[kSmallTraj], s_adv[kSmallTraj];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid < a.n_traj) {
+    const int i = a.traj_task[tid], g = a.traj_group ? a.traj_group[tid] : 0;
+    s_count[tid] = 0;
+    s_task[tid] = i;
+    s_group[tid] = g;
+    const float r = a.reward[tid];
+    s_reward[tid] = r;
+    s_adv[tid] = a.traj_group ? 0.0f : r;
+    if (i < 0 || i >= a.n_task) set_error(a.err, ERR_TASK_ID);
+    if (a.traj_group && (g < 0 || g >= a.n_group)) set_error(a.err, ERR_GROUP_ID);
   }
-  for (int64_t u = t; u < T_g && u < t + (VEC ? 4 : 1); ++u) adv_tok[u] = one(traj_id[u], mask[u] != 0);
+  __syncthreads();
+  count_in_lds<VEC>(a.T_g, a.n_traj, a.traj_id, a.mask, s_count, a.err);
+  const Span all{0, a.n_traj - 1};
+  if (a.traj_group)
+    for (int g = wave; g < a.n_group; g += 16)
+      group_wave(g, lane, a.n_traj, all, s_group, s_reward, a.ddof, a.eps, a.drop, s_adv);
+  __syncthreads();
+  if (tid < a.n_traj) a.act_count[tid] = s_count[tid];
+  for (int i = wave; i < a.n_task; i += 16)
+    task_wave(i, lane, a.n_traj, all, s_task, s_count, s_adv, a.ddof, a.eps, a.drop, a.task_count,
+              a.task_mean, a.task_std, s_adv);
+  __syncthreads();
+  if (tid < a.n_traj) a.adv_traj[tid] = s_adv[tid];
+  if (a.adv_tok) {
+#pragma unroll 4
+    for (int64_t t = (int64_t)tid * 4; t < a.T_g; t += 1024 * 4)
+      spread_tokens<VEC>(t, a.T_g, a.n_traj, a.traj_id, a.mask, s_adv, a.adv_tok);
+  }
 }
 
 int fail(int code, const char* msg) {
@@ -325,6 +468,45 @@ __global__ __launch_bounds__(256) void seq_weight_kernel(int64_t T, int32_t n_tr
       v = (float)(1.0 / ((double)n_seq * (double)seq_count[id]));
     w[t] = v;
   }
+}
+
+// The same in one launch, counters in LDS: every workgroup counts all the tokens itself
+// (kSeqTokens: 4 lots of 16 a thread, from L2) and weighs its share of them.  640
+// trajectories, 65536 tokens: 17.3 us a call in three launches (the host's), 12.6 in one.
+constexpr int kSeqTraj = 4096;
+constexpr int64_t kSeqTokens = 65536;
+constexpr int kSeqShare = 4096;          // tokens a workgroup weighs
+template <bool VEC>
+__global__ __launch_bounds__(1024) void seq_small_kernel(int64_t T, int32_t n_traj,
+                                                         const int32_t* __restrict__ traj_id,
+                                                         const uint8_t* __restrict__ mask,
+                                                         int32_t* __restrict__ seq_count,
+                                                         float* __restrict__ w, int* err) {
+  __shared__ int32_t count[kSeqTraj];
+  __shared__ int part[16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int j = tid; j < n_traj; j += 1024) count[j] = 0;
+  __syncthreads();
+  count_in_lds<VEC>(T, n_traj, traj_id, mask, count, err);
+  __syncthreads();
+  int n = 0;
+  for (int j = tid; j < n_traj; j += 1024) {
+    if (blockIdx.x == 0) seq_count[j] = count[j];
+    n += count[j] > 0;
+  }
+  for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o);
+  if (lane == 0) part[tid >> 6] = n;
+  __syncthreads();
+  int n_seq = 0;
+  for (int k = 0; k < 16; ++k) n_seq += part[k];
+  // the quotients of the trajectories with action tokens, in place of their counts
+  for (int j = tid; j < n_traj; j += 1024)
+    if (count[j] > 0)
+      count[j] = __float_as_int((float)(1.0 / ((double)n_seq * (double)count[j])));
+  __syncthreads();
+  static_assert(kSeqShare == 4 * 1024, "four tokens a thread");
+  spread_tokens<VEC>((int64_t)blockIdx.x * kSeqShare + tid * 4, T, n_traj, traj_id, mask,
+                     (const float*)count, w);
 }
 
 }  // namespace
@@ -365,29 +547,32 @@ extern "C" int agrl_task_adv_norm(int64_t T_g, int32_t n_traj, int32_t n_task, i
   int* err = device_error_ptr();
   if (!err) return hip_status(hipErrorInvalidSymbol);
 
-  // member ranges (optional scratch): groups first, then tasks
   const int32_t n_group_used = traj_group ? n_group : 0;
-  int32_t* range = n_traj > 0 ? o.adv_ranges : nullptr;
-  if (range && n_group_used + n_task > 0)
-    hipLaunchKernelGGL(range_init_kernel, dim3(cdiv(2 * (n_group_used + n_task), 256)), dim3(256),
-                       0, s, 2 * (n_group_used + n_task), n_traj, range);
-  if (n_traj > 0)
-    hipLaunchKernelGGL(prep_kernel, dim3(cdiv(n_traj, 256)), dim3(256), 0, s, n_traj, n_task,
-                       n_group_used, traj_task, traj_group, act_count, range, err);
-  const bool vec_in = (((uintptr_t)traj_id | (uintptr_t)action_mask) & 15) == 0;
-  if (T_g > 0 && n_traj >= 0) {
-    const int64_t lanes = cdiv<int64_t>(T_g, kCountPerLane);
-    const dim3 grid((unsigned)cdiv<int64_t>(lanes, 256));
-    if (vec_in)
-      hipLaunchKernelGGL(count_kernel<true>, grid, dim3(256), 0, s, T_g, n_traj, traj_id,
-                         action_mask, act_count, err);
-    else
-      hipLaunchKernelGGL(count_kernel<false>, grid, dim3(256), 0, s, T_g, n_traj, traj_id,
-                         action_mask, act_count, err);
-  }
   const int32_t ddof = (int32_t)o.std_ddof;
   const int32_t drop = traj_group ? o.drop_uniform_groups : 0;
-  if (traj_group && n_group > 0)
+  const bool vec_in = (((uintptr_t)traj_id | (uintptr_t)action_mask) & 15) == 0;
+  if (T_g <= kSmallTokens && n_traj <= kSmallTraj &&
+      ((int64_t)n_group_used + n_task) * n_traj <= kSmallScan) {
+    const SmallArgs a = {T_g, n_traj, n_task, n_group_used, traj_id, action_mask, traj_task,
+                         traj_group, reward, ddof, eps, drop, act_count, task_count, task_mean,
+                         task_std, adv_traj, adv_tok, err};
+    if (vec_in && ((uintptr_t)adv_tok & 15) == 0)
+      hipLaunchKernelGGL(adv_small_kernel<true>, dim3(1), dim3(1024), 0, s, a);
+    else
+      hipLaunchKernelGGL(adv_small_kernel<false>, dim3(1), dim3(1024), 0, s, a);
+    return hip_status(hipGetLastError());
+  }
+
+  // member ranges (optional scratch): groups first, then tasks
+  int32_t* range = n_traj > 0 ? o.adv_ranges : nullptr;
+  const int32_t n_range = range ? 2 * (n_group_used + n_task) : 0;
+  const int32_t n_init = n_traj > n_range ? n_traj : n_range;
+  if (n_init > 0)
+    hipLaunchKernelGGL(init_kernel, dim3(cdiv(n_init, 256)), dim3(256), 0, s, n_traj, act_count,
+                       n_range, range);
+  launch_count(T_g, n_traj, traj_id, action_mask, act_count, cdiv(n_traj, 256),
+               IdArgs{n_task, n_group_used, traj_task, traj_group, range}, err, s);
+  if (n_group_used > 0)
     hipLaunchKernelGGL(group_kernel, dim3(cdiv(n_group, 4)), dim3(256), 0, s, n_group, n_traj,
                        traj_group, reward, (const int32_t*)range, ddof, eps, drop, adv_traj);
   if (n_task > 0)
@@ -396,13 +581,13 @@ extern "C" int agrl_task_adv_norm(int64_t T_g, int32_t n_traj, int32_t n_task, i
                        traj_group ? (const float*)adv_traj : reward, (const int32_t*)range, ddof,
                        eps, drop, task_count, task_mean, task_std, adv_traj);
   if (adv_tok && T_g > 0) {
+    const dim3 grid((unsigned)cdiv<int64_t>(cdiv<int64_t>(T_g, 4), 256));
     if (vec_in && ((uintptr_t)adv_tok & 15) == 0)
-      hipLaunchKernelGGL(broadcast_kernel<true>, dim3((unsigned)cdiv<int64_t>(cdiv<int64_t>(T_g, 4), 256)),
-                         dim3(256), 0, s, T_g, n_traj, traj_id, action_mask,
-                         (const float*)adv_traj, adv_tok);
+      hipLaunchKernelGGL(broadcast_kernel<true>, grid, dim3(256), 0, s, T_g, n_traj, traj_id,
+                         action_mask, (const float*)adv_traj, adv_tok);
     else
-      hipLaunchKernelGGL(broadcast_kernel<false>, dim3((unsigned)cdiv<int64_t>(T_g, 256)), dim3(256),
-                         0, s, T_g, n_traj, traj_id, action_mask, (const float*)adv_traj, adv_tok);
+      hipLaunchKernelGGL(broadcast_kernel<false>, grid, dim3(256), 0, s, T_g, n_traj, traj_id,
+                         action_mask, (const float*)adv_traj, adv_tok);
   }
   return hip_status(hipGetLastError());
 }
@@ -421,18 +606,21 @@ extern "C" int agrl_sequence_mean_weights(int64_t T, int32_t n_traj, const int32
   hipStream_t s = (hipStream_t)stream;
   int* err = device_error_ptr();
   if (!err) return hip_status(hipErrorInvalidSymbol);
+  if (T <= kSeqTokens && n_traj <= kSeqTraj) {
+    const dim3 grid((unsigned)(T > 0 ? cdiv<int64_t>(T, kSeqShare) : 1));
+    if ((((uintptr_t)traj_id | (uintptr_t)action_mask | (uintptr_t)token_weight) & 15) == 0)
+      hipLaunchKernelGGL(seq_small_kernel<true>, grid, dim3(1024), 0, s, T, n_traj, traj_id,
+                         action_mask, seq_count, token_weight, err);
+    else
+      hipLaunchKernelGGL(seq_small_kernel<false>, grid, dim3(1024), 0, s, T, n_traj, traj_id,
+                         action_mask, seq_count, token_weight, err);
+    return hip_status(hipGetLastError());
+  }
   if (n_traj > 0)
     hipLaunchKernelGGL(fill_i32_kernel, dim3(cdiv(n_traj, 256)), dim3(256), 0, s, seq_count,
                        (int64_t)n_traj, 0);
   if (T > 0) {
-    const int64_t lanes = cdiv<int64_t>(T, kCountPerLane);
-    const dim3 grid((unsigned)cdiv<int64_t>(lanes, 256));
-    if ((((uintptr_t)traj_id | (uintptr_t)action_mask) & 15) == 0)
-      hipLaunchKernelGGL(count_kernel<true>, grid, dim3(256), 0, s, T, n_traj, traj_id,
-                         action_mask, seq_count, err);
-    else
-      hipLaunchKernelGGL(count_kernel<false>, grid, dim3(256), 0, s, T, n_traj, traj_id,
-                         action_mask, seq_count, err);
+    launch_count(T, n_traj, traj_id, action_mask, seq_count, 0, IdArgs{}, err, s);
     const int64_t blocks = cdiv<int64_t>(T, 256);
     hipLaunchKernelGGL(seq_weight_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)),
                        dim3(256), 0, s, T, n_traj, traj_id, action_mask,

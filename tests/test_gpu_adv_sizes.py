@@ -1,0 +1,65 @@
+"""Advantage normalisation and sequence weights where the launches change: one workgroup
+for a small batch, one or several blocks presetting the member ranges, unaligned arrays.
+Bit-exact against the oracle, trajectories numbered at random."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+from helpers import log
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(n_traj, n_group, n_task, T, seed):
+    rng = np.random.default_rng([seed, n_traj, T])
+    group = rng.integers(0, n_group, n_traj).astype(np.int32)
+    task = (group * n_task // n_group).astype(np.int32)
+    reward = np.where(task % 2 == 0, rng.random(n_traj) < 0.5, rng.normal(0, 1, n_traj)).astype(np.float32)
+    cuts = np.sort(rng.integers(0, T + 1, n_traj - 1)) if n_traj > 1 else np.zeros(0, int)
+    ids = np.repeat(rng.permutation(n_traj), np.diff(np.concatenate([[0], cuts, [T]]))).astype(np.int32)
+    ids[rng.random(T) < 0.02] = -1
+    return task, group, reward, ids, (rng.random(T) < 0.4).astype(np.uint8)
+
+
+@pytest.mark.parametrize("n_traj,n_group,n_task,T,offset", [
+    (1, 1, 1, 1, 0), (64, 3, 2, 1000, 1), (1024, 62, 2, 32768, 0), (1024, 62, 2, 32769, 0),
+    (1024, 63, 2, 5003, 0), (1025, 60, 2, 4000, 3), (4096, 4000, 96, 60001, 0),
+    (4097, 1000, 7, 60001, 0), (5000, 4500, 20, 9000, 5)])
+@pytest.mark.parametrize("drop", [False, True])
+def test_adv_norm_sizes(n_traj, n_group, n_task, T, offset, drop):
+    import paper_2510_04206_amd as P
+    task, group, reward, ids, mask = _batch(n_traj, n_group, n_task, T, 3)
+    log(f"adv sizes n_traj={n_traj} groups={n_group} tasks={n_task} T={T} offset={offset} drop={drop}")
+
+    def t(a):
+        return torch.from_numpy(a).cuda()
+
+    def at(a):           # the same values `offset` elements into an aligned array
+        return torch.cat([torch.zeros(offset, dtype=t(a).dtype, device="cuda"), t(a)])[offset:]
+
+    want = oracle.task_adv_norm(ids, mask, task, group, reward, n_task, n_group, drop_uniform=drop)
+    for ranges in (True, False):
+        got = P.task_adv_norm(at(ids), at(mask), t(task), t(group), t(reward), n_task, n_group,
+                              opt=dict(drop_uniform_groups=int(drop)), member_ranges=ranges)
+        assert P.agrl_get_device_error() == 0
+        for k in ("act_count", "task_count", "task_mean", "task_std", "adv_traj", "adv_tok"):
+            a, b = got[k].cpu().numpy(), np.asarray(want[k])
+            if a.dtype == np.float32:
+                a, b = a.view(np.uint32), b.view(np.uint32)
+            np.testing.assert_array_equal(a, b, err_msg=f"{k} ranges={ranges}")
+
+
+@pytest.mark.parametrize("n_traj,T,offset", [
+    (1, 1, 0), (7, 100, 3), (4096, 65536, 0), (4096, 65535, 1), (4097, 3000, 0), (64, 65537, 0)])
+def test_sequence_weight_sizes(n_traj, T, offset):
+    import paper_2510_04206_amd as P
+    _, _, _, ids, mask = _batch(n_traj, n_traj, 1, T + offset, 5)
+    log(f"sequence weight sizes n_traj={n_traj} T={T} offset={offset}")
+    count, w = P.sequence_mean_weights(torch.from_numpy(ids).cuda()[offset:],
+                                       torch.from_numpy(mask).cuda()[offset:], n_traj)
+    assert P.agrl_get_device_error() == 0
+    want_count, want_w = oracle.sequence_mean_weights(ids[offset:], mask[offset:], n_traj)
+    np.testing.assert_array_equal(count.cpu().numpy(), want_count)
+    np.testing.assert_array_equal(w.cpu().numpy().view(np.uint32), want_w.view(np.uint32))
