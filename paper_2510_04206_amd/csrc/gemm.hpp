@@ -184,10 +184,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 template <uint32_t LDS_OFF>
 __device__ __forceinline__ void copy16(const void* base, uint32_t off, uint32_t lds) {
   // scalar base + 32-bit per-lane offset: no 64-bit address arithmetic per copy;
-  // M0 = lds + LDS_OFF in one scalar add
+  // M0 = lds + LDS_OFF in one scalar add (which writes SCC: undeclared, the compiler may
+  // put a copy between the two halves of a 64-bit address add and lose the carry)
   asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base),
                "s"(lds), "n"(LDS_OFF)
-               : "memory");
+               : "memory", "scc");
 }
 
 // 16 x 16 x 32 loop: what rides along with MFMA slot q of a stage (slot
