@@ -3,14 +3,12 @@
 // storage), fp32 accumulation, with a fused epilogue functor.
 //
 // Block tile 256 x 256, 4 waves in a 2 x 2 arrangement, each wave owning a
-// 128 x 128 sub-tile as 4 x 4 blocks of 32 x 32 MFMA accumulators
-// (v_mfma_f32_32x32x16_bf16), or, in the 16 x 16 mode, as 8 x 8 blocks of
-// v_mfma_f32_16x16x32_bf16 accumulators (half the accumulator traffic per flop:
-// under the board power limit the chip then holds a higher clock).
+// 128 x 128 sub-tile as 8 x 8 blocks of v_mfma_f32_16x16x32_bf16 accumulators (half
+// the accumulator traffic per flop of the 32 x 32 shape: under the board power limit
+// the chip then holds a higher clock).
 // Each K stage moves 128 bytes of every tile row from global memory straight into
-// LDS (no register staging), double-buffered (one barrier per stage in the 32 x 32
-// loop; in the 16 x 16 loop a second one in the middle of the stage, so that a
-// stage's copies have until then to land).  The 16-byte chunk c of tile row r is
+// LDS (no register staging), double-buffered (a second barrier in the middle of the
+// stage gives a stage's copies until then to land).  The 16-byte chunk c of tile row r is
 // stored at chunk c ^ ((r >> 1) & 7): a 128-bit LDS read serves 16 lanes per pass
 // from a 256-byte window (two 128-byte rows), and this places the 16 rows such a
 // pass touches in 16 distinct bank groups.
@@ -102,15 +100,6 @@ __host__ __device__ __forceinline__ int64_t tiled_cm_index(int64_t r, int64_t k,
          ((((k & 63) >> 3) ^ ((r >> 1) & 7)) << 3) + (k & 7);
 }
 
-// Accumulator element (i, j, r) of a wave sits at
-//   row = wm*128 + i*32 + 8*(r/4) + 4*(lane/32) + r%4,  col = wn*128 + j*32 + lane%32.
-__device__ __forceinline__ int acc_row(int wm, int i, int r, int lane) {
-  return wm * 128 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-}
-__device__ __forceinline__ int acc_col(int wn, int j, int lane) {
-  return wn * 128 + j * 32 + (lane & 31);
-}
-
 // Swizzle of a tile row: the chunk offset XORed into its 16-byte chunks.
 __device__ __forceinline__ int row_swizzle(int r) { return (r >> 1) & 7; }
 
@@ -126,46 +115,27 @@ typedef __attribute__((address_space(1))) void glb_void_t;
 //   * every MFMA of a slice is paired with at most one LDS fragment read or
 //     one stage copy (sched_barrier keeps that order), so the matrix pipe is
 //     never left waiting behind a burst of memory instructions;
-//   * (32 x 32 loop) the barrier of stage kt sits before its last 16-deep
-//     slice: by then the slice's fragments are in registers, stage kt+1 has
-//     landed and stage kt's buffer is free, so the last slice's MFMAs cover
-//     the barrier, the reads of stage kt+1's first slice and the copies of
-//     stage kt+2 into the freed buffer.  __syncthreads() is avoided because
-//     it would also wait for the copies still in flight.
+//   * the barriers are bare s_barrier: __syncthreads() would also wait for the
+//     copies still in flight.
 namespace bf16k {
 constexpr int SK = 64;                        // k per stage
 constexpr int ROW = SK * 2;                   // bytes per tile row per stage
 constexpr int STAGE = (GBM + GBN) * ROW;      // 64 KiB
 constexpr int HALF = GBM * ROW;               // one operand's part of a stage (32 KiB)
 constexpr int NB = 2;                         // stage buffers
-constexpr int KK = SK / 16;                   // 16-deep slices per stage
 constexpr int RPI = 1024 / ROW;               // tile rows per copy instruction (8)
 constexpr int IPW = 64 / RPI;                 // copy instructions per wave per operand (8)
 constexpr int NCOPY = 2 * IPW;                // per wave per stage (16)
 static_assert(NB * STAGE <= GEMM_LDS, "LDS");
-static_assert((NB - 1) * HALF + 3 * 32 * ROW < 65536, "fragment offsets fit a DS immediate");
-static_assert(NCOPY == 16, "one copy per MFMA of the last slice");
+static_assert((NB - 1) * HALF + 7 * 16 * ROW < 65536, "fragment offsets fit a DS immediate");
 // Transposed A (a_trans).  The stage's A half holds 64 k-rows of the tile's 256
 // rows of A, 512 bytes per k-row: the 64-byte window w (rows 32 w .. 32 w + 31)
-// of k-row k sits at window w ^ (k & 3).  A fragment (rows 32-block i, k slice
-// kk) is two transposing reads (ds_read_b64_tr_b16): within each 16-lane
-// group, lane s supplies k-row (s >> 2) and rows 4 (s & 3) .. + 3, and lane
-// 4a + b receives row 4a + b of k-rows 0..3 — in a 32-lane half the four k-rows
-// land in four distinct 64-byte bank windows.
+// of k-row k sits at window w ^ (k & 3) (see loop16 for the reads).
 constexpr int TR_KROW = GBM * 2;                // bytes per k-row (512)
-static_assert((NB - 1) * HALF + (KK - 1) * 16 * TR_KROW + 4 * TR_KROW < 65536,
+static_assert((NB - 1) * HALF + 32 * TR_KROW + 4 * TR_KROW < 65536,
               "transposed fragment offsets fit a DS immediate");
-// Copy schedule.  The 16 copies of stage s are spread over the MFMAs that
-// follow the barrier freeing their buffer: MFMA slot 0..15 is the last slice
-// of stage s - 2, slots 16..63 are slices 0..2 of stage s - 1, and copy c
-// (B rows first, then A rows) goes to slot c * CSTRIDE.  Issuing all 16
-// copies of a wave against 16 MFMAs stalls issue when the memory pipeline is
-// backed up, and a stalled wave leaves its matrix pipe idle; copies issued
-// later have less time to land before stage s - 1's barrier.
-constexpr int CSTRIDE = 2;
-static_assert(CSTRIDE >= 1 && 15 * CSTRIDE < 48, "copy schedule");
+// B rows first, then A rows
 __device__ __forceinline__ constexpr int copy_order(int c) { return (c + IPW) % NCOPY; }
-constexpr int NEARLY = (15 / CSTRIDE) + 1;      // copies issued in slot 0..15
 static_assert(NB == 2, "the vmcnt waits assume two stage buffers");
 
 template <int N>
@@ -408,18 +378,17 @@ __host__ __device__ inline int dh_split(int n_act, int nv, int d, int cus, int m
   return (int)(parts < most ? parts : most);
 }
 
-// EVEN: every problem's K is a multiple of 2 stages (a device-read K is rounded
-// up to one, the operands being zero-padded that far); such launches run the
-// 16 x 16 loop (MF16), whose stage pairs know their buffers at compile time, so
-// every LDS address of the loop is a base register plus an immediate.  Other
-// launches (a hidden size that is not a multiple of 128) run the 32 x 32 loop on
-// row-major operands.  ATR: a problem may read A transposed out of stage-tiled
-// storage (GemmShape::a_trans; 16 x 16 loop only).
-template <class Epi, bool EVEN, bool ATR, bool MF16 = false>
+// Stages run in pairs, so that which LDS buffer a stage reads and refills is known at
+// compile time and every LDS address of the loop is a base register plus an immediate.
+// ODD: K is an odd number of stages (a hidden size that is no multiple of 128; forward
+// and recompute only): the first stage runs before the pairs, unpipelined.  At 17 stages
+// (d = 1088, V = 131001, 2122 tokens) the forward takes 635 us and the recompute 240 us per
+// 43776 columns, against 680 and 272 us (same box) in a loop on 32 x 32 blocks that chose
+// its buffer at run time.  ATR: a problem may read A transposed (GemmShape::a_trans).
+template <class Epi, bool ATR, bool ODD = false>
 __global__ void __launch_bounds__(GEMM_THREADS)
     __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_bf16_kernel(GemmBatch<Epi> bat) {
-  static_assert(MF16 == EVEN, "stage-pair launches run the 16 x 16 loop, the others the 32 x 32 loop");
-  static_assert(!ATR || MF16, "transposed A in the 16 x 16 loop only");
+  static_assert(!(ATR && ODD), "the products that read A transposed have whole stage pairs");
   // both products read A transposed, problem 0 (dH) out of row-major W with K split
   constexpr bool GRAD = std::is_same<Epi, EpiGrad>::value;
   using namespace bf16k;
@@ -438,7 +407,7 @@ __global__ void __launch_bounds__(GEMM_THREADS)
     // device-read sizes are the same in every lane; keep them scalar (see below)
     Mp[p] = __builtin_amdgcn_readfirstlane(gp.m_dev ? *gp.m_dev : gp.M);
     Np[p] = __builtin_amdgcn_readfirstlane(gp.n_dev ? *gp.n_dev : gp.N);
-    constexpr int KR = EVEN ? 2 * SK : SK;
+    constexpr int KR = 2 * SK;
     Kp[p] = __builtin_amdgcn_readfirstlane(gp.k_dev ? cdiv(*gp.k_dev, KR) * KR : gp.K);
     tmp[p] = cdiv(Mp[p], GBM);
     tnp[p] = cdiv(Np[p], GBN);
@@ -451,19 +420,7 @@ __global__ void __launch_bounds__(GEMM_THREADS)
     totp[0] *= parts;
   }
 
-  // fragment reads: lane l reads row (l & 31) of each 32-row block, chunk
-  // 2 kk + l / 32 of slice kk.  LDS holds the A halves of the two stage buffers
-  // first, then the B halves, so a read's buffer and block are an offset of at
-  // most 45 KiB from a per-slice base.
-  const int frow = lane & 31;
-  const int fsw = row_swizzle(frow);
-  int ra[KK], rb[KK];
-#pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    const int chk = ((kk * 2 + (lane >> 5)) ^ fsw) << 4;
-    ra[kk] = (wm * 128 + frow) * ROW + chk;
-    rb[kk] = NB * HALF + (wn * 128 + frow) * ROW + chk;
-  }
+  // LDS holds the A halves of the two stage buffers first, then the B halves.
   // LDS byte address of the stage buffers
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_t*)smem);
 
@@ -575,7 +532,7 @@ __global__ void __launch_bounds__(GEMM_THREADS)
       place(g.a_tiled, g.lda, lda_b, tm, m0, a_off, a_ks);
     }
     place(g.b_tiled, g.ldb, ldb_b, tn, n0, b_off, b_ks);
-    // serpentine K (16 x 16 loop): odd rounds of the problem's tile order copy
+    // serpentine K: odd rounds of the problem's tile order copy
     // the stages last to first
     // (an item of row-major W goes forwards: its tail is another buffer)
     if constexpr (GRAD) {
@@ -588,7 +545,7 @@ __global__ void __launch_bounds__(GEMM_THREADS)
         tail_delta = ((const uint8_t*)g.a_tail - (int64_t)g.a_tail_stage * a_ks) -
                      (const uint8_t*)g.A;
     }
-    if (MF16 && CopySched<Epi>::serpentine && !atr_rows && ((L / (32 * nq)) & 1)) {
+    if (CopySched<Epi>::serpentine && !atr_rows && ((L / (32 * nq)) & 1)) {
       a_off += (int64_t)(nk - 1) * a_ks;
       b_off += (int64_t)(nk - 1) * b_ks;
       a_ks = -a_ks;
@@ -642,50 +599,48 @@ __global__ void __launch_bounds__(GEMM_THREADS)
     }
 
     // (the LDS address is formed from scalars only, so it stays in SGPRs)
-    // copy Q of stage s into stage buffer BUF (or buf when BUF < 0): the LDS
-    // address is a scalar base plus a constant of the copy site
+    // copy Q of stage s into stage buffer BUF: the LDS address is a scalar base plus
+    // a constant of the copy site
     const uint32_t lds_w = lds0 + (uint32_t)(wave * 64 * ROW);
-    auto copy = [&](int s, auto q_c, auto buf_c, int buf) {
+    auto copy = [&](int s, auto q_c, auto buf_c) {
       constexpr int Q = decltype(q_c)::value;
       constexpr int BUF = decltype(buf_c)::value;
       constexpr uint32_t b = Q % IPW;
-      constexpr uint32_t fixed = BUF >= 0 ? (uint32_t)BUF * HALF : 0u;
-      const uint32_t base = BUF >= 0 ? lds_w : lds_w + (uint32_t)(buf * HALF);
+      constexpr uint32_t fixed = (uint32_t)BUF * HALF;
       if constexpr (Q < IPW && GRAD)
         copy16<fixed + b * RPI * ROW>(
             a_base + s * a_ks + (atr_rows && k0 + s >= g.a_tail_stage ? tail_delta : 0), offa[b],
-            base);
+            lds_w);
       else if constexpr (Q < IPW)
-        copy16<fixed + b * RPI * ROW>(a_base + s * a_ks, offa[b], base);
+        copy16<fixed + b * RPI * ROW>(a_base + s * a_ks, offa[b], lds_w);
       else
-        copy16<NB * HALF + fixed + b * RPI * ROW>(b_base + s * b_ks, offb[b], base);
+        copy16<NB * HALF + fixed + b * RPI * ROW>(b_base + s * b_ks, offb[b], lds_w);
     };
     // q is a constant at every call site once the loops are unrolled
-    auto copy_q = [&](int s, int q, auto buf_c, int buf) {
+    auto copy_q = [&](int s, int q, auto buf_c) {
       static_assert(NCOPY == 16, "one case per copy");
       switch (q) {
-        case 0: copy(s, std::integral_constant<int, 0>{}, buf_c, buf); break;
-        case 1: copy(s, std::integral_constant<int, 1>{}, buf_c, buf); break;
-        case 2: copy(s, std::integral_constant<int, 2>{}, buf_c, buf); break;
-        case 3: copy(s, std::integral_constant<int, 3>{}, buf_c, buf); break;
-        case 4: copy(s, std::integral_constant<int, 4>{}, buf_c, buf); break;
-        case 5: copy(s, std::integral_constant<int, 5>{}, buf_c, buf); break;
-        case 6: copy(s, std::integral_constant<int, 6>{}, buf_c, buf); break;
-        case 7: copy(s, std::integral_constant<int, 7>{}, buf_c, buf); break;
-        case 8: copy(s, std::integral_constant<int, 8>{}, buf_c, buf); break;
-        case 9: copy(s, std::integral_constant<int, 9>{}, buf_c, buf); break;
-        case 10: copy(s, std::integral_constant<int, 10>{}, buf_c, buf); break;
-        case 11: copy(s, std::integral_constant<int, 11>{}, buf_c, buf); break;
-        case 12: copy(s, std::integral_constant<int, 12>{}, buf_c, buf); break;
-        case 13: copy(s, std::integral_constant<int, 13>{}, buf_c, buf); break;
-        case 14: copy(s, std::integral_constant<int, 14>{}, buf_c, buf); break;
-        case 15: copy(s, std::integral_constant<int, 15>{}, buf_c, buf); break;
+        case 0: copy(s, std::integral_constant<int, 0>{}, buf_c); break;
+        case 1: copy(s, std::integral_constant<int, 1>{}, buf_c); break;
+        case 2: copy(s, std::integral_constant<int, 2>{}, buf_c); break;
+        case 3: copy(s, std::integral_constant<int, 3>{}, buf_c); break;
+        case 4: copy(s, std::integral_constant<int, 4>{}, buf_c); break;
+        case 5: copy(s, std::integral_constant<int, 5>{}, buf_c); break;
+        case 6: copy(s, std::integral_constant<int, 6>{}, buf_c); break;
+        case 7: copy(s, std::integral_constant<int, 7>{}, buf_c); break;
+        case 8: copy(s, std::integral_constant<int, 8>{}, buf_c); break;
+        case 9: copy(s, std::integral_constant<int, 9>{}, buf_c); break;
+        case 10: copy(s, std::integral_constant<int, 10>{}, buf_c); break;
+        case 11: copy(s, std::integral_constant<int, 11>{}, buf_c); break;
+        case 12: copy(s, std::integral_constant<int, 12>{}, buf_c); break;
+        case 13: copy(s, std::integral_constant<int, 13>{}, buf_c); break;
+        case 14: copy(s, std::integral_constant<int, 14>{}, buf_c); break;
+        case 15: copy(s, std::integral_constant<int, 15>{}, buf_c); break;
         default: break;
       }
     };
-    using BUF_RT = std::integral_constant<int, -1>;
 
-    if constexpr (MF16) {
+    {
       // 16 x 16 x 32 loop.  acc[i][j] is the 16 x 16 block (i, j) of the wave's
       // 128 x 128 sub-tile: lane l holds column 16 j + (l & 15), rows 16 i +
       // 4 (l >> 4) .. + 3 (Epi::SWAP: row 16 i + (l & 15), columns 16 j +
@@ -752,17 +707,48 @@ __global__ void __launch_bounds__(GEMM_THREADS)
         auto rd_b = [&](int j, int kk, int buf) {
           return *(const bf16x8*)(smem + rb16[kk] + buf * HALF + j * 16 * ROW);
         };
-        // stages 0 and 1 whole (stage 1 in the loop's copy order, which the
-        // first stage's waits assume)
-#pragma unroll
-        for (int q = 0; q < NCOPY; ++q) copy_q(0, q, std::integral_constant<int, 0>{}, 0);
-#pragma unroll
-        for (int q = 0; q < NCOPY; ++q)
-          copy_q(1, CopySched<Epi>::a_first ? q : copy_order(q), std::integral_constant<int, 1>{}, 1);
-        wait_vmcnt<NCOPY>();        // stage 0 landed (stage pairs: nk >= 2)
-        __builtin_amdgcn_s_barrier();
         using P0 = std::integral_constant<int, 0>;
         using P1 = std::integral_constant<int, 1>;
+        if constexpr (ODD) {
+          // the first stage through buffer 1, the copies of the next behind it
+#pragma unroll
+          for (int q = 0; q < NCOPY; ++q) copy_q(0, q, P1{});
+          const int more = nk > 1 ? 1 : 0;
+          a_base += more * a_ks;
+          b_base += more * b_ks;
+          nk -= 1;
+#pragma unroll
+          for (int q = 0; q < NCOPY; ++q) copy_q(0, q, P0{});
+          wait_vmcnt<NCOPY>();
+          __builtin_amdgcn_s_barrier();
+          static_for<2>([&](auto kk_c) {
+            constexpr int kk = decltype(kk_c)::value;
+            bf16x8 b[8];
+            static_for<8>([&](auto j_c) { b[j_c.value] = rd_b(j_c.value, kk, 1); });
+            static_for<8>([&](auto i_c) {
+              constexpr int i = decltype(i_c)::value;
+              const bf16x8 a = rd_a(i, kk, 1);
+              static_for<8>([&](auto j_c) {
+                constexpr int j = decltype(j_c)::value;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    Epi::SWAP ? b[j] : a, Epi::SWAP ? a : b[j], acc[i][j], 0, 0, 0);
+              });
+            });
+          });
+          // every wave is done with buffer 1
+          asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+          if (nk == 0) return;
+        }
+        // stages 0 and 1 whole (stage 1 in the loop's copy order, which the
+        // first stage's waits assume)
+        if constexpr (!ODD)
+#pragma unroll
+        for (int q = 0; q < NCOPY; ++q) copy_q(0, q, P0{});
+#pragma unroll
+        for (int q = 0; q < NCOPY; ++q)
+          copy_q(1, CopySched<Epi>::a_first ? q : copy_order(q), P1{});
+        wait_vmcnt<NCOPY>();        // stage 0 landed (stage pairs: nk >= 2)
+        __builtin_amdgcn_s_barrier();
         // stage 0's fragments
         bf16x8 fa[8][2], fa7[2], fb[2][8][2];
 #pragma unroll
@@ -816,7 +802,7 @@ __global__ void __launch_bounds__(GEMM_THREADS)
                                                                 Epi::SWAP ? a : b, acc[i][j], 0, 0, 0);
             if constexpr (op >= MF16_COPY && op < MF16_COPY + 16) {
               constexpr int c = op - MF16_COPY;
-              copy_q(kc, CopySched<Epi>::a_first ? c : copy_order(c), PC{}, P);
+              copy_q(kc, CopySched<Epi>::a_first ? c : copy_order(c), PC{});
             } else if constexpr (op >= MF16_BREAD && op < MF16_BREAD + 16) {
               constexpr int n = op - MF16_BREAD;
               fb[P ^ 1][n >> 1][n & 1] = rd_b(n >> 1, n & 1, P ^ 1);
@@ -860,94 +846,6 @@ __global__ void __launch_bounds__(GEMM_THREADS)
         } else
         epi.tile16(acc, m0, n0, tn, M, N, smem, wm, wn, lane_e, wave * 64 + lane_e);
       }
-    } else {
-      f32x16 acc[4][4];
-  #pragma unroll
-      for (int i = 0; i < 4; ++i)
-  #pragma unroll
-        for (int j = 0; j < 4; ++j)
-  #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-      if (nk > 0) {
-        // stage 0 whole; stage 1's slot 0..15 copies (stage 0 issues the rest)
-  #pragma unroll
-        for (int q = 0; q < NCOPY; ++q) copy_q(0, q, std::integral_constant<int, 0>{}, 0);
-        if (nk > 1) {
-  #pragma unroll
-          for (int c = 0; c < NEARLY; ++c)
-            copy_q(1, copy_order(c), std::integral_constant<int, 1>{}, 1);
-          wait_vmcnt<NEARLY>();      // stage 0 landed
-        } else {
-          wait_vmcnt<0>();
-        }
-        __builtin_amdgcn_s_barrier();
-        // the fragment read paired with MFMA q of a slice (slice kn, buffer
-        // offset off): A blocks first, then B
-        auto frag = [&](int q, int kn, int off, bf16x8 (&fan)[4], bf16x8 (&fbn)[4]) {
-          if (q < 4)
-            fan[q] = *(const bf16x8*)(smem + ra[kn] + off + q * 32 * ROW);
-          else if (q < 8)
-            fbn[q - 4] = *(const bf16x8*)(smem + rb[kn] + off + (q - 4) * 32 * ROW);
-        };
-        bf16x8 fa[2][4], fb[2][4];
-  #pragma unroll
-        for (int q = 0; q < 16; ++q) frag(q, 0, 0, fa[0], fb[0]);
-
-        // stage kt reads buffer kt % NB
-        auto stage = [&](int kt, auto refill_c, auto more_c) {
-          constexpr bool REFILL = decltype(refill_c)::value;   // copy stage kt + NB
-          constexpr bool MORE = decltype(more_c)::value;       // stage kt + 1 exists
-          const int pr = kt % NB;
-          const int cur_off = pr * HALF, nxt_off = (pr ^ 1) * HALF;
-          __builtin_amdgcn_sched_barrier(0);
-  #pragma unroll
-          for (int kk = 0; kk < KK; ++kk) {
-            const int cur = kk & 1, nxt = cur ^ 1;
-            if (kk == KK - 1) {
-              if constexpr (MORE) {
-                // stage kt+1 landed (its copies are the only ones in flight)
-                wait_vmcnt<0>();
-              }
-              asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-              __builtin_amdgcn_s_barrier();
-              __builtin_amdgcn_sched_barrier(0);
-            }
-  #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-              const int i = q >> 2, j = q & 3;
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[i][j],
-                                                                  0, 0, 0);
-              if (kk < KK - 1) {
-                frag(q, kk + 1, cur_off, fa[nxt], fb[nxt]);
-                if constexpr (MORE) {
-                  const int slot = 16 * (kk + 1) + q;
-                  if (slot % CSTRIDE == 0 && slot / CSTRIDE < NCOPY)
-                    copy_q(kt + 1, copy_order(slot / CSTRIDE), BUF_RT{}, pr ^ 1);
-                }
-              } else {
-                if constexpr (MORE) frag(q, 0, nxt_off, fa[nxt], fb[nxt]);
-                if constexpr (REFILL) {
-                  if (q % CSTRIDE == 0) copy_q(kt + NB, copy_order(q / CSTRIDE), BUF_RT{}, pr);
-                }
-              }
-              __builtin_amdgcn_sched_barrier(0);
-            }
-          }
-        };
-        using T_ = std::true_type;
-        using F_ = std::false_type;
-        int kt = 0;
-        for (; kt + NB < nk; ++kt) stage(kt, T_{}, T_{});
-        for (; kt + 1 < nk; ++kt) stage(kt, F_{}, T_{});
-        stage(kt, F_{}, F_{});
-      }
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-      __syncthreads();
-      {
-        const int lane_e = fresh_lane();
-        epi.tile(acc, m0, n0, tn, M, N, smem, wm, wn, lane_e, wave * 64 + lane_e);
-      }
     }
     __syncthreads();
   }
@@ -970,87 +868,6 @@ struct EpiLseCols {
   int64_t ld_part;
   float* zy;             // [tokens] logit of the target token
   float scale;           // 1 / temperature
-
-  template <bool FULL>
-  __device__ __forceinline__ void cols(const f32x16 (&acc)[4][4], int m0, int n0, int M,
-                                       const int* sy, f32x2* red, int wm, int wn,
-                                       int lane) const {
-    const float k1 = scale * 1.44269504088896341f;
-    // this lane's rows are wm * 128 + hb + o with o = 32 i + 8 (r >> 2) + (r & 3)
-    const int hb = 4 * (lane >> 5);
-    const int lim = M - m0 - wm * 128 - hb;     // rows o >= lim are beyond the vocabulary
-    auto live = [&](int i, int r) { return FULL || 32 * i + 8 * (r >> 2) + (r & 3) < lim; };
-    float mx[4], sm[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) mx[j] = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) mx[j] = fmaxf(mx[j], live(i, r) ? acc[i][j][r] : -INFINITY);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 32));
-      sm[j] = 0.0f;
-    }
-    float mk[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) mk[j] = FULL || mx[j] != -INFINITY ? -mx[j] * k1 : 0.0f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float e = __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], k1, mk[j]));
-          sm[j] += live(i, r) ? e : 0.0f;
-        }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      sm[j] += __shfl_xor(sm[j], 32);
-      const int c = wn * 128 + j * 32 + (lane & 31);
-      if (lane < 32) red[wm * GBN + c] = f32x2{mx[j] * scale, sm[j]};
-      // target logit: local row o of the target, held here iff 0 <= o < 128 and
-      // bit 2 of o is clear; the register is picked by a select tree over o's bits
-      const int o = sy[c] - wm * 128 - hb;
-      float v[64];
-#pragma unroll
-      for (int q = 0; q < 64; ++q) v[q] = acc[q >> 4][j][q & 15];
-      const int idx = ((o >> 5) << 4) | (((o >> 3) & 3) << 2) | (o & 3);
-#pragma unroll
-      for (int b = 0, w = 32; b < 6; ++b, w >>= 1) {
-        const bool hi = (idx >> b) & 1;
-#pragma unroll
-        for (int q = 0; q < w; ++q) v[q] = hi ? v[2 * q + 1] : v[2 * q];
-      }
-      if ((unsigned)o < 128u && (o & 4) == 0) zy[n0 + c] = v[0] * scale;
-    }
-  }
-
-  __device__ __forceinline__ void tile(f32x16 (&acc)[4][4], int m0, int n0, int tn, int M,
-                                       int N, uint8_t* smem, int wm, int wn, int lane,
-                                       int tid) const {
-    int* sy = (int*)smem;
-    f32x2* red = (f32x2*)(smem + 1024);
-    // target row relative to the tile (-1: dead column; a target outside the
-    // tile matches no row)
-    sy[tid] = (n0 + tid < N) ? y[n0 + tid] - m0 : -1;
-    __syncthreads();
-    if (m0 + GBM <= M)
-      cols<true>(acc, m0, n0, M, sy, red, wm, wn, lane);
-    else
-      cols<false>(acc, m0, n0, M, sy, red, wm, wn, lane);
-    __syncthreads();
-    const int col = n0 + tid;
-    if (col < N) {
-      const f32x2 a = red[tid], b = red[GBN + tid];
-      const float m = fmaxf(a.x, b.x);
-      const float s = (a.y > 0.0f ? a.y * __expf(a.x - m) : 0.0f) +
-                      (b.y > 0.0f ? b.y * __expf(b.x - m) : 0.0f);
-      part[(int64_t)(m0 / GBM) * ld_part + col] = f32x2{m, s};
-    }
-  }
 
   // The same on the 16 x 16 accumulator layout: lane l holds 8 token columns
   // (16 j + (l & 15)) and 32 vocabulary rows of each (16 i + 4 (l >> 4) + r),
@@ -1155,47 +972,6 @@ struct EpiLogitGrad {
   float scale;
   int32_t col0;          // vocabulary index of this chunk's column 0
 
-  template <bool FULL, int h>
-  __device__ __forceinline__ void stage_pass(const f32x16 (&acc)[4][4], int n0, int N,
-                                             uint8_t* smem, int wm, int wn, int lane) const {
-    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    const float k1 = scale * 1.44269504088896341f;
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii) {
-      const int i = 2 * h + ii;
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const int rt = acc_row(wm, i, r4 * 4, lane);      // tile row of element q = 0
-        const i32x4 ry = *(const i32x4*)(smem + EPI_META + 4 * rt);
-        const f32x4 rn = *(const f32x4*)(smem + EPI_META + 1024 + 4 * rt);
-        const f32x4 rg = *(const f32x4*)(smem + EPI_META + 2048 + 4 * rt);
-        const int lr = wm * 64 + ii * 32 + 8 * r4 + 4 * (lane >> 5);   // pass-local row
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int cl = acc_col(wn, j, lane);
-          float gv[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float p = __builtin_amdgcn_exp2f(fmaf(acc[i][j][r4 * 4 + q], k1, rn[q]));
-            gv[q] = fmaf(-rg[q], p, cl == ry[q] ? rg[q] : 0.0f);
-            if constexpr (!FULL) gv[q] = n0 + cl < N ? gv[q] : 0.0f;
-          }
-          const uint32_t p01 = __builtin_bit_cast(
-              uint32_t, __builtin_convertvector(f32x2{gv[0], gv[1]}, bf16x2_t));
-          const uint32_t p23 = __builtin_bit_cast(
-              uint32_t, __builtin_convertvector(f32x2{gv[2], gv[3]}, bf16x2_t));
-          uint8_t* gs_at = smem + EPI_GS + lr * EPI_G_ROW + cl * 2;
-          *(uint16_t*)(gs_at) = (uint16_t)p01;
-          *(uint16_t*)(gs_at + EPI_G_ROW) = (uint16_t)(p01 >> 16);
-          *(uint16_t*)(gs_at + 2 * EPI_G_ROW) = (uint16_t)p23;
-          *(uint16_t*)(gs_at + 3 * EPI_G_ROW) = (uint16_t)(p23 >> 16);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
-
   // per tile row: target column relative to the tile, -lse * log2(e) (-inf on
   // dead rows, so their exponentials are 0 and G is +0 there), dL/dlogp
   __device__ __forceinline__ void meta(int m0, int n0, int M, uint8_t* smem, int tid) const {
@@ -1204,17 +980,6 @@ struct EpiLogitGrad {
     ((float*)(smem + EPI_META + 1024))[tid] =
         live ? -lse[m0 + tid] * 1.44269504088896341f : -INFINITY;
     ((float*)(smem + EPI_META + 2048))[tid] = live ? gs[m0 + tid] : 0.0f;
-  }
-
-  __device__ __forceinline__ void tile(f32x16 (&acc)[4][4], int m0, int n0, int tn, int M,
-                                       int N, uint8_t* smem, int wm, int wn, int lane,
-                                       int tid) const {
-    meta(m0, n0, M, smem, tid);
-    __syncthreads();
-    const bool full = n0 + GBN <= N;
-    pass<0>(acc, full, m0, n0, N, smem, wm, wn, lane, tid);
-    __syncthreads();
-    pass<1>(acc, full, m0, n0, N, smem, wm, wn, lane, tid);
   }
 
   // 16 x 16 swapped accumulators: pass h takes blocks i = 4 h .. 4 h + 3 of both
@@ -1275,20 +1040,6 @@ struct EpiLogitGrad {
       stage_pass16<false, 1>(acc, n0, N, smem, wm, wn, lane);
     __syncthreads();
     copy_out<1>(m0, n0, smem, tid);
-  }
-
-  template <int h>
-  __device__ __forceinline__ void pass(const f32x16 (&acc)[4][4], bool full, int m0, int n0,
-                                       int N, uint8_t* smem, int wm, int wn, int lane,
-                                       int tid) const {
-    {
-      if (full)
-        stage_pass<true, h>(acc, n0, N, smem, wm, wn, lane);
-      else
-        stage_pass<false, h>(acc, n0, N, smem, wm, wn, lane);
-      __syncthreads();
-      copy_out<h>(m0, n0, smem, tid);
-    }
   }
 
   // G: 128 rows of 512 bytes staged in LDS by pass h; pass rows 0..63 are tile

@@ -744,16 +744,14 @@ void launch_gemm(const GemmShape* g, const Epi* e, int n, int max_tiles, int32_t
   // pairs (the vocabulary chunk rounded up to 128, the device-read token count
   // rounded up in the kernel), so it always runs the 16 x 16 loop.
   if constexpr (std::is_base_of<EpiStore, Epi>::value) {
-    hipLaunchKernelGGL((gemm_bf16_kernel<Epi, true, true, true>), dim3(grid), dim3(GEMM_THREADS),
-                       0, s, b);
+    hipLaunchKernelGGL((gemm_bf16_kernel<Epi, true>), dim3(grid), dim3(GEMM_THREADS), 0, s, b);
   } else {
-    // K (the hidden size) a whole number of stage pairs
+    // K, the hidden size: a whole number of stage pairs, or one stage more
     if (g[0].K % (2 * bf16k::SK) == 0)
-      hipLaunchKernelGGL((gemm_bf16_kernel<Epi, true, false, true>), dim3(grid),
-                         dim3(GEMM_THREADS), 0, s, b);
+      hipLaunchKernelGGL((gemm_bf16_kernel<Epi, false>), dim3(grid), dim3(GEMM_THREADS), 0, s, b);
     else
-      hipLaunchKernelGGL((gemm_bf16_kernel<Epi, false, false>), dim3(grid), dim3(GEMM_THREADS),
-                         0, s, b);
+      hipLaunchKernelGGL((gemm_bf16_kernel<Epi, false, true>), dim3(grid), dim3(GEMM_THREADS), 0,
+                         s, b);
   }
   record(o, 2 * ph + 1, s);
   if (ph2 >= 0) {
