@@ -99,7 +99,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _stream(stream) -> ctypes.c_void_p:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the handle of torch.cuda.current_stream() without the Stream object, which costs
+        # as much host time (4 us) as the launch of a small call
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
