@@ -311,8 +311,12 @@ struct CopySched<EpiStore> {
   static constexpr bool serpentine = true;
   static constexpr bool round_sync = true;
 };
+// (with few tokens dW's tiles are short and the sync costs more than the panels it keeps
+// in step: 1.80 -> 1.56 ms at 700 tokens, 6.44 -> 6.37 at 2871, 8.90 -> 8.92 at 6000)
 template <>
-struct CopySched<EpiGrad> : CopySched<EpiStore> {};
+struct CopySched<EpiGrad> : CopySched<EpiStore> {
+  static constexpr bool round_sync = false;
+};
 constexpr int ROUND_SLACK = 2;   // tiles of the earlier rounds that may still run
 constexpr int ROUND_SPIN = 32;   // polls of the finished-tile counter (~0.3 us apart)
 
@@ -363,8 +367,8 @@ __device__ __forceinline__ int queue_tile(int k, const QueueShare& s, int q, int
 // V = 152064, 3 ms, whatever the chip could do beside it): parts of a third of a compute
 // unit's share of the launch let the queues balance them against dW's tiles, whose
 // epilogue (256 KiB written) costs about 12 stages.  dH + dW at V = 152064, d = 3584, 700
-// tokens, dW accumulated: 3250 us in one piece (and 400 us of W^T before it), 2080 us in
-// parts; V = 43776, d = 1088, 2122 tokens: 750 and 415 us.  2 or 5 instead of 3, or 24
+// tokens, dW accumulated: 3250 us in one piece (and 400 us of W^T before it), 1830 us in
+// parts; V = 43776, d = 1088, 2122 tokens: 750 and 418 us.  2 or 5 instead of 3, or 24
 // stages for the epilogue, are within the runs' noise.
 constexpr int DH_PARTS = 3, DW_EPI_STAGES = 12, DH_MIN_STAGES = 16;
 __host__ __device__ inline int dh_split(int n_act, int nv, int d, int cus, int most) {
@@ -847,7 +851,9 @@ __global__ void __launch_bounds__(GEMM_THREADS)
         epi.tile16(acc, m0, n0, tn, M, N, smem, wm, wn, lane_e, wave * 64 + lane_e);
       }
     }
-    __syncthreads();
+    // the next tile's copies overwrite what the epilogue staged in LDS; its stores stay
+    // in flight under the next tile's claim and first copies
+    lds_barrier();
   }
 }
 
@@ -1102,24 +1108,36 @@ struct EpiStore {
                                         float* st, const int* sr, int wm, int wn, int lane) const {
     const int wave = wm * 2 + wn;
     const bool col_ok = n0 + 4 * lane < N;         // N is a multiple of 64
-    f32x4 old[16];
-    // staged row pr of pass h is tile row 64 h + pr (pr < 64) or 64 h + pr + 64; wave w
-    // writes rows w, w + 4, ...  (dst is null for a row past M or a column past N)
-    auto dst = [&](int h, int k) {
-      const int pr = wave + 4 * k, tr = 64 * h + (pr < 64 ? pr : pr + 64);
-      const int64_t row = row_map ? (int64_t)sr[tr] : (int64_t)(m0 + tr);
-      return m0 + tr < M && col_ok ? (f32x4*)(out + row * ldo + n0 + 4 * lane) : nullptr;
+    // Staged row pr of pass h is tile row 64 h + pr (pr < 64) or 64 h + pr + 64; wave w
+    // handles rows w, w + 4, ... in two batches of 16, the first below 64.  Lane k holds
+    // output row k of a batch; a row's address is then a scalar, two multiplies and an add
+    // (with a 64-bit address and an exec mask formed per row and lane, the 32 stores of a
+    // pass took 7.7k cycles; dH + dW at V = 152064, d = 3584, 700 tokens 1.60 -> 1.47 ms).
+    const uint32_t ld_b = (uint32_t)(ldo * 4);
+    int rows = 0;
+    auto first = [&](int h, int b) { return 64 * h + 128 * b + wave; };     // tile row
+    auto batch = [&](int h, int b) {
+      const int tr = first(h, b) + 4 * (lane & 15);
+      rows = row_map ? sr[tr] : m0 + tr;
     };
-    auto read = [&](int h, int k0) {
+    auto at = [&](int k) {
+      const uint32_t row = __builtin_amdgcn_readlane(rows, k);
+      return (f32x4*)((char*)(out + n0) + (uint64_t)row * ld_b + (uint32_t)(16 * lane));
+    };
+    f32x4 old[16];
+    // (vmcnt counts stores too and in order: the next rows are read before a batch is
+    // stored, also across the passes, so that no read waits for a store)
+    auto read = [&](int h, int b) {
+      batch(h, b);
+      if (col_ok) {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const f32x4* p = dst(h, k0 + k);
-        old[k] = p ? *p : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k = 0; k < 16; ++k)
+          if (m0 + first(h, b) + 4 * k < M) old[k] = *at(k);
       }
     };
+    if constexpr (ACC) read(0, 0);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      if constexpr (ACC) read(h, 0);
       if (h) lds_barrier();                        // pass 0's rows have been read
 #pragma unroll
       for (int ii = 0; ii < 4; ++ii)
@@ -1129,20 +1147,21 @@ struct EpiStore {
                     4 * (lane >> 4)) = acc[4 * h + ii][j];
       lds_barrier();                               // rows staged
 #pragma unroll
-      for (int k0 = 0; k0 < 32; k0 += 16) {
+      for (int b = 0; b < 2; ++b) {
         f32x4 v[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-          v[k] = *(const f32x4*)(st + (wave + 4 * (k0 + k)) * EPI_F32_ROW + 4 * lane);
+          v[k] = *(const f32x4*)(st + (wave + 64 * b + 4 * k) * EPI_F32_ROW + 4 * lane);
           if constexpr (ACC) v[k] += old[k];
         }
         if constexpr (ACC) {
-          if (k0 == 0) read(h, 16);
+          if (h == 0 || b == 0) read(h + b, 1 - b);
         }
+        batch(h, b);
+        if (col_ok) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          f32x4* p = dst(h, k0 + k);
-          if (p) *p = v[k];
+          for (int k = 0; k < 16; ++k)
+            if (m0 + first(h, b) + 4 * k < M) *at(k) = v[k];
         }
       }
     }
