@@ -1014,7 +1014,7 @@ struct EpiLogitGrad {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const float p = __builtin_amdgcn_exp2f(fmaf(acc[i][j][q], k1, rn));
-          gv[q] = fmaf(-rg, p, 16 * j + q == oy ? rg : 0.0f);
+          gv[q] = fmaf(-rg, p, 0.0f);
           if constexpr (!FULL) gv[q] = n0 + c0 + 16 * j + q < N ? gv[q] : 0.0f;
         }
         *(u32x2*)(gs_at + 32 * j) =
@@ -1022,6 +1022,20 @@ struct EpiLogitGrad {
                                      __builtin_convertvector(f32x2{gv[0], gv[1]}, bf16x2_t)),
                   __builtin_bit_cast(uint32_t,
                                      __builtin_convertvector(f32x2{gv[2], gv[3]}, bf16x2_t))};
+      }
+      // a token whose target lies in this lane's columns (rare: one tile in V / 256 per
+      // token) gets that entry again, instead of a compare and a select per entry: 11780
+      // -> 11700 us per chunk at d = 5120, 22793 tokens, 3205 -> 3157 at 2871
+      const bool held = (unsigned)oy < 128u && (oy & 12) == 0;
+      if (__any(held)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (oy == 16 * j + q) {
+              const float p = __builtin_amdgcn_exp2f(fmaf(acc[i][j][q], k1, rn));
+              *(uint16_t*)(gs_at + 32 * j + 2 * q) = f32_to_bf16_bits(fmaf(-rg, p, rg));
+            }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
