@@ -34,7 +34,7 @@ PEAK_BF16 = 2.5e15          # MI355X dense bf16 matrix-core peak, FLOP/s
 PEAK_F32 = 157.3e12
 HBM_PEAK = 8.0e12
 METRIC = "policy-loss fwd+bwd tokens/s and % of bf16 MFMA peak, 1 MI355X"
-PHASES = ["forward logits + lse", "backward logit recompute -> G", "dW = G^T H (+ dH = G W in the same launch for bf16)", "dH = G W (separate launch)"]
+PHASES = ["forward logits + lse", "backward logit recompute -> G", "dW = G^T H and dH = G W (one launch)", "dH = G W (separate launch)"]
 
 
 class HipEvents:
@@ -385,7 +385,8 @@ def main():
     kernel_names = ["gemm_bf16_kernel<EpiLseCols>", "gemm_bf16_kernel<EpiLogitGrad>",
                     "gemm_bf16_kernel<EpiStore>", "gemm_bf16_kernel<EpiStore>"]
     if code != P.AGRL_BF16:
-        kernel_names = [k.replace("gemm_bf16_kernel", "gemm_nt_kernel") for k in kernel_names]
+        kernel_names = ["f32_logits_kernel<forward>", "f32_logits_kernel<G>", "f32_grad_kernel",
+                        "f32_grad_kernel"]
     dom_kernel = kernel_names[dom]
     rec = committed_traffic(w.spec.name, dom_kernel + (" grouped" if grouped and dom == 2 else ""))
     step_flops = 4 * gemm_flops

@@ -112,7 +112,8 @@ typedef struct {
   /* agrl_task_adv_norm only: NULL, or a device array of 2 * (n_group + n_task)
    * int32 (2 * n_task without traj_group) that the call uses as scratch.  With
    * it, the call records the lowest and the highest index of each group's and
-   * each task's trajectories, and each group's and task's wave scans only that
+   * each task's trajectories (a batch small enough for one workgroup does not
+   * need them and leaves it as it is), and each group's and task's wave scans only that
    * index range instead of all n_traj trajectories: the stages then take work
    * proportional to the members' spans rather than n_group * n_traj and
    * n_task * n_traj (trajectories stored segment by segment make every span its

@@ -181,24 +181,31 @@ __global__ __launch_bounds__(kCompactRows) void compact_kernel(CompactArgs a) {
   int before = 0, total = 0;
   const int64_t from = a.blk_off ? base / kScanTile * kScanTile : 0;
   const int64_t to = a.blk_off ? base : a.T;
-  if (((uintptr_t)a.mask & 15) == 0) {         // base and from are multiples of 256
-    const int64_t whole = from + (to - from) / 16 * 16;
+  // 16-byte words of the mask between the bytes before its first and after its last whole
+  // word (a micro-batch's mask may start anywhere in the batch's)
+  const int64_t head = min(to, from + (int64_t)((16 - ((uintptr_t)a.mask & 15)) & 15));
+  const int64_t whole = head + (to - head) / 16 * 16;
 #pragma unroll 4
-    for (int64_t c = from + 16 * tid; c < whole; c += 16 * kCompactRows) {
-      const u32x4 v = *(const u32x4*)(a.mask + c);
-      const int n = nonzero_bytes(v[0]) + nonzero_bytes(v[1]) + nonzero_bytes(v[2]) +
-                    nonzero_bytes(v[3]);
-      total += n;
-      before += c < base ? n : 0;
+  for (int64_t c = head + 16 * tid; c < whole; c += 16 * kCompactRows) {
+    const u32x4 v = *(const u32x4*)(a.mask + c);
+    const int n = nonzero_bytes(v[0]) + nonzero_bytes(v[1]) + nonzero_bytes(v[2]) +
+                  nonzero_bytes(v[3]);
+    total += n;
+    if (c + 16 <= base) {
+      before += n;
+    } else if (c < base) {                     // base lies inside the word
+      const int in_base = (int)(base - c);
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        before += e < in_base && ((v[e >> 2] >> (8 * (e & 3))) & 0xFFu) != 0;
     }
-    if (whole + tid < to) total += a.mask[whole + tid] != 0;
-  } else {
-#pragma unroll 8
-    for (int64_t c = from + tid; c < to; c += kCompactRows) {
-      const int n = a.mask[c] != 0;
-      total += n;
-      before += c < base ? n : 0;
-    }
+  }
+  const int odd = (int)(head - from);          // bytes before the words; fewer than 16 after
+  if (tid < odd + (int)(to - whole)) {
+    const int64_t c = tid < odd ? from + tid : whole + tid - odd;
+    const int n = a.mask[c] != 0;
+    total += n;
+    before += c < base ? n : 0;
   }
   for (int o = 32; o >= 1; o >>= 1) {
     before += __shfl_xor(before, o);
