@@ -33,8 +33,7 @@ constexpr int LDS_ROW = 128;                            // bytes per tile row pe
 constexpr int STAGE_BYTES = (GBM + GBN) * LDS_ROW;      // 64 KiB
 constexpr int GEMM_LDS = 2 * STAGE_BYTES;               // 128 KiB of stage buffers
 // bf16 logit-gradient epilogue (two passes of 128 tile rows): G rows staged
-// row-major with 528-byte pitch (the two half-waves of a 16-bit store land in
-// different banks); three 256-entry per-row arrays at EPI_META, above both the
+// row-major with 528-byte pitch; three 256-entry per-row arrays at EPI_META, above both the
 // stage buffers and the store epilogue's 130 KiB staging of a pass
 constexpr int EPI_G_ROW = 528;
 constexpr int EPI_GS = 0;
@@ -107,7 +106,7 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) void glb_void_t;
 
 // ---------------------------------------------------------------------------
-// bf16 kernel.  Same tile, waves and swizzle as above, with a software
+// The kernel: the tile, waves and swizzle described at the top, with a software
 // pipeline tuned for one wave per SIMD:
 //   * the per-lane global offsets of the stage copies are computed once per
 //     tile (32-bit, relative to the tile's first row); each stage only moves a

@@ -52,7 +52,10 @@ struct Tile {
 
   // p: element (row r0, k = 0) of the operand; rows: rows from r0 to the end
   __device__ __forceinline__ void init(const float* p, int64_t ld, int rows, int wave, int lane) {
-    base = (const uint8_t*)p;
+    // The base is the first row that the wave copies (64 rows of at most 2^23 floats, or 32
+    // k-rows, stay within the 32-bit offsets; a tile's 256 rows would not)
+    const int first = KM ? 0 : min(wave * NC * 8, rows - 1);
+    base = (const uint8_t*)(p + first * ld);
     ld_b = (uint32_t)(ld * 4);
     if constexpr (KM) {
       step = (int64_t)SK * ld * 4;
@@ -66,7 +69,7 @@ struct Tile {
 #pragma unroll
       for (int b = 0; b < NC; ++b) {
         const int row = (wave * NC + b) * 8 + (lane >> 3);
-        off[b] = (uint32_t)min(row, rows - 1) * ld_b +
+        off[b] = (uint32_t)(min(row, rows - 1) - first) * ld_b +
                  (uint32_t)(((lane & 7) ^ row_swizzle(row)) << 4);
       }
     }

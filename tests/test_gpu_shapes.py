@@ -121,3 +121,23 @@ def test_compaction(T, offset):
 @pytest.mark.parametrize("V,d,n_act", [(700, 64, 300), (513, 192, 257), (1000, 1088, 40)])
 def test_bf16_odd_stages(V, d, n_act):
     _case(torch.bfloat16, V, d, n_act)
+
+
+# fp32 with rows so long that a tile's last rows lie more than 2^32 bytes after its first,
+# against fp64.  A logit is a sum of 2^22 terms of rms 2^-11 whose partial sums are of order 1,
+# each rounded by up to 2^-24 of itself: a random walk of 2^11 * 2^-24 = 1.2e-4.
+def test_fp32_rows_beyond_32_bit_offsets():
+    import paper_2510_04206_amd as P
+    T, V, d = 2, 256, 4210816                        # 255 * 4 d = 2^32 + 65024
+    log(f"long fp32 rows V={V} d={d}")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    H = torch.randn((T, d), generator=g, device="cuda")
+    W = torch.randn((V, d), generator=g, device="cuda").mul_(d ** -0.5)
+    y = torch.tensor([5, V - 1], dtype=torch.int32, device="cuda")
+    mask = torch.tensor([0, 1], dtype=torch.uint8, device="cuda")
+    lp = P.TokenLogprob(T, d, V, H.dtype, max_act=1)
+    logp, lse = lp(H, W, y, mask)
+    assert P.agrl_get_device_error() == 0
+    z = torch.stack([torch.dot(H[1].double(), w.double()) for w in W])
+    assert abs(lse[1].item() - z.logsumexp(0).item()) < 1e-3
+    assert abs(logp[1].item() - torch.log_softmax(z, 0)[V - 1].item()) < 1e-3
