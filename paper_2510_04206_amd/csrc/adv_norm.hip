@@ -65,11 +65,39 @@ struct Tokens {
       m[i >> 2] |= (in && mask[t0 + i] ? 1u : 0u) << (8 * (i & 3));
     }
   }
+  // Trajectories are mostly longer than 16 tokens, so a lane nearly always has one of them or
+  // two: their action tokens are then counted as bits, about half the instructions of the walk,
+  // which is what bounded a workgroup that counts all the tokens: 12.5 -> 8.4 us a call of
+  // sequence weights at 65536 tokens, 640 trajectories; 33.1 -> 31.7 us a large advantage call.
   __device__ __forceinline__ Run count(int32_t n_traj, int32_t* count, int* err) const {
-    Run r;
+    uint32_t changes = 0;                  // bit i: token i's id differs from the one before
 #pragma unroll
-    for (int i = 0; i < kCountPerLane; ++i)
-      r.token(ids[i >> 2][i & 3], (m[i >> 2] >> (8 * (i & 3))) & 0xFFu, n_traj, count, err);
+    for (int i = 1; i < kCountPerLane; ++i)
+      changes |= (ids[i >> 2][i & 3] != ids[(i - 1) >> 2][(i - 1) & 3] ? 1u : 0u) << i;
+    Run r;
+    if (changes & (changes - 1)) {
+#pragma unroll
+      for (int i = 0; i < kCountPerLane; ++i)
+        r.token(ids[i >> 2][i & 3], (m[i >> 2] >> (8 * (i & 3))) & 0xFFu, n_traj, count, err);
+      return r;
+    }
+    uint32_t act = 0;                      // bit 8 j + k: token 4 k + j is an action token
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      act |= ((((m[k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | m[k]) & 0x80808080u) >> (7 - k);
+    const int first = ids[0][0], last = ids[3][3];
+    if (max(first, last) >= n_traj) set_error(err, ERR_TRAJ_ID);
+    uint32_t head = 0;                     // the tokens before the change, if there is one
+    if (changes) {
+      const int at = __builtin_ctz(changes), k = at >> 2, j = at & 3;
+      head = ((0x01010101u << k) - 0x01010101u) | ((0x01010101u & ((1u << (8 * j)) - 1)) << k);
+      const int n = __popc(act & head);
+      if (n && first >= 0 && first < n_traj) atomicAdd(&count[first], n);
+    }
+    if (last >= 0 && last < n_traj) {
+      r.cur = last;
+      r.cnt = __popc(act & ~head);
+    }
     return r;
   }
 };
@@ -163,7 +191,7 @@ __device__ __forceinline__ void check_ids(const IdArgs& a, int j, int32_t n_traj
 
 // The token counts, and beside them the id checks, which do not need them: the first
 // id_blocks blocks take 256 trajectories each, the others 256 * kCountPerLane tokens.
-// One launch less at 2560 trajectories and 9M tokens: 38.6 -> 33.6 us a call.  (Ranges
+// One launch less at 2560 trajectories and 9M tokens: 38.6 -> 33.6 us a call (31.7 since).  (Ranges
 // preset and recorded by one block: 16.3 us for that launch alone.)
 template <bool VEC>
 __global__ __launch_bounds__(256) void count_kernel(int64_t T_g, int32_t n_traj,
@@ -472,7 +500,7 @@ __global__ __launch_bounds__(256) void seq_weight_kernel(int64_t T, int32_t n_tr
 
 // The same in one launch, counters in LDS: every workgroup counts all the tokens itself
 // (kSeqTokens: 4 lots of 16 a thread, from L2) and weighs its share of them.  640
-// trajectories, 65536 tokens: 17.3 us a call in three launches (the host's), 12.6 in one.
+// trajectories, 65536 tokens: 17.3 us a call in three launches (the host's), 8.4 in one.
 constexpr int kSeqTraj = 4096;
 constexpr int64_t kSeqTokens = 65536;
 constexpr int kSeqShare = 4096;          // tokens a workgroup weighs

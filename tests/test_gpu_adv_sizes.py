@@ -63,3 +63,23 @@ def test_sequence_weight_sizes(n_traj, T, offset):
     want_count, want_w = oracle.sequence_mean_weights(ids[offset:], mask[offset:], n_traj)
     np.testing.assert_array_equal(count.cpu().numpy(), want_count)
     np.testing.assert_array_equal(w.cpu().numpy().view(np.uint32), want_w.view(np.uint32))
+
+
+# a lane's 16 tokens with no, one (at each place) and several changes of trajectory, ids that
+# are skipped among them; any nonzero mask byte is an action token
+@pytest.mark.parametrize("T,n_traj", [(4096, 256), (70000, 5000)])
+def test_count_trajectory_changes(T, n_traj):
+    import paper_2510_04206_amd as P
+    rng = np.random.default_rng(T)
+    ids = np.repeat(rng.integers(-1, n_traj, T // 16 + 1), 16)[:T].astype(np.int32)
+    for at in range(T // 16):
+        if at % 3:
+            ids[16 * at + at % 16:16 * at + 16] = rng.integers(-1, n_traj)
+        if at % 7 == 0:
+            ids[16 * at + 5:16 * at + 9] = rng.integers(0, n_traj)
+    mask = np.where(rng.random(T) < 0.5, rng.integers(1, 256, T), 0).astype(np.uint8)
+    log(f"trajectory changes T={T}")
+    count, _ = P.sequence_mean_weights(torch.from_numpy(ids).cuda(), torch.from_numpy(mask).cuda(), n_traj)
+    assert P.agrl_get_device_error() == 0
+    want = np.bincount(ids[(mask != 0) & (ids >= 0)], minlength=n_traj)
+    np.testing.assert_array_equal(count.cpu().numpy(), want)
