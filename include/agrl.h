@@ -42,6 +42,9 @@
  *     makes its dH row and every row of dW NaN.  Other tokens' logp and lse
  *     are unaffected.  With more action tokens than max_act the loss is NaN
  *     and the other outputs are unspecified.
+ *   - A NaN or +inf logit makes its token's logp and lse non-finite and the
+ *     loss NaN (a NaN old_logp on an action token the loss); a -inf logit
+ *     carries no weight.
  *   - Results are deterministic: every reduction has a fixed order, no
  *     floating-point atomics are used.
  */

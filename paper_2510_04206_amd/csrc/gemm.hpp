@@ -899,7 +899,7 @@ struct EpiLseCols {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 32));
-      mk[j] = FULL || mx[j] != -INFINITY ? -mx[j] * k1 : 0.0f;
+      mk[j] = mx[j] != -INFINITY ? -mx[j] * k1 : 0.0f;
       sm[j] = 0.0f;
     }
 #pragma unroll
@@ -952,8 +952,10 @@ struct EpiLseCols {
     if (col < N) {
       const f32x2 a = red[tid], b = red[GBN + tid];
       const float m = fmaxf(a.x, b.x);
-      const float s = (a.y > 0.0f ? a.y * __expf(a.x - m) : 0.0f) +
-                      (b.y > 0.0f ? b.y * __expf(b.x - m) : 0.0f);
+      // only an empty sum is left out (its max may be -inf): a NaN or infinite logit makes
+      // its half's sum NaN, and with it the token's lse
+      const float s = (a.y == 0.0f ? 0.0f : a.y * __expf(a.x - m)) +
+                      (b.y == 0.0f ? 0.0f : b.y * __expf(b.x - m));
       part[(int64_t)(m0 / GBM) * ld_part + col] = f32x2{m, s};
     }
   }

@@ -285,7 +285,7 @@ __global__ __launch_bounds__(THREADS, 2) void f32_logits_kernel(LogitsArgs g) {
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         const f32x2 p = red[w * 32 * BJ + c];
-        s += p.y > 0.0f ? p.y * __expf(p.x - m) : 0.0f;
+        s += p.y == 0.0f ? 0.0f : p.y * __expf(p.x - m);   // (a NaN sum stays)
       }
       g.part[(int64_t)(m0 / 256) * g.ld_part + n0 + c] = f32x2{m, s};
     }

@@ -442,7 +442,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_loss_kernel(MergeArgs 
       f -= a.kl_beta * (a.kl_est == 1 ? -u : expm1f(u) - u);
     }
     sv = a.weighted ? (double)a.w_act[n] * (double)f : (double)f;
-    if (bad) sv = NAN;
+    if (isnan(rho)) sv = NAN;      // (the clamps above take the bound for a NaN; bad ids too)
     hi = (A > 0.0f && rho > 1.0f + a.eps_hi);
     lo = (A < 0.0f && rho < 1.0f - a.eps_lo);
     const int t = a.idx[n];
