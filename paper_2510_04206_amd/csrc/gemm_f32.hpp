@@ -189,6 +189,7 @@ struct LogitsArgs {
   float* G;                // [tokens][ldg]
   int64_t ldg;
   int32_t col0;            // vocabulary index of row 0
+  int32_t block0;          // workgroups of the launch before this one's (a multiple of 8)
 };
 
 // Two workgroups per compute unit: 72 or 80 KiB of LDS each.  A tile spans the 256
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(THREADS, 2) void f32_logits_kernel(LogitsArgs g) {
   const int n_act = __builtin_amdgcn_readfirstlane(*g.n_act);
   const int tiles_n = cdiv(n_act, 32 * BJ), tiles_m = cdiv(g.nv, 256);
   const int total = tiles_m * tiles_n;
-  const int t = xcd_item(blockIdx.x, total);
+  const int t = xcd_item(blockIdx.x + g.block0, total);
   if (t >= total) return;
   // all token tiles of a vocabulary tile in a row: its panel of W is read once
   const int m0 = (t / tiles_n) * 256, n0 = (t % tiles_n) * 32 * BJ;

@@ -772,17 +772,23 @@ void launch_gemm(const GemmShape* g, const Epi* e, int n, int max_tiles, int32_t
 // fill the two workgroups that fit a compute unit.  Either side of the line is flat:
 // 38.0 + 42.5 us wide against 41.0 + 36.5 us at V = 4096, d = 256, 1519 tokens (384 wide
 // tiles), 419 + 425 against 430 + 418 us at V = 16391, d = 1024, 1333 tokens.
+// (A launch holds fewer than 2^32 threads, 2^24 of these workgroups: 2^20 tokens on 2^18
+// vocabulary entries have more, so a launch stops at half of that.)
 template <bool GRAD>
-void launch_logits_f32(const f32k::LogitsArgs& g, int64_t rows, hipStream_t s) {
+void launch_logits_f32(f32k::LogitsArgs g, int64_t rows, hipStream_t s) {
+  constexpr int64_t kMost = (int64_t)1 << 23;
   const int tiles_m = cdiv(g.nv, 256);
   const int64_t wide = cdiv<int64_t>(rows, 64) * tiles_m;
-  if (wide >= 2 * device_cu_count())
-    hipLaunchKernelGGL((f32k::f32_logits_kernel<2, GRAD>), dim3((unsigned)round_up(wide, 8)),
-                       dim3(f32k::THREADS), 0, s, g);
-  else
-    hipLaunchKernelGGL((f32k::f32_logits_kernel<1, GRAD>),
-                       dim3((unsigned)round_up(cdiv<int64_t>(rows, 32) * tiles_m, 8)),
-                       dim3(f32k::THREADS), 0, s, g);
+  const bool is_wide = wide >= 2 * device_cu_count();
+  const int64_t blocks = round_up(is_wide ? wide : cdiv<int64_t>(rows, 32) * tiles_m, 8);
+  for (int64_t at = 0; at < blocks; at += kMost) {
+    const dim3 grid((unsigned)(blocks - at < kMost ? blocks - at : kMost));
+    g.block0 = (int32_t)at;
+    if (is_wide)
+      hipLaunchKernelGGL((f32k::f32_logits_kernel<2, GRAD>), grid, dim3(f32k::THREADS), 0, s, g);
+    else
+      hipLaunchKernelGGL((f32k::f32_logits_kernel<1, GRAD>), grid, dim3(f32k::THREADS), 0, s, g);
+  }
 }
 
 // Up to this many tokens the compaction is one launch.

@@ -141,3 +141,27 @@ def test_fp32_rows_beyond_32_bit_offsets():
     z = torch.stack([torch.dot(H[1].double(), w.double()) for w in W])
     assert abs(lse[1].item() - z.logsumexp(0).item()) < 1e-3
     assert abs(logp[1].item() - torch.log_softmax(z, 0)[V - 1].item()) < 1e-3
+
+
+# fp32 with more than 2^24 logit tiles of 64 tokens, 2^32 threads at 256 each: more than one
+# launch holds.  Tokens spread over all tiles, the first and the last, against fp64.
+def test_fp32_more_tiles_than_a_launch():
+    import paper_2510_04206_amd as P
+    T, V, d = 1 << 20, (1 << 18) + 5, 64
+    log(f"fp32 logit tiles T={T} V={V} d={d}")
+    g = torch.Generator(device="cuda").manual_seed(4)
+    H = torch.randn((T, d), generator=g, device="cuda")
+    W = torch.randn((V, d), generator=g, device="cuda").mul_(0.1)
+    y = torch.randint(0, V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    y[-1] = V - 1
+    mask = torch.ones(T, dtype=torch.uint8, device="cuda")
+    lp = P.TokenLogprob(T, d, V, H.dtype)
+    logp, lse = lp(H, W, y, mask)
+    assert P.agrl_get_device_error() == 0
+    at = torch.cat([torch.arange(0, T, 4099, device="cuda"), torch.tensor([T - 64, T - 1], device="cuda")])
+    for part in at.split(64):
+        z = H[part].double() @ W.double().t()
+        want_lse = z.logsumexp(1)
+        want = z.gather(1, y[part].long()[:, None])[:, 0] - want_lse
+        assert (lse[part].double() - want_lse).abs().max() < 2e-5
+        assert (logp[part].double() - want).abs().max() < 5e-5
