@@ -165,7 +165,7 @@ __device__ __forceinline__ int nonzero_bytes(uint32_t x) {
 // masked tokens get (logp = lse = 0; dH row +0).  Block (b, r) covers the tokens
 // [256 b, 256 b + 256); the blocks of one b share its rows out, the first writes the
 // scalars.  Every block counts the action tokens before its own, and all of them, from
-// the mask itself: for a mask of up to 256 KiB (kOneLaunchTokens) that is a few loads of
+// the mask itself: for a mask of up to 64 KiB (kOneLaunchTokens) that is a few loads of
 // 16 bytes in flight per thread, cheaper than the two launches (5 us each) that it
 // replaces; beyond, scan_count / scan_offsets come first and blk_off is given.  Against
 // the scan, scatter, gather and zero kernels it replaces (forward + backward): 79 and 22 us
@@ -791,8 +791,12 @@ void launch_logits_f32(f32k::LogitsArgs g, int64_t rows, hipStream_t s) {
   }
 }
 
-// Up to this many tokens the compaction is one launch.
-constexpr int64_t kOneLaunchTokens = (int64_t)1 << 18;
+// Up to this many tokens the compaction is one launch, whose blocks each count the mask:
+// T^2 / 256 bytes read, against two short launches.  Log-prob pass, V = 300, one launch
+// against three: 24.2 and 29.3 us at T = 1024, 28.6 and 31.5 at 32768, 30.7 and 31.4 at
+// 65536, 34.3 and 32.1 at 98304, 51.1 and 32.5 at 262144 (d = 64, 64 action tokens); 180.4
+// and 183.6 at 65536, 326.6 and 325.5 at 131072 (d = 4096, a third action tokens).
+constexpr int64_t kOneLaunchTokens = (int64_t)1 << 16;
 
 void compact(const Common& c, const Layout& L, uint8_t* ws, const uint8_t* mask,
              const int32_t* token_id, const float* adv, const float* old, const float* lse_in,

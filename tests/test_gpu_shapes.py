@@ -79,8 +79,9 @@ def test_bf16_few_tokens_chunks_accumulate_loose_bound():
 
 
 # compaction: tokens before, at and after a block of 256, a mask that starts off a 16-byte
-# boundary, more tokens than one launch handles (2^18)
+# boundary, as many tokens as one launch handles (2^16) and more
 @pytest.mark.parametrize("T,offset", [(1, 0), (255, 3), (256, 0), (257, 1), (4097, 16), (5000, 7),
+                                      (1 << 16, 0), (1 << 16, 9), ((1 << 16) + 1, 0),
                                       ((1 << 18) + 333, 0), ((1 << 18) + 77, 5)])
 def test_compaction(T, offset):
     import paper_2510_04206_amd as P
