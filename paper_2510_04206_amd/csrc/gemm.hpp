@@ -1122,32 +1122,41 @@ struct EpiStore {
   __device__ __forceinline__ void out16(const f32x4 (&acc)[8][8], int m0, int n0, int M, int N,
                                         float* st, const int* sr, int wm, int wn, int lane) const {
     const int wave = wm * 2 + wn;
-    const bool col_ok = n0 + 4 * lane < N;         // N is a multiple of 64
+    // (a column past the last is one of the row's padding: N is a multiple of 64, or a token
+    // count in rows of a multiple of 256, of which the reduce takes the first N columns)
+    const bool col_ok = n0 + 4 * lane < N;
     // Staged row pr of pass h is tile row 64 h + pr (pr < 64) or 64 h + pr + 64; wave w
-    // handles rows w, w + 4, ... in two batches of 16, the first below 64.  Lane k holds
+    // handles rows w, w + 4, ... in two batches of 16, the first below 64.  Lane k forms
     // output row k of a batch; a row's address is then a scalar, two multiplies and an add
     // (with a 64-bit address and an exec mask formed per row and lane, the 32 stores of a
     // pass took 7.7k cycles; dH + dW at V = 152064, d = 3584, 700 tokens 1.60 -> 1.47 ms).
+    // The scalars are read outside the branches on col_ok: inside, lanes 1..15 may be off
+    // (257 tokens leave one column of the last tile).
     const uint32_t ld_b = (uint32_t)(ldo * 4);
-    int rows = 0;
+    struct Rows {
+      uint32_t of[16];
+    };
     auto first = [&](int h, int b) { return 64 * h + 128 * b + wave; };     // tile row
     auto batch = [&](int h, int b) {
       const int tr = first(h, b) + 4 * (lane & 15);
-      rows = row_map ? sr[tr] : m0 + tr;
+      const int rows = row_map ? sr[tr] : m0 + tr;
+      Rows r;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) r.of[k] = __builtin_amdgcn_readlane(rows, k);
+      return r;
     };
-    auto at = [&](int k) {
-      const uint32_t row = __builtin_amdgcn_readlane(rows, k);
+    auto at = [&](uint32_t row) {
       return (f32x4*)((char*)(out + n0) + (uint64_t)row * ld_b + (uint32_t)(16 * lane));
     };
     f32x4 old[16];
     // (vmcnt counts stores too and in order: the next rows are read before a batch is
     // stored, also across the passes, so that no read waits for a store)
     auto read = [&](int h, int b) {
-      batch(h, b);
+      const Rows r = batch(h, b);
       if (col_ok) {
 #pragma unroll
         for (int k = 0; k < 16; ++k)
-          if (m0 + first(h, b) + 4 * k < M) old[k] = *at(k);
+          if (m0 + first(h, b) + 4 * k < M) old[k] = *at(r.of[k]);
       }
     };
     if constexpr (ACC) read(0, 0);
@@ -1172,11 +1181,11 @@ struct EpiStore {
         if constexpr (ACC) {
           if (h == 0 || b == 0) read(h + b, 1 - b);
         }
-        batch(h, b);
+        const Rows r = batch(h, b);
         if (col_ok) {
 #pragma unroll
           for (int k = 0; k < 16; ++k)
-            if (m0 + first(h, b) + 4 * k < M) *at(k) = v[k];
+            if (m0 + first(h, b) + 4 * k < M) *at(r.of[k]) = v[k];
         }
       }
     }

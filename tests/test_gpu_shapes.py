@@ -66,7 +66,7 @@ def test_fp32_chunks_accumulate_loose_bound():
 # dH's K; W's last rows a whole stage pair or a remainder of 1, 63, 64, 127; a hidden
 # size that leaves a partial 256-tile; one row of tokens more and less than a tile
 @pytest.mark.parametrize("V,d,n_act", [
-    (1, 64, 1), (127, 64, 255), (129, 128, 256), (2048, 192, 257), (8191, 320, 100),
+    (1, 64, 1), (127, 64, 255), (129, 128, 256), (2048, 192, 257), (4100, 192, 261), (8191, 320, 100),
     (20031, 128, 300), (50240, 256, 70), (33, 512, 2000)])
 def test_bf16_few_tokens(V, d, n_act):
     _case(torch.bfloat16, V, d, n_act)
