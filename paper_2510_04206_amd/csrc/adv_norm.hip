@@ -39,19 +39,31 @@ struct Run {
   }
 };
 
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+// Four values in one 16-byte access at any element's address (global memory takes one that
+// is only 4-byte aligned)
+typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
-// The ids and mask bytes of a lane's tokens [t0, t0 + 16): VEC (both arrays 16-byte
-// aligned) with four 16-byte id loads and one 16-byte mask load.  Tokens past T_g are
+// Tokens are taken in runs of N whose mask bytes start at a multiple of N in memory: a
+// micro-batch's arrays may start anywhere in the batch's.  The first run then begins up to
+// N - 1 tokens before the arrays.  Read element by element where the arrays are not aligned,
+// sequence weights of 65536 tokens took 46.6 us a call and an advantage call of 512
+// trajectories and 32000 tokens 56.2, now 11.6 and 27.6 (aligned 8.4 and 26.2).
+template <int N>
+__host__ __device__ __forceinline__ int run_shift(const uint8_t* mask) {
+  return (int)((uintptr_t)mask & (N - 1));
+}
+
+// The ids and mask bytes of a lane's tokens [t0, t0 + 16), with four 16-byte id loads and one
+// 16-byte mask load; the tokens of the first and the last run that lie outside the arrays are
 // padding.
-template <bool VEC>
 struct Tokens {
   i32x4 ids[4];
   u32x4 m;
   __device__ __forceinline__ void load(int64_t t0, int64_t T_g, const int32_t* __restrict__ traj_id,
                                        const uint8_t* __restrict__ mask) {
     static_assert(kCountPerLane == 16, "one 16-byte mask load per lane");
-    if (VEC && t0 + kCountPerLane <= T_g) {
+    if (t0 >= 0 && t0 + kCountPerLane <= T_g) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) ids[k] = *(const i32x4*)(traj_id + t0 + 4 * k);
       m = *(const u32x4*)(mask + t0);
@@ -60,7 +72,7 @@ struct Tokens {
     m = u32x4{0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < kCountPerLane; ++i) {
-      const bool in = t0 + i < T_g;
+      const bool in = t0 + i >= 0 && t0 + i < T_g;
       ids[i >> 2][i & 3] = in ? traj_id[t0 + i] : -1;
       m[i >> 2] |= (in && mask[t0 + i] ? 1u : 0u) << (8 * (i & 3));
     }
@@ -104,11 +116,10 @@ struct Tokens {
 
 // A wave's tokens from t0 (each lane's first) into counters in memory: lanes that end on
 // the same trajectory are merged into one atomic.
-template <bool VEC>
 __device__ __forceinline__ void count_tokens(int64_t t0, int64_t T_g, int32_t n_traj,
                                              const int32_t* traj_id, const uint8_t* mask,
                                              int32_t* count, int* err) {
-  Tokens<VEC> tok;
+  Tokens tok;
   tok.load(t0, T_g, traj_id, mask);
   Run r = tok.count(n_traj, count, err);
   const int lane = threadIdx.x & 63;
@@ -126,13 +137,13 @@ __device__ __forceinline__ void count_tokens(int64_t t0, int64_t T_g, int32_t n_
 
 // All T_g tokens by one workgroup of 1024 threads into counters in LDS, two batches of
 // loads in flight.
-template <bool VEC>
 __device__ __forceinline__ void count_in_lds(int64_t T_g, int32_t n_traj, const int32_t* traj_id,
                                              const uint8_t* mask, int32_t* count, int* err) {
   constexpr int B = 2;
   constexpr int64_t step = 1024 * kCountPerLane;
-  for (int64_t t0 = (int64_t)threadIdx.x * kCountPerLane; t0 < T_g; t0 += B * step) {
-    Tokens<VEC> tok[B];
+  const int shift = run_shift<kCountPerLane>(mask);
+  for (int64_t t0 = (int64_t)threadIdx.x * kCountPerLane - shift; t0 < T_g; t0 += B * step) {
+    Tokens tok[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) tok[b].load(t0 + b * step, T_g, traj_id, mask);
 #pragma unroll
@@ -193,7 +204,6 @@ __device__ __forceinline__ void check_ids(const IdArgs& a, int j, int32_t n_traj
 // id_blocks blocks take 256 trajectories each, the others 256 * kCountPerLane tokens.
 // One launch less at 2560 trajectories and 9M tokens: 38.6 -> 33.6 us a call (31.7 since).  (Ranges
 // preset and recorded by one block: 16.3 us for that launch alone.)
-template <bool VEC>
 __global__ __launch_bounds__(256) void count_kernel(int64_t T_g, int32_t n_traj,
                                                     const int32_t* __restrict__ traj_id,
                                                     const uint8_t* __restrict__ mask,
@@ -203,21 +213,19 @@ __global__ __launch_bounds__(256) void count_kernel(int64_t T_g, int32_t n_traj,
     check_ids(ids, blockIdx.x * 256 + threadIdx.x, n_traj, err);
     return;
   }
-  count_tokens<VEC>(((int64_t)(blockIdx.x - id_blocks) * 256 + threadIdx.x) * kCountPerLane, T_g,
-                    n_traj, traj_id, mask, act_count, err);
+  count_tokens(((int64_t)(blockIdx.x - id_blocks) * 256 + threadIdx.x) * kCountPerLane -
+                   run_shift<kCountPerLane>(mask),
+               T_g, n_traj, traj_id, mask, act_count, err);
 }
 
 void launch_count(int64_t T_g, int32_t n_traj, const int32_t* traj_id, const uint8_t* mask,
                   int32_t* act_count, int32_t id_blocks, const IdArgs& ids, int* err,
                   hipStream_t s) {
-  const int64_t blocks = id_blocks + cdiv<int64_t>(cdiv<int64_t>(T_g, kCountPerLane), 256);
+  const int64_t tokens = T_g > 0 ? T_g + run_shift<kCountPerLane>(mask) : 0;
+  const int64_t blocks = id_blocks + cdiv<int64_t>(tokens, 256 * kCountPerLane);
   if (blocks == 0) return;
-  if ((((uintptr_t)traj_id | (uintptr_t)mask) & 15) == 0)
-    hipLaunchKernelGGL(count_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, T_g, n_traj,
-                       traj_id, mask, act_count, id_blocks, ids, err);
-  else
-    hipLaunchKernelGGL(count_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, T_g, n_traj,
-                       traj_id, mask, act_count, id_blocks, ids, err);
+  hipLaunchKernelGGL(count_kernel, dim3((unsigned)blocks), dim3(256), 0, s, T_g, n_traj, traj_id,
+                     mask, act_count, id_blocks, ids, err);
 }
 
 // The trajectories a segment's wave visits: [first, last] of its members when
@@ -380,30 +388,33 @@ __global__ __launch_bounds__(256) void task_kernel(int32_t n_task, int32_t n_gro
               task_std, adv_traj);
 }
 
-// tok[t .. t + 3] = value[traj_id] on action tokens, 0 elsewhere.  VEC: traj_id, mask and
-// tok are 16-byte aligned: one 16-byte id load, one 4-byte mask load, one 16-byte store.
-template <bool VEC>
-__device__ __forceinline__ void spread_tokens(int64_t t, int64_t T, int32_t n_traj,
+// tok = value[traj_id] on action tokens, 0 elsewhere: run r of four tokens, with one 16-byte id
+// load, one 4-byte mask load and one 16-byte store.
+__device__ __forceinline__ void spread_tokens(int64_t r, int64_t T, int32_t n_traj,
                                               const int32_t* __restrict__ traj_id,
                                               const uint8_t* __restrict__ mask,
                                               const float* value, float* tok) {
   auto one = [&](int id, bool m) { return (m && id >= 0 && id < n_traj) ? value[id] : 0.0f; };
-  if (VEC && t + 4 <= T) {
+  const int64_t t = 4 * r - run_shift<4>(mask);
+  if (t >= 0 && t + 4 <= T) {
     const i32x4 id = *(const i32x4*)(traj_id + t);
     const uint32_t m = *(const uint32_t*)(mask + t);
-    *(f32x4*)(tok + t) = f32x4{one(id[0], m & 0xFFu), one(id[1], (m >> 8) & 0xFFu),
-                               one(id[2], (m >> 16) & 0xFFu), one(id[3], m >> 24)};
+    *(f32x4_any*)(tok + t) = f32x4_any{one(id[0], m & 0xFFu), one(id[1], (m >> 8) & 0xFFu),
+                                       one(id[2], (m >> 16) & 0xFFu), one(id[3], m >> 24)};
     return;
   }
-  for (int64_t u = t; u < T && u < t + 4; ++u) tok[u] = one(traj_id[u], mask[u] != 0);
+  for (int64_t u = t < 0 ? 0 : t; u < T && u < t + 4; ++u) tok[u] = one(traj_id[u], mask[u] != 0);
+}
+// runs that cover T tokens
+__host__ __device__ __forceinline__ int64_t spread_runs(int64_t T, const uint8_t* mask) {
+  return cdiv<int64_t>(T + run_shift<4>(mask), 4);
 }
 
-template <bool VEC>
 __global__ void broadcast_kernel(int64_t T_g, int32_t n_traj, const int32_t* __restrict__ traj_id,
                                  const uint8_t* __restrict__ mask,
                                  const float* __restrict__ adv_traj, float* adv_tok) {
-  spread_tokens<VEC>(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4, T_g, n_traj, traj_id,
-                     mask, adv_traj, adv_tok);
+  spread_tokens((int64_t)blockIdx.x * blockDim.x + threadIdx.x, T_g, n_traj, traj_id, mask,
+                adv_traj, adv_tok);
 }
 
 // A whole call in one workgroup, for batches small enough that launches are what they
@@ -433,7 +444,6 @@ struct SmallArgs {
   float* adv_tok;
   int* err;
 };
-template <bool VEC>
 __global__ __launch_bounds__(1024) void adv_small_kernel(SmallArgs a) {
   __shared__ int32_t s_count[kSmallTraj], s_task[kSmallTraj], s_group[kSmallTraj];
   __shared__ float s_reward[kSmallTraj], s_adv[kSmallTraj];
@@ -450,7 +460,7 @@ __global__ __launch_bounds__(1024) void adv_small_kernel(SmallArgs a) {
     if (a.traj_group && (g < 0 || g >= a.n_group)) set_error(a.err, ERR_GROUP_ID);
   }
   __syncthreads();
-  count_in_lds<VEC>(a.T_g, a.n_traj, a.traj_id, a.mask, s_count, a.err);
+  count_in_lds(a.T_g, a.n_traj, a.traj_id, a.mask, s_count, a.err);
   const Span all{0, a.n_traj - 1};
   if (a.traj_group)
     for (int g = wave; g < a.n_group; g += 16)
@@ -464,8 +474,8 @@ __global__ __launch_bounds__(1024) void adv_small_kernel(SmallArgs a) {
   if (tid < a.n_traj) a.adv_traj[tid] = s_adv[tid];
   if (a.adv_tok) {
 #pragma unroll 4
-    for (int64_t t = (int64_t)tid * 4; t < a.T_g; t += 1024 * 4)
-      spread_tokens<VEC>(t, a.T_g, a.n_traj, a.traj_id, a.mask, s_adv, a.adv_tok);
+    for (int64_t r = tid; r < spread_runs(a.T_g, a.mask); r += 1024)
+      spread_tokens(r, a.T_g, a.n_traj, a.traj_id, a.mask, s_adv, a.adv_tok);
   }
 }
 
@@ -504,7 +514,6 @@ __global__ __launch_bounds__(256) void seq_weight_kernel(int64_t T, int32_t n_tr
 constexpr int kSeqTraj = 4096;
 constexpr int64_t kSeqTokens = 65536;
 constexpr int kSeqShare = 4096;          // tokens a workgroup weighs
-template <bool VEC>
 __global__ __launch_bounds__(1024) void seq_small_kernel(int64_t T, int32_t n_traj,
                                                          const int32_t* __restrict__ traj_id,
                                                          const uint8_t* __restrict__ mask,
@@ -515,7 +524,7 @@ __global__ __launch_bounds__(1024) void seq_small_kernel(int64_t T, int32_t n_tr
   const int tid = threadIdx.x, lane = tid & 63;
   for (int j = tid; j < n_traj; j += 1024) count[j] = 0;
   __syncthreads();
-  count_in_lds<VEC>(T, n_traj, traj_id, mask, count, err);
+  count_in_lds(T, n_traj, traj_id, mask, count, err);
   __syncthreads();
   int n = 0;
   for (int j = tid; j < n_traj; j += 1024) {
@@ -533,8 +542,8 @@ __global__ __launch_bounds__(1024) void seq_small_kernel(int64_t T, int32_t n_tr
       count[j] = __float_as_int((float)(1.0 / ((double)n_seq * (double)count[j])));
   __syncthreads();
   static_assert(kSeqShare == 4 * 1024, "four tokens a thread");
-  spread_tokens<VEC>((int64_t)blockIdx.x * kSeqShare + tid * 4, T, n_traj, traj_id, mask,
-                     (const float*)count, w);
+  spread_tokens((int64_t)blockIdx.x * (kSeqShare / 4) + tid, T, n_traj, traj_id, mask,
+                (const float*)count, w);
 }
 
 }  // namespace
@@ -578,16 +587,12 @@ extern "C" int agrl_task_adv_norm(int64_t T_g, int32_t n_traj, int32_t n_task, i
   const int32_t n_group_used = traj_group ? n_group : 0;
   const int32_t ddof = (int32_t)o.std_ddof;
   const int32_t drop = traj_group ? o.drop_uniform_groups : 0;
-  const bool vec_in = (((uintptr_t)traj_id | (uintptr_t)action_mask) & 15) == 0;
   if (T_g <= kSmallTokens && n_traj <= kSmallTraj &&
       ((int64_t)n_group_used + n_task) * n_traj <= kSmallScan) {
     const SmallArgs a = {T_g, n_traj, n_task, n_group_used, traj_id, action_mask, traj_task,
                          traj_group, reward, ddof, eps, drop, act_count, task_count, task_mean,
                          task_std, adv_traj, adv_tok, err};
-    if (vec_in && ((uintptr_t)adv_tok & 15) == 0)
-      hipLaunchKernelGGL(adv_small_kernel<true>, dim3(1), dim3(1024), 0, s, a);
-    else
-      hipLaunchKernelGGL(adv_small_kernel<false>, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL(adv_small_kernel, dim3(1), dim3(1024), 0, s, a);
     return hip_status(hipGetLastError());
   }
 
@@ -609,13 +614,9 @@ extern "C" int agrl_task_adv_norm(int64_t T_g, int32_t n_traj, int32_t n_task, i
                        traj_group ? (const float*)adv_traj : reward, (const int32_t*)range, ddof,
                        eps, drop, task_count, task_mean, task_std, adv_traj);
   if (adv_tok && T_g > 0) {
-    const dim3 grid((unsigned)cdiv<int64_t>(cdiv<int64_t>(T_g, 4), 256));
-    if (vec_in && ((uintptr_t)adv_tok & 15) == 0)
-      hipLaunchKernelGGL(broadcast_kernel<true>, grid, dim3(256), 0, s, T_g, n_traj, traj_id,
-                         action_mask, (const float*)adv_traj, adv_tok);
-    else
-      hipLaunchKernelGGL(broadcast_kernel<false>, grid, dim3(256), 0, s, T_g, n_traj, traj_id,
-                         action_mask, (const float*)adv_traj, adv_tok);
+    const dim3 grid((unsigned)cdiv<int64_t>(spread_runs(T_g, action_mask), 256));
+    hipLaunchKernelGGL(broadcast_kernel, grid, dim3(256), 0, s, T_g, n_traj, traj_id, action_mask,
+                       (const float*)adv_traj, adv_tok);
   }
   return hip_status(hipGetLastError());
 }
@@ -635,13 +636,9 @@ extern "C" int agrl_sequence_mean_weights(int64_t T, int32_t n_traj, const int32
   int* err = device_error_ptr();
   if (!err) return hip_status(hipErrorInvalidSymbol);
   if (T <= kSeqTokens && n_traj <= kSeqTraj) {
-    const dim3 grid((unsigned)(T > 0 ? cdiv<int64_t>(T, kSeqShare) : 1));
-    if ((((uintptr_t)traj_id | (uintptr_t)action_mask | (uintptr_t)token_weight) & 15) == 0)
-      hipLaunchKernelGGL(seq_small_kernel<true>, grid, dim3(1024), 0, s, T, n_traj, traj_id,
-                         action_mask, seq_count, token_weight, err);
-    else
-      hipLaunchKernelGGL(seq_small_kernel<false>, grid, dim3(1024), 0, s, T, n_traj, traj_id,
-                         action_mask, seq_count, token_weight, err);
+    const dim3 grid((unsigned)(T > 0 ? cdiv<int64_t>(spread_runs(T, action_mask), kSeqShare / 4) : 1));
+    hipLaunchKernelGGL(seq_small_kernel, grid, dim3(1024), 0, s, T, n_traj, traj_id, action_mask,
+                       seq_count, token_weight, err);
     return hip_status(hipGetLastError());
   }
   if (n_traj > 0)

@@ -83,3 +83,41 @@ def test_count_trajectory_changes(T, n_traj):
     assert P.agrl_get_device_error() == 0
     want = np.bincount(ids[(mask != 0) & (ids >= 0)], minlength=n_traj)
     np.testing.assert_array_equal(count.cpu().numpy(), want)
+
+
+# ids, mask and token outputs that start anywhere in their arrays, each by itself: runs of 16
+# and of 4 tokens cut at both ends, one workgroup (1023 trajectories) and several launches
+@pytest.mark.parametrize("n_traj", [1023, 5000])
+@pytest.mark.parametrize("T", [1, 3, 15, 16, 17, 33, 4099, 66001])
+@pytest.mark.parametrize("o_id,o_mask,o_out", [(0, 1, 0), (1, 0, 2), (1, 1, 1), (3, 15, 3), (0, 4, 1), (2, 17, 0)])
+def test_arrays_that_start_anywhere(n_traj, T, o_id, o_mask, o_out):
+    import paper_2510_04206_amd as P
+    task, group, reward, ids, mask = _batch(n_traj, 40, 3, T, 7)
+    mask = mask * np.random.default_rng(T).integers(1, 256, T).astype(np.uint8)
+    log(f"arrays at {o_id}, {o_mask}, {o_out}: n_traj={n_traj} T={T}")
+
+    def at(a, k):        # `a` from element k on of a larger array whose other elements would count
+        t = torch.from_numpy(a).cuda()
+        pad = torch.full((k + 16,), 1, dtype=t.dtype, device="cuda")
+        return torch.cat([pad[:k], t, pad[k:]])[k:k + T]
+
+    t_ids, t_mask = at(ids, o_id), at(mask, o_mask)
+    dev = dict(device="cuda")
+    outs = (torch.empty(n_traj, dtype=torch.int32, **dev), torch.empty(3, dtype=torch.int64, **dev),
+            torch.empty(3, **dev), torch.empty(3, **dev), torch.empty(n_traj, **dev))
+    whole = torch.full((2, T + o_out + 16), 7.0, **dev)
+    tok, w = whole[0, o_out:o_out + T], whole[1, o_out:o_out + T]
+    t = [torch.from_numpy(a).cuda() for a in (task, group, reward)]
+    P.agrl_task_adv_norm(T, n_traj, 3, 40, t_ids, t_mask, *t, None, *outs, tok)
+    count = torch.empty(n_traj, dtype=torch.int32, **dev)
+    P.agrl_sequence_mean_weights(T, n_traj, t_ids, t_mask, count, w)
+    assert P.agrl_get_device_error() == 0
+    want = oracle.task_adv_norm(ids, mask, task, group, reward, 3, 40)
+    want_count, want_w = oracle.sequence_mean_weights(ids, mask, n_traj)
+    np.testing.assert_array_equal(outs[0].cpu().numpy(), want["act_count"])
+    np.testing.assert_array_equal(outs[1].cpu().numpy(), want["task_count"])
+    np.testing.assert_array_equal(count.cpu().numpy(), want_count)
+    for a, b in ((outs[2], want["task_mean"]), (outs[3], want["task_std"]), (outs[4], want["adv_traj"]),
+                 (tok, want["adv_tok"]), (w, want_w)):
+        np.testing.assert_array_equal(a.cpu().numpy().view(np.uint32), b.view(np.uint32))
+    assert (whole[:, :o_out] == 7).all() and (whole[:, o_out + T:] == 7).all()   # nothing beside them
