@@ -419,12 +419,27 @@ __global__ void broadcast_kernel(int64_t T_g, int32_t n_traj, const int32_t* __r
 
 // A whole call in one workgroup, for batches small enough that launches are what they
 // cost: the same stages on arrays in LDS.  32 trajectories, 3.8k tokens, 8 groups, 2
-// tasks: 8.0 us, against 18.6 us of six kernels and as much between them.  The limits keep
-// it ahead: at 32768 tokens two lots of 16 a thread, and at most 64k ids scanned by 16
-// waves (about 64 steps each).
+// tasks: 8.0 us, against 18.6 us of six kernels and as much between them.
 constexpr int kSmallTraj = 1024;          // trajectories
+// Two lots of 16 tokens a thread.  One workgroup against several launches, 64 trajectories:
+// 10.7 and 19.7 us at 32768 tokens, 15.3 and 19.7 at 65536, 20.3 and 19.7 at 98304; 256
+// trajectories: 15.6 and 23.2, 21.4 and 23.1, 26.4 and 23.1.
 constexpr int64_t kSmallTokens = 32768;
-constexpr int64_t kSmallScan = 1 << 16;   // segments x trajectories: what the stages' waves scan
+// The stages: 16 waves take a segment each, in turn, and walk the trajectories in steps of
+// 64; a turn costs about 0.2 us and 0.32 us a step (5 and 8 units), an empty segment's too.
+// Several launches cost 6 us more than the rest of this kernel, more with many trajectories,
+// and merge a wave's 1024 tokens trajectory by trajectory.  One workgroup against several
+// launches, groups and tasks 7 : 1 (tokens 32768; 2000): 256 trajectories, 64 segments 17.7
+// and 24.6 us (15.7 and 37.0), 128 segments 25.0 and 26.5 (20.8 and 36.9), 256 segments
+// 38.2 and 30.9 (33.2 and 36.8); 1024 trajectories, 64 segments 38.3 and 46.6 (35.1 and
+// 57.6), 128 segments 55.5 and 46.6 (50.1 and 57.0); 64 trajectories, 128 segments 16.5 and
+// 21.6 (11.1 and 22.3), 512 segments 24.2 and 30.3 (19.1 and 30.6); one trajectory and
+// 65535 tasks 2441 against 25.
+__host__ inline bool stages_are_short(int64_t T, int32_t n_traj, int32_t n_group, int32_t n_task) {
+  const int64_t turns = (int64_t)cdiv(n_group, 16) + cdiv(n_task, 16);
+  const int64_t merged = T > 0 ? (int64_t)1024 * n_traj / T : 0;   // trajectories in a wave's tokens
+  return turns * (5 + 8 * cdiv(n_traj, 64)) <= 155 + n_traj / 2 + 5 * (merged < 64 ? merged : 64);
+}
 struct SmallArgs {
   int64_t T_g;
   int32_t n_traj, n_task, n_group;
@@ -509,8 +524,10 @@ __global__ __launch_bounds__(256) void seq_weight_kernel(int64_t T, int32_t n_tr
 }
 
 // The same in one launch, counters in LDS: every workgroup counts all the tokens itself
-// (kSeqTokens: 4 lots of 16 a thread, from L2) and weighs its share of them.  640
-// trajectories, 65536 tokens: 17.3 us a call in three launches (the host's), 8.4 in one.
+// (kSeqTokens: 4 lots of 16 a thread, from L2) and weighs its share of them.  One launch
+// against three, 640 trajectories: 8.5 and 11.7 us a call at 65536 tokens, 10.7 and 11.7 at
+// 98304, 12.4 and 11.6 at 131072; with arrays one element off alignment 11.6 and 12.7, 14.0
+// and 11.9, 16.0 and 11.7.
 constexpr int kSeqTraj = 4096;
 constexpr int64_t kSeqTokens = 65536;
 constexpr int kSeqShare = 4096;          // tokens a workgroup weighs
@@ -588,7 +605,7 @@ extern "C" int agrl_task_adv_norm(int64_t T_g, int32_t n_traj, int32_t n_task, i
   const int32_t ddof = (int32_t)o.std_ddof;
   const int32_t drop = traj_group ? o.drop_uniform_groups : 0;
   if (T_g <= kSmallTokens && n_traj <= kSmallTraj &&
-      ((int64_t)n_group_used + n_task) * n_traj <= kSmallScan) {
+      stages_are_short(T_g, n_traj, n_group_used, n_task)) {
     const SmallArgs a = {T_g, n_traj, n_task, n_group_used, traj_id, action_mask, traj_task,
                          traj_group, reward, ddof, eps, drop, act_count, task_count, task_mean,
                          task_std, adv_traj, adv_tok, err};

@@ -26,7 +26,10 @@ def _batch(n_traj, n_group, n_task, T, seed):
 @pytest.mark.parametrize("n_traj,n_group,n_task,T,offset", [
     (1, 1, 1, 1, 0), (64, 3, 2, 1000, 1), (1024, 62, 2, 32768, 0), (1024, 62, 2, 32769, 0),
     (1024, 63, 2, 5003, 0), (1025, 60, 2, 4000, 3), (4096, 4000, 96, 60001, 0),
-    (4097, 1000, 7, 60001, 0), (5000, 4500, 20, 9000, 5)])
+    (4097, 1000, 7, 60001, 0), (5000, 4500, 20, 9000, 5),
+    # the most segments that one workgroup takes, and one more
+    (256, 240, 16, 3000, 0), (256, 241, 16, 3000, 0), (1024, 80, 16, 32000, 1), (1024, 81, 16, 32000, 1),
+    (3, 112, 74, 2000, 0), (3, 113, 74, 2000, 0), (3, 4000, 3000, 200, 0)])
 @pytest.mark.parametrize("drop", [False, True])
 def test_adv_norm_sizes(n_traj, n_group, n_task, T, offset, drop):
     import paper_2510_04206_amd as P

@@ -1,6 +1,6 @@
 """A call is not much slower than its neighbour on the other side of a dispatch's line.  Each pair
-does the same work or the second a little more; the bounds lie between what was measured (1.0,
-sequence weights 1.35) and what they guard against (1.6 to 12)."""
+does the same work or the second a little more; the bounds lie between what was measured (up to 1.0,
+sequence weights 1.35) and what they guard against (1.6 to 200)."""
 import pytest
 import torch
 
@@ -92,3 +92,11 @@ def _adv_call(n_traj, n_group, n_task, T, offset=0):
 def test_advantages_of_a_small_batch_unaligned(offset):
     _not_slower(f"advantages at offset {offset}", _adv_call(512, 64, 8, 32000, offset), _adv_call(512, 64, 8, 32000),
                 bound=1.6)
+
+
+# many segments and few trajectories, which one workgroup once took, against more trajectories
+@pytest.mark.parametrize("n_traj,n_group,n_task", [(0, 0, 100000), (1, 0, 65535), (8, 8, 8000), (256, 250, 6)])
+def test_advantages_of_many_segments(n_traj, n_group, n_task):
+    T = 1000 if n_traj else 0
+    _not_slower(f"advantages of {n_traj} trajectories, {n_group} groups, {n_task} tasks",
+                _adv_call(n_traj, n_group, n_task, T), _adv_call(1025, n_group, n_task, 1000))
