@@ -124,3 +124,68 @@ def test_arrays_that_start_anywhere(n_traj, T, o_id, o_mask, o_out):
                  (tok, want["adv_tok"]), (w, want_w)):
         np.testing.assert_array_equal(a.cpu().numpy().view(np.uint32), b.view(np.uint32))
     assert (whole[:, :o_out] == 7).all() and (whole[:, o_out + T:] == 7).all()   # nothing beside them
+
+
+# ids outside their ranges, in one workgroup's batch and in the launches': the error bit, and
+# everything that the id does not touch as if its token were padding, or its trajectory apart
+SIZES = [(64, 16, 4, 4096), (2000, 300, 20, 70000)]
+
+
+def _call(ids, mask, task, group, reward, n_task, n_group, ranges=True):
+    import paper_2510_04206_amd as P
+    t = lambda a: torch.from_numpy(a).cuda()                         # noqa: E731
+    out = P.task_adv_norm(t(ids), t(mask), t(task), t(group), t(reward), n_task, n_group, member_ranges=ranges)
+    return {k: v.cpu().numpy() for k, v in out.items() if k != "member_ranges"}, P.agrl_get_device_error()
+
+
+@pytest.mark.parametrize("n_traj,n_group,n_task,T", SIZES)
+@pytest.mark.parametrize("run,place", [("first", 3), ("second", 9), ("whole", 0), ("third", 5)])
+@pytest.mark.parametrize("action", [False, True])
+def test_bad_trajectory_ids(n_traj, n_group, n_task, T, run, place, action):
+    import paper_2510_04206_amd as P
+    task, group, reward, ids, mask = _batch(n_traj, n_group, n_task, T, 11)
+    ids = np.repeat(ids[::16], 16)[:T].copy()            # whole runs of 16 tokens
+    at = 16 * (T // 40)
+    bad = {"first": slice(at, at + place), "second": slice(at + place, at + 16), "whole": slice(at, at + 16),
+           "third": slice(at + place, at + place + 4)}[run]
+    ids[at:at + 16] = n_traj // 2
+    if run == "third":
+        ids[at + 12:at + 16] = 1
+    ids[bad] = n_traj + (1 << 20)
+    mask[bad] = action
+    log(f"bad trajectory ids n_traj={n_traj} {run} action={action}")
+    clean = np.where(ids >= n_traj, -1, ids).astype(np.int32)
+    want = oracle.task_adv_norm(clean, mask, task, group, reward, n_task, n_group)
+    got, err = _call(ids, mask, task, group, reward, n_task, n_group)
+    assert err == 2
+    for k in want:
+        np.testing.assert_array_equal(np.asarray(got[k]).view(np.uint8), np.asarray(want[k]).view(np.uint8), err_msg=k)
+    count, w = P.sequence_mean_weights(torch.from_numpy(ids).cuda(), torch.from_numpy(mask).cuda(), n_traj)
+    assert P.agrl_get_device_error() == 2
+    want_count, want_w = oracle.sequence_mean_weights(clean, mask, n_traj)
+    np.testing.assert_array_equal(count.cpu().numpy(), want_count)
+    np.testing.assert_array_equal(w.cpu().numpy().view(np.uint32), want_w.view(np.uint32))
+
+
+@pytest.mark.parametrize("n_traj,n_group,n_task,T", SIZES)
+@pytest.mark.parametrize("ranges", [True, False])
+@pytest.mark.parametrize("what,value,bit", [("task", -1, 4), ("task", 1 << 20, 4), ("group", -5, 8), ("group", 1 << 20, 8)])
+def test_bad_task_and_group_ids(n_traj, n_group, n_task, T, ranges, what, value, bit):
+    task, group, reward, ids, mask = _batch(n_traj, n_group, n_task, T, 13)
+    j = n_traj // 3
+    good = (task.copy(), group.copy())
+    good[what == "group"][j] = (n_task, n_group)[what == "group"]     # a task or group of its own
+    touched = {"task": np.arange(n_traj) == j, "group": task == task[j]}[what]
+    log(f"bad {what} id {value} n_traj={n_traj} ranges={ranges}")
+    want = oracle.task_adv_norm(ids, mask, *good, reward, n_task + 1, n_group + 1)
+    (task, group)[what == "group"][j] = value
+    got, err = _call(ids, mask, task, group, reward, n_task, n_group, ranges)
+    assert err == bit
+    np.testing.assert_array_equal(got["act_count"], want["act_count"])
+    np.testing.assert_array_equal(got["task_count"], want["task_count"][:n_task])
+    np.testing.assert_array_equal(got["adv_traj"][~touched].view(np.uint32), want["adv_traj"][~touched].view(np.uint32))
+    keep = np.ones(n_task, bool)
+    if what == "group":
+        keep[task[j]] = False
+    for k in ("task_mean", "task_std"):
+        np.testing.assert_array_equal(got[k][keep].view(np.uint32), want[k][:n_task][keep].view(np.uint32))

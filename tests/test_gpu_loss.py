@@ -96,7 +96,8 @@ def test_vocabulary_chunks_short_last_chunk():
 
 def _launch_tiles(n_act, V, d, vc):
     """Tiles of each matrix-core launch: forward (vocabulary x tokens), recompute
-    per chunk (tokens x chunk columns), dH + dW per chunk (tokens x d, chunk x d)."""
+    per chunk (tokens x chunk columns), dH + dW per chunk (tokens x d, chunk x d; with few
+    action tokens each of dH's tiles is several items more, parts of its K)."""
     t = lambda x: -(-x // 256)
     chunks = [min(vc, V - v0) for v0 in range(0, V, vc)]
     return (t(V) * t(n_act), [t(n_act) * t(c) for c in chunks],
@@ -109,7 +110,8 @@ def test_whole_batch_multi_round_three_chunks():
     rounds of 256 tiles per launch (every workgroup takes several tiles, the
     queues' full-round and final partial-round branches both run), with three
     vocabulary chunks, the last one ragged: every output element against the
-    oracle's whole batch."""
+    oracle's whole batch.  (Few enough action tokens that dH reads W as it lies;
+    test_gpu_shapes.py has such a batch for the backward that builds W^T.)"""
     import paper_2510_04206_amd as P
     w = gen.make(gen.small_spec(V=131000, d=384, dtype="bf16", n_tasks=3, n_groups=2,
                                 group_size=7, name="whole batch V131000 d384"),

@@ -28,7 +28,10 @@ def _case(dtype, V, d, n_act, *, T=None, seed=1, opt=None, max_act=None, dW0=Non
     W = torch.randn((V, d), generator=g).mul_(0.1).to(dtype)
     y = rng.integers(0, V, T).astype(np.int32)
     y[:: 7] = V - 1                                  # the last vocabulary row's tile
-    logp = torch.log_softmax(H.float() @ W.float().t(), 1)[torch.arange(T), torch.from_numpy(y).long()]
+    act = torch.from_numpy(np.nonzero(mask)[0])
+    logp = torch.zeros(T)
+    logp[act] = torch.log_softmax(H[act].float() @ W.float().t(), 1).gather(
+        1, torch.from_numpy(y).long()[act][:, None])[:, 0]
     old = (logp.numpy() + 0.2 * rng.standard_normal(T)).astype(np.float32)
     adv = rng.standard_normal(T).astype(np.float32)
     log(f"shape {dtype} V={V} d={d} n_act={n_act} T={T} max_act={max_act} {opt}")
@@ -62,14 +65,88 @@ def test_fp32_chunks_accumulate_loose_bound():
           max_act=0, dW0=0.25)
 
 
+def _pad(n):
+    return -(-n // 256) * 256
+
+
+def _reads_w(T, max_act, V, d):
+    """Whether a bf16 backward reads W as it lies for dH (EpiGrad) or builds W^T (EpiStore): the
+    bound on the action tokens is at most 8192, and W^T's place holds one part of dH beside
+    W's padded tail."""
+    A = _pad(max_act or T)
+    return A <= 8192 and (_pad(d) * _pad(V) * 2 - _pad(128 * d * 2)) // (A * d * 4) > 0
+
+
 # bf16 with few action tokens (dH reads W as it lies): one, several and many parts of
 # dH's K; W's last rows a whole stage pair or a remainder of 1, 63, 64, 127; a hidden
 # size that leaves a partial 256-tile; one row of tokens more and less than a tile
 @pytest.mark.parametrize("V,d,n_act", [
-    (1, 64, 1), (127, 64, 255), (129, 128, 256), (2048, 192, 257), (4100, 192, 261), (8191, 320, 100),
-    (20031, 128, 300), (50240, 256, 70), (33, 512, 2000)])
+    (1, 64, 1), (127, 64, 255), (1025, 128, 256), (2048, 192, 257), (4100, 192, 261), (8191, 320, 100),
+    (20031, 128, 300), (50240, 256, 70), (6079, 512, 2000)])
 def test_bf16_few_tokens(V, d, n_act):
+    assert _reads_w(0, n_act, V, d)
     _case(torch.bfloat16, V, d, n_act)
+
+
+# bf16 with W^T: a vocabulary too small for a part of dH; more than 8192 action tokens; and a
+# bound above that with few tokens.  The last: two chunks whose dW tiles fill two rounds of
+# the queues, the last chunk ragged, d partial, dH added to over the chunks and dW added to.
+@pytest.mark.parametrize("V,d,n_act,T,opt", [
+    (129, 128, 256, None, {}), (33, 512, 2000, None, {}), (700, 192, 8300, None, {}), (1, 64, 1, 8200, {}),
+    (257, 1088, 257, 8300, {}), (1027, 320, 600, 9000, dict(dw_accumulate=1)),
+    (1665, 192, 300, 9000, dict(g_chunk_bytes=9216 * 2 * 512, dw_accumulate=1)),
+    (131001, 320, 600, 9000, dict(g_chunk_bytes=9216 * 2 * 65536, dw_accumulate=1))])
+def test_bf16_with_transposed_w(V, d, n_act, T, opt):
+    import paper_2510_04206_amd as P
+    max_act = 0 if T else n_act
+    assert not _reads_w(T, max_act, V, d)
+    if V > 100000:
+        vc = P.PolicyLoss(T, d, V, torch.bfloat16, opt=opt).vocab_chunk
+        tiles = [-(-c // 256) * -(-d // 256) for c in (vc, V - vc)]      # of dW, in each launch
+        assert vc < V < 2 * vc and min(tiles) >= 2 * 256 and (V - vc) % 256 and d % 256
+    _case(torch.bfloat16, V, d, n_act, T=T, opt=opt, max_act=max_act, dW0=0.25 if opt else None)
+
+
+# the same launch without action tokens (dW written as zeros, or left as it is), with an id
+# outside the vocabulary, and with more action tokens than the bound
+def test_bf16_with_transposed_w_faults():
+    import paper_2510_04206_amd as P
+    T, V, d, n_act = 8300, 400, 192, 300
+    log("W^T backward: no action tokens, bad id, over the bound")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    H = torch.randn((T, d), generator=g, device="cuda").bfloat16()
+    W = torch.randn((V, d), generator=g, device="cuda").mul_(0.1).bfloat16()
+    y = torch.randint(0, V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    adv, old = torch.randn(T, generator=g, device="cuda"), torch.full((T,), -6.0, device="cuda")
+    mask = torch.zeros(T, dtype=torch.uint8, device="cuda")
+    for acc in (0, 1):
+        pl = P.PolicyLoss(T, d, V, H.dtype, opt=dict(dw_accumulate=acc))
+        pl.dW.fill_(2.0)
+        pl.dH.fill_(float("nan"))
+        loss, *_ = pl.forward(H, W, y, mask, adv, old)
+        dH, dW = pl.backward(H, W, y, mask, adv, old)
+        assert loss.item() == 0 and (dH == 0).all() and not torch.signbit(dH).any()
+        assert (dW == 2.0 * acc).all()
+    mask[torch.randperm(T, generator=g, device="cuda")[:n_act]] = 1
+    act = torch.nonzero(mask)[:, 0]
+    bad = int(act[n_act // 2])
+    y[bad] = V
+    pl = P.PolicyLoss(T, d, V, H.dtype)
+    loss, logp, lse, _ = pl.forward(H, W, y, mask, adv, old)
+    dH, dW = pl.backward(H, W, y, mask, adv, old)
+    assert P.agrl_get_device_error() == 1
+    others = act[act != bad]
+    assert loss.isnan().item() and logp[bad].isnan() and lse[bad].isnan()
+    assert logp[others].isfinite().all() and dH[others].isfinite().all()
+    assert dH[bad].isnan().all() and dW.isnan().all() and (dH[mask == 0] == 0).all()
+    # over the bound, at the sizes of the one-launch and of the three-launch compaction
+    for T2 in (T, 70000):
+        H2, m2 = torch.zeros((T2, d), dtype=H.dtype, device="cuda"), torch.ones(T2, dtype=torch.uint8, device="cuda")
+        z = torch.zeros(T2, device="cuda")
+        pl = P.PolicyLoss(T2, d, V, H.dtype, max_act=T2 - 1)
+        loss, *_ = pl.forward(H2, W, torch.zeros(T2, dtype=torch.int32, device="cuda"), m2, z, z)
+        assert loss.isnan().item() and P.agrl_get_device_error() == 16
+    assert P.agrl_get_device_error() == 0
 
 
 def test_bf16_few_tokens_chunks_accumulate_loose_bound():
