@@ -281,8 +281,7 @@ struct GemmBatch {
 };
 
 // Copy schedule of the 16 x 16 loop, per epilogue (measured on the 32B-shaped
-// workload): MFMA slots between two stage copies, whether A's copies go before
-// B's, and whether odd rounds of tiles sweep K backwards (a round then starts
+// workload): MFMA slots between two stage copies, and whether odd rounds of tiles sweep K backwards (a round then starts
 // on the operand chunks the previous round of its XCD read last: 2% faster for
 // the long-K dH + dW tiles, while the forward and recompute gained nothing and
 // their L2 hit rate dropped).
@@ -292,21 +291,18 @@ struct EpiGrad;
 template <class Epi>
 struct CopySched {
   static constexpr int spacing = 6;
-  static constexpr bool a_first = false;
   static constexpr bool serpentine = false;
   static constexpr bool round_sync = false;
 };
 template <>
 struct CopySched<EpiLseCols> {
   static constexpr int spacing = 8;
-  static constexpr bool a_first = false;
   static constexpr bool serpentine = false;
   static constexpr bool round_sync = false;
 };
 template <>
 struct CopySched<EpiStore> {
   static constexpr int spacing = 8;
-  static constexpr bool a_first = false;
   static constexpr bool serpentine = true;
   static constexpr bool round_sync = true;
 };
@@ -749,7 +745,7 @@ __global__ void __launch_bounds__(GEMM_THREADS)
         for (int q = 0; q < NCOPY; ++q) copy_q(0, q, P0{});
 #pragma unroll
         for (int q = 0; q < NCOPY; ++q)
-          copy_q(1, CopySched<Epi>::a_first ? q : copy_order(q), P1{});
+          copy_q(1, copy_order(q), P1{});
         wait_vmcnt<NCOPY>();        // stage 0 landed (stage pairs: nk >= 2)
         __builtin_amdgcn_s_barrier();
         // stage 0's fragments
@@ -772,7 +768,6 @@ __global__ void __launch_bounds__(GEMM_THREADS)
           constexpr int CS = CopySched<Epi>::spacing;
           constexpr bool SPLIT = TR;
           static_assert(mf16_schedule_ok<CS, SPLIT>(), "16 x 16 slot schedule");
-          static_assert(!SPLIT || !CopySched<Epi>::a_first, "B's copies go first");
           const int kc = min(kt + 2, nk - 1);                  // stage to copy
           // every wave has read its fragments of this stage's buffer, which the
           // copies below refill
@@ -805,7 +800,7 @@ __global__ void __launch_bounds__(GEMM_THREADS)
                                                                 Epi::SWAP ? a : b, acc[i][j], 0, 0, 0);
             if constexpr (op >= MF16_COPY && op < MF16_COPY + 16) {
               constexpr int c = op - MF16_COPY;
-              copy_q(kc, CopySched<Epi>::a_first ? c : copy_order(c), PC{});
+              copy_q(kc, copy_order(c), PC{});
             } else if constexpr (op >= MF16_BREAD && op < MF16_BREAD + 16) {
               constexpr int n = op - MF16_BREAD;
               fb[P ^ 1][n >> 1][n & 1] = rd_b(n >> 1, n & 1, P ^ 1);
@@ -860,12 +855,12 @@ __global__ void __launch_bounds__(GEMM_THREADS)
 // Epilogues.  Each receives the finished accumulators of one tile.
 
 // Forward partial log-sum-exp on a transposed tile: rows are vocabulary
-// entries (A = W), columns are compacted tokens (B = H_act).  The accumulator
-// layout gives every lane 64 rows of each of its 4 token columns, so the
-// reduction over the tile's vocabulary is lane-local except for one exchange
-// between lanes l and l ^ 32 (the two 4-row halves) and one merge of the two
-// row waves through LDS: (max, sum exp) per token and vocabulary tile, and the
-// target logit.
+// entries (A = W), columns are compacted tokens (B = H_act).  Lane l holds 8 token
+// columns (16 j + (l & 15)) and 32 vocabulary rows of each (16 i + 4 (l >> 4) + r);
+// the other 96 rows of the wave's half sit in lanes l ^ 16, l ^ 32, l ^ 48.  So the
+// reduction over the tile's vocabulary is lane-local except for two exchanges and one
+// merge of the two row waves through LDS: (max, sum exp) per token and vocabulary
+// tile, and the target logit.
 struct EpiLseCols {
   static constexpr bool SWAP = false;
   const int32_t* y;      // [tokens] target id of each compacted row
@@ -874,9 +869,6 @@ struct EpiLseCols {
   float* zy;             // [tokens] logit of the target token
   float scale;           // 1 / temperature
 
-  // The same on the 16 x 16 accumulator layout: lane l holds 8 token columns
-  // (16 j + (l & 15)) and 32 vocabulary rows of each (16 i + 4 (l >> 4) + r),
-  // the other 96 rows of the wave's half sit in lanes l ^ 16, l ^ 32, l ^ 48.
   template <bool FULL>
   __device__ __forceinline__ void cols16(const f32x4 (&acc)[8][8], int m0, int n0, int M,
                                          const int* sy, f32x2* red, int wm, int wn,
@@ -989,8 +981,7 @@ struct EpiLogitGrad {
     ((float*)(smem + EPI_META + 2048))[tid] = live ? gs[m0 + tid] : 0.0f;
   }
 
-  // 16 x 16 swapped accumulators: pass h takes blocks i = 4 h .. 4 h + 3 of both
-  // wave rows (the same tile rows as the 32 x 32 layout's pass h); lane l holds
+  // Swapped accumulators: pass h takes blocks i = 4 h .. 4 h + 3 of both wave rows; lane l holds
   // columns 16 j + 4 (l >> 4) .. + 3 of row 16 i + (l & 15): its token's values are
   // read once per block row and four entries of G leave as one 8-byte LDS write (four
   // 2-byte writes before: 11830 -> 11750 us per 76032-column chunk at d = 5120, 22793

@@ -12,7 +12,7 @@
 //             exchange.  Forward (log-sum-exp partials) and recompute (G) run the
 //             same loop, so the backward's logits are the forward's to the bit.
 //   gradients dH = G W (K = vocabulary) and dW = G^T H_act (K = tokens) in one
-//             launch, tile 64 BI x 64 BJ, K split so that every part is a fraction
+//             launch, tile 64 x 64, K split so that every part is a fraction
 //             of a compute unit's share; parts go to fp32 partial buffers that one
 //             more kernel adds in a fixed order.
 //
@@ -322,17 +322,18 @@ struct GradArgs {
 // 816 us at V = 16391, d = 1024, 1333 tokens, where dW's 4112 tiles need no split.)
 constexpr int PARTS = 4;
 constexpr int MIN_STAGES = 12;
+constexpr int GT = 64;                 // rows and columns of a tile
 struct Split {
   int tiles_d, th, tw;     // column tiles; tiles of dH and dW
   int kh, kw;              // stages
   int sh, sw;              // splits
 };
-__host__ __device__ inline Split grad_split(int n_act, int nv, int d, int tm, int tn, int cus,
-                                            int ph_max, int pw_max) {
+__host__ __device__ inline Split grad_split(int n_act, int nv, int d, int cus, int ph_max,
+                                            int pw_max) {
   Split s;
-  s.tiles_d = cdiv(d, tn);
-  s.th = cdiv(n_act, tm) * s.tiles_d;
-  s.tw = cdiv(nv, tm) * s.tiles_d;
+  s.tiles_d = cdiv(d, GT);
+  s.th = cdiv(n_act, GT) * s.tiles_d;
+  s.tw = cdiv(nv, GT) * s.tiles_d;
   s.kh = cdiv(nv, SK);
   s.kw = cdiv(n_act, SK);
   const int64_t work = (int64_t)s.th * s.kh + (int64_t)s.tw * s.kw;
@@ -347,29 +348,23 @@ __host__ __device__ inline Split grad_split(int n_act, int nv, int d, int tm, in
 
 // Items <= tiles + work / most, and most is PARTS' share rounded down (>= 12: by at
 // most a twelfth); each product's blocks are a multiple of 8.
-__host__ inline int max_blocks(int rows, int nv, int d, int tm, int tn, int cus) {
-  const int64_t tiles = (int64_t)(cdiv(rows, tm) + cdiv(nv, tm)) * cdiv(d, tn);
+__host__ inline int max_blocks(int rows, int nv, int d, int cus) {
+  const int64_t tiles = (int64_t)(cdiv(rows, GT) + cdiv(nv, GT)) * cdiv(d, GT);
   return (int)(tiles + cus * PARTS * 13 / 12 + 16);
 }
 
-template <int BI, int BJ>
-__device__ __forceinline__ void store_tile(const f32x16 (&acc)[BI][BJ], float* out, int64_t ld,
+__device__ __forceinline__ void store_tile(const f32x16 (&acc)[1][1], float* out, int64_t ld,
                                            const int32_t* row_map, bool add, int m0, int M, int n0,
                                            int N, int wm, int wn, int lane) {
+  const int c = n0 + wn * 32 + (lane & 31);
 #pragma unroll
-  for (int i = 0; i < BI; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = m0 + (wm * BI + i) * 32 + acc_r(r, lane);
-      if (row < M) {
-        float* dst = out + (int64_t)(row_map ? row_map[row] : row) * ld;
-#pragma unroll
-        for (int j = 0; j < BJ; ++j) {
-          const int c = n0 + (wn * BJ + j) * 32 + (lane & 31);
-          if (c < N) dst[c] = add ? dst[c] + acc[i][j][r] : acc[i][j][r];
-        }
-      }
+  for (int r = 0; r < 16; ++r) {
+    const int row = m0 + wm * 32 + acc_r(r, lane);
+    if (row < M) {
+      float* dst = out + (int64_t)(row_map ? row_map[row] : row) * ld;
+      if (c < N) dst[c] = add ? dst[c] + acc[0][0][r] : acc[0][0][r];
     }
+  }
 }
 
 // 64 x 64 tiles, five workgroups per compute unit: 74 us at V = 4096, d = 256, 1519
@@ -377,33 +372,31 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[BI][BJ], float* o
 // of the 151 a large fp32 library product reaches); 256 x 256 tiles over the whole K
 // and transposed copies took 1352 and 4614 us, with 6 and 24 workgroups for dH.
 // 128 x 64, 64 x 128 and 128 x 128 tiles are within 6% of it at both sizes.
-template <int BI, int BJ>
 __global__ __launch_bounds__(THREADS, 2) void f32_grad_kernel(GradArgs g) {
-  constexpr int TM = 64 * BI, TN = 64 * BJ;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[2 * (TM + TN) * ROW];
+  __shared__ __attribute__((aligned(16))) uint8_t smem[2 * (GT + GT) * ROW];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_act = __builtin_amdgcn_readfirstlane(*g.n_act);
-  const Split s = grad_split(n_act, g.nv, g.d, TM, TN, g.cus, g.ph_max, g.pw_max);
+  const Split s = grad_split(n_act, g.nv, g.d, g.cus, g.ph_max, g.pw_max);
   // dH's items first, each product's spread over all XCDs
   const int items_h = s.th * s.sh, items_w = s.tw * s.sw, blocks_h = 8 * cdiv(items_h, 8);
   const bool is_h = (int)blockIdx.x < blocks_h;
   int t = is_h ? xcd_item(blockIdx.x, items_h) : xcd_item(blockIdx.x - blocks_h, items_w);
   if (t >= (is_h ? items_h : items_w)) return;
-  f32x16 acc[BI][BJ];
+  f32x16 acc[1][1];
   clear(acc);
   const int wm = wave >> 1, wn = wave & 1;
   if (is_h) {
     // dH: rows tokens, K = the chunk's vocabulary
     const int part = t / s.th;
     t -= part * s.th;
-    const int m0 = (t / s.tiles_d) * TM, n0 = (t % s.tiles_d) * TN;
+    const int m0 = (t / s.tiles_d) * GT, n0 = (t % s.tiles_d) * GT;
     const int per = cdiv(s.kh, s.sh), k0 = part * per, k1 = min(s.kh, k0 + per);
-    Tile<TM, false> A;
-    Tile<TN, true> B;
+    Tile<GT, false> A;
+    Tile<GT, true> B;
     A.init(g.G + (int64_t)m0 * g.ldg, g.ldg, n_act - m0, wave, lane);
     B.init(g.W + n0, g.d, g.d - n0, wave, lane);
-    main_loop<2, 2, BI, BJ>(acc, smem, A, B, k0, k1, g.nv - 1, wave, lane);
+    main_loop<2, 2, 1, 1>(acc, smem, A, B, k0, k1, g.nv - 1, wave, lane);
     if (s.sh > 1)
       store_tile(acc, g.ph + (int64_t)part * g.ph_rows * g.d, g.d, nullptr, false, m0, n_act, n0,
                  g.d, wm, wn, lane);
@@ -413,13 +406,13 @@ __global__ __launch_bounds__(THREADS, 2) void f32_grad_kernel(GradArgs g) {
     // dW: rows vocabulary, K = tokens
     const int part = t / s.tw;
     t -= part * s.tw;
-    const int m0 = (t / s.tiles_d) * TM, n0 = (t % s.tiles_d) * TN;
+    const int m0 = (t / s.tiles_d) * GT, n0 = (t % s.tiles_d) * GT;
     const int per = cdiv(s.kw, s.sw), k0 = part * per, k1 = min(s.kw, k0 + per);
-    Tile<TM, true> A;
-    Tile<TN, true> B;
+    Tile<GT, true> A;
+    Tile<GT, true> B;
     A.init(g.G + m0, g.ldg, (int)g.ldg - m0, wave, lane);
     B.init(g.H + n0, g.d, g.d - n0, wave, lane);
-    main_loop<2, 2, BI, BJ>(acc, smem, A, B, k0, k1, 1 << 30, wave, lane);
+    main_loop<2, 2, 1, 1>(acc, smem, A, B, k0, k1, 1 << 30, wave, lane);
     if (s.sw > 1)
       store_tile(acc, g.pw + (int64_t)part * g.nv * g.d, g.d, nullptr, false, m0, g.nv, n0, g.d,
                  wm, wn, lane);
@@ -429,9 +422,9 @@ __global__ __launch_bounds__(THREADS, 2) void f32_grad_kernel(GradArgs g) {
 }
 
 // The split products' parts, added in ascending order: dH rows go to their tokens.
-__global__ __launch_bounds__(THREADS) void f32_reduce_kernel(GradArgs g, int tm, int tn) {
+__global__ __launch_bounds__(THREADS) void f32_reduce_kernel(GradArgs g) {
   const int n_act = *g.n_act;
-  const Split s = grad_split(n_act, g.nv, g.d, tm, tn, g.cus, g.ph_max, g.pw_max);
+  const Split s = grad_split(n_act, g.nv, g.d, g.cus, g.ph_max, g.pw_max);
   const int64_t c4 = g.d / 4;
   const int64_t nh = s.sh > 1 ? n_act * c4 : 0, nw = s.sw > 1 ? g.nv * c4 : 0;
   for (int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x; i < nh + nw;

@@ -564,8 +564,9 @@ struct Layout {
 
 constexpr int64_t kDefaultChunkBytes = (int64_t)4 << 30;
 
-// Up to this many (padded) action tokens dH reads W as it lies, transposing in the LDS
-// read, instead of a W^T built first.  The transpose costs a pass over W whatever the
+// Up to a bound of this many (padded) action tokens dH reads W as it lies, transposing in the
+// LDS read, instead of a W^T built first.  (The bound, not the tokens there are: it sizes the
+// parts' buffers, in W^T's place, which must hold one part: about V_pad >= 2 A_pad.)  The transpose costs a pass over W whatever the
 // tokens, the transposing reads a share of dH's time.  Backward products and transpose,
 // W^T against W (V = 152064): 7.33 against 6.53 ms at d = 5120 and 2871 tokens, 15.70
 // against 15.57 ms at d = 3584 and 10515, 45.0 against 45.8 ms at d = 5120 and 22793.
@@ -975,16 +976,13 @@ void bwd_gemms_f32(const Common& c, const Layout& L, uint8_t* ws, const void* W,
     a.pw_max = L.pw_max;
     a.cus = cus;
     record(c.o, 2 * PH_DW, s);
-    constexpr int BI = 1, BJ = 1, TM = 64 * BI, TN = 64 * BJ;   // see f32_grad_kernel
-    hipLaunchKernelGGL((f32k::f32_grad_kernel<BI, BJ>),
-                       dim3(f32k::max_blocks((int)L.A_pad, nv, c.d, TM, TN, cus)),
+    hipLaunchKernelGGL(f32k::f32_grad_kernel, dim3(f32k::max_blocks((int)L.A_pad, nv, c.d, cus)),
                        dim3(f32k::THREADS), 0, s, a);
     record(c.o, 2 * PH_DW + 1, s);
     record(c.o, 2 * PH_DH, s);
     record(c.o, 2 * PH_DH + 1, s);
     if (L.ph_max > 1 || L.pw_max > 1)
-      hipLaunchKernelGGL(f32k::f32_reduce_kernel, dim3(4 * cus), dim3(f32k::THREADS), 0, s, a, TM,
-                         TN);
+      hipLaunchKernelGGL(f32k::f32_reduce_kernel, dim3(4 * cus), dim3(f32k::THREADS), 0, s, a);
   }
 }
 
