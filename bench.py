@@ -34,7 +34,7 @@ PEAK_BF16 = 2.5e15          # MI355X dense bf16 matrix-core peak, FLOP/s
 PEAK_F32 = 157.3e12
 HBM_PEAK = 8.0e12
 METRIC = "policy-loss fwd+bwd tokens/s and % of bf16 MFMA peak, 1 MI355X"
-PHASES = ["forward logits + lse", "backward logit recompute -> G", "dW = G^T H and dH = G W (one launch)", "dH = G W (separate launch)"]
+PHASES = ["forward logits + lse", "backward logit recompute -> G", "dW = G^T H and dH = G W (one launch)"]
 
 
 class HipEvents:
@@ -371,24 +371,22 @@ def main():
     nv_last = V - (n_chunks - 1) * vc
     chunk_flops = 2.0 * n_act * nv_last * d
     phase_ms = [float(np.mean([events.elapsed_ms(8 * i + 2 * p, 8 * i + 2 * p + 1)
-                               for i in range(Wm, Wm + K)])) for p in range(4)]
+                               for i in range(Wm, Wm + K)])) for p in range(3)]
     peak = PEAK_BF16 if code == P.AGRL_BF16 else PEAK_F32
-    # products per bracketed launch: dW and dH share one launch when phase 3 is empty
-    grouped = phase_ms[3] < 0.05          # an empty event pair reads a few microseconds
-    prods = [1, 1, 2 if grouped else 1, 0 if grouped else 1]
-    per_launch = [gemm_flops] + [chunk_flops * n for n in prods[1:]]
+    # products per bracketed launch: dW and dH share one
+    per_launch = [gemm_flops, chunk_flops, 2 * chunk_flops]
     rates = [f / (ms_ * 1e-3) if f > 0 else 0.0 for f, ms_ in zip(per_launch, phase_ms)]
     # the dominant kernel: most time per step (launch time x launches per step)
-    per_step = [phase_ms[0], phase_ms[1] * n_chunks, phase_ms[2] * n_chunks, phase_ms[3] * n_chunks]
+    per_step = [phase_ms[0], phase_ms[1] * n_chunks, phase_ms[2] * n_chunks]
     dom = int(np.argmax(per_step))
     achieved = per_launch[dom] / (phase_ms[dom] * 1e-3)
-    kernel_names = ["gemm_bf16_kernel<EpiLseCols>", "gemm_bf16_kernel<EpiLogitGrad>",
-                    "gemm_bf16_kernel<EpiStore>", "gemm_bf16_kernel<EpiStore>"]
-    if code != P.AGRL_BF16:
-        kernel_names = ["f32_logits_kernel<forward>", "f32_logits_kernel<G>", "f32_grad_kernel",
-                        "f32_grad_kernel"]
+    if code == P.AGRL_BF16:      # (the last: dH out of W as it lies, with few action tokens)
+        kernel_names = ["gemm_bf16_kernel<EpiLseCols>", "gemm_bf16_kernel<EpiLogitGrad>",
+                        "gemm_bf16_kernel<EpiGrad>" if n_act <= 8192 else "gemm_bf16_kernel<EpiStore>"]
+    else:
+        kernel_names = ["f32_logits_kernel<forward>", "f32_logits_kernel<G>", "f32_grad_kernel"]
     dom_kernel = kernel_names[dom]
-    rec = committed_traffic(w.spec.name, dom_kernel + (" grouped" if grouped and dom == 2 else ""))
+    rec = committed_traffic(w.spec.name, dom_kernel + (" grouped" if dom == 2 else ""))
     step_flops = 4 * gemm_flops
     log("phases (ms): " + ", ".join(f"{n}: {m:.3f}" for n, m in zip(PHASES, phase_ms)))
 
@@ -420,11 +418,9 @@ def main():
         "logprob_pass": {"ms": lp_ms, "tokens_per_s": T / (lp_ms * 1e-3),
                          "mfma_frac": 2.0 * n_act * V * d / (lp_ms * 1e-3) / (
                              PEAK_BF16 if code == P.AGRL_BF16 else PEAK_F32)},
-        "gemm_launches_per_step": {"fwd": 1, "recompute": n_chunks,
-                                   "dW+dH" if grouped else "dW": n_chunks},
-        "gemm_ms": dict(zip(["fwd", "recompute", "dW+dH" if grouped else "dW", "dH"], phase_ms)),
-        "gemm_tflops": dict(zip(["fwd", "recompute", "dW+dH" if grouped else "dW", "dH"],
-                                [r / 1e12 for r in rates])),
+        "gemm_launches_per_step": {"fwd": 1, "recompute": n_chunks, "dW+dH": n_chunks},
+        "gemm_ms": dict(zip(["fwd", "recompute", "dW+dH"], phase_ms)),
+        "gemm_tflops": dict(zip(["fwd", "recompute", "dW+dH"], [r / 1e12 for r in rates])),
         "roofline": {"kernel": f"{dom_kernel} ({PHASES[dom]})", "bound": "mfma",
                      "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
                      "frac": achieved / peak,

@@ -43,10 +43,13 @@
  *     are unaffected.  With more action tokens than max_act the loss is NaN
  *     and the other outputs are unspecified.
  *   - A NaN or +inf logit makes its token's logp and lse non-finite and the
- *     loss NaN (a NaN old_logp on an action token the loss); a -inf logit
- *     carries no weight.
+ *     loss NaN; a -inf logit carries no weight.  A NaN old_logp on an action
+ *     token makes the loss NaN.
  *   - Results are deterministic: every reduction has a fixed order, no
- *     floating-point atomics are used.
+ *     floating-point atomics are used.  A repeated call keeps its bits.  The
+ *     order of the sums of dH and dW may depend on the sizes, on max_act and
+ *     g_chunk_bytes, on the number of action tokens and on the device's compute
+ *     units: another bound or a partitioned device may change their last bits.
  */
 #ifndef AGRL_H
 #define AGRL_H

@@ -55,3 +55,23 @@ def test_non_finite_logits(dtype, plant, n_act):
         else:
             assert not torch.isfinite(lse[act]).any() and not torch.isfinite(logp[act]).any()
     assert bool(torch.isfinite(loss).all()) == finite
+
+
+def test_nan_old_logp():
+    import paper_2510_04206_amd as P
+    T, V, d = 300, 500, 64
+    log("NaN behaviour log-prob on one action token")
+    g = torch.Generator(device="cuda").manual_seed(1)
+    H = torch.randn((T, d), generator=g, device="cuda").bfloat16()
+    W = torch.randn((V, d), generator=g, device="cuda").bfloat16()
+    y = torch.randint(0, V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    mask = (torch.arange(T, device="cuda") % 3 == 0).to(torch.uint8)
+    adv, old = torch.randn(T, generator=g, device="cuda"), torch.full((T,), -6.0, device="cuda")
+    pl = P.PolicyLoss(T, d, V, H.dtype)
+    old[100] = float("nan")                      # not an action token: never read
+    assert pl.forward(H, W, y, mask, adv, old)[0].isfinite().item()
+    old[99] = float("nan")
+    loss, logp, lse, _ = pl.forward(H, W, y, mask, adv, old)
+    assert loss.isnan().item() and logp.isfinite().all() and lse.isfinite().all()
+    dH, _ = pl.backward(H, W, y, mask, adv, old)
+    assert dH[99].isnan().all() and dH[102].isfinite().all()
