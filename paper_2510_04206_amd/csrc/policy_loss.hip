@@ -394,11 +394,15 @@ __device__ __forceinline__ float mass(float sum, float at, float to) {
 // kernel is their latency: at V = 152064, with 4 waves and one load at a time, 74 us at 150
 // tokens and 86 at 22793; now 14 and 41); wave 0
 // combines them, then forms logp, rho and the clipped surrogate and writes the block's
-// fixed-order partial sums.  The block that finishes last adds those in block order.
+// fixed-order partial sums.  The block that finishes last adds those in block order; blocks
+// past the last action token leave at once (a bound of 281575 tokens launches 4400: counting
+// themselves finished took them 106 us, 7 now).
 __global__ __launch_bounds__(64 * kMergeWaves) void merge_loss_kernel(MergeArgs a) {
   constexpr int U = 8;
   __shared__ f32x2 wpart[kMergeWaves][kMergeRows];
   const int n_act = a.ctrl[CTRL_N];
+  const int blocks = max(1, cdiv(n_act, kMergeRows));
+  if ((int)blockIdx.x >= blocks) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = blockIdx.x * kMergeRows + lane;
   float m = -INFINITY, s = 0.0f;
@@ -470,11 +474,11 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_loss_kernel(MergeArgs 
     done = __hip_atomic_fetch_add(a.ctrl + CTRL_MERGED, 1, __ATOMIC_ACQ_REL,
                                   __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (__shfl(done, 0) != (int)gridDim.x - 1) return;
+  if (__shfl(done, 0) != blocks - 1) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   sv = 0.0;
   hi = lo = 0;
-  for (int b = lane; b < (int)gridDim.x; b += 64) {
+  for (int b = lane; b < blocks; b += 64) {
     sv += __builtin_bit_cast(double, __hip_atomic_load(sums + b, __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_AGENT));
     hi += (long long)__hip_atomic_load(a.blk_clip + 2 * b, __ATOMIC_RELAXED,
