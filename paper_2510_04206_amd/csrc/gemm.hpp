@@ -380,10 +380,13 @@ __host__ __device__ inline int dh_split(int n_act, int nv, int d, int cus, int m
 // Stages run in pairs, so that which LDS buffer a stage reads and refills is known at
 // compile time and every LDS address of the loop is a base register plus an immediate.
 // ODD: K is an odd number of stages (a hidden size that is no multiple of 128; forward
-// and recompute only): the first stage runs before the pairs, unpipelined.  At 17 stages
-// (d = 1088, V = 131001, 2122 tokens) the forward takes 635 us and the recompute 240 us per
-// 43776 columns, against 680 and 272 us (same box) in a loop on 32 x 32 blocks that chose
-// its buffer at run time.  ATR: a problem may read A transposed (GemmShape::a_trans).
+// and recompute only): the first stage runs before the pairs, slice by slice, so that its
+// second slice and the next stage's fragments are read under MFMAs.  The forward of 29440
+// tokens on 157952 entries at 3 stages takes 3125 us, with the first stage's reads and the
+// next's in the open 3387, in a loop on 32 x 32 blocks that chose its buffer at run time
+// 3089; at 17 stages (d = 1088, V = 131001, 2122 tokens) 549 us, 560 and 582, and the
+// recompute per 43776 columns 213 us against 218 (and 272, on a slower box where the second
+// took 240).  ATR: a problem may read A transposed (GemmShape::a_trans).
 template <class Epi, bool ATR, bool ODD = false>
 __global__ void __launch_bounds__(GEMM_THREADS)
     __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_bf16_kernel(GemmBatch<Epi> bat) {
@@ -708,8 +711,12 @@ __global__ void __launch_bounds__(GEMM_THREADS)
         };
         using P0 = std::integral_constant<int, 0>;
         using P1 = std::integral_constant<int, 1>;
+        bf16x8 fa[8][2], fa7[2], fb[2][8][2];
         if constexpr (ODD) {
-          // the first stage through buffer 1, the copies of the next behind it
+          // The first stage, through buffer 1, slice by slice: under the first slice's MFMAs
+          // the second slice's fragments are read, under the second's the fragments of the
+          // next stage, which went through buffer 0, and the copies of the one after it (a
+          // single stage is copied in place of either and read for nothing).
 #pragma unroll
           for (int q = 0; q < NCOPY; ++q) copy_q(0, q, P1{});
           const int more = nk > 1 ? 1 : 0;
@@ -720,43 +727,56 @@ __global__ void __launch_bounds__(GEMM_THREADS)
           for (int q = 0; q < NCOPY; ++q) copy_q(0, q, P0{});
           wait_vmcnt<NCOPY>();
           __builtin_amdgcn_s_barrier();
-          static_for<2>([&](auto kk_c) {
-            constexpr int kk = decltype(kk_c)::value;
-            bf16x8 b[8];
-            static_for<8>([&](auto j_c) { b[j_c.value] = rd_b(j_c.value, kk, 1); });
-            static_for<8>([&](auto i_c) {
-              constexpr int i = decltype(i_c)::value;
-              const bf16x8 a = rd_a(i, kk, 1);
-              static_for<8>([&](auto j_c) {
-                constexpr int j = decltype(j_c)::value;
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    Epi::SWAP ? b[j] : a, Epi::SWAP ? a : b[j], acc[i][j], 0, 0, 0);
-              });
-            });
+          bf16x8 a[2][8], b[2][8];
+          a[0][0] = rd_a(0, 0, 1);
+          static_for<8>([&](auto j_c) { b[0][j_c.value] = rd_b(j_c.value, 0, 1); });
+          static_for<7>([&](auto i_c) { a[0][i_c.value + 1] = rd_a(i_c.value + 1, 0, 1); });
+          __builtin_amdgcn_sched_barrier(0);
+          static_for<128>([&](auto q_c) {
+            constexpr int kk = q_c.value >> 6, q = q_c.value & 63, i = q >> 3, j = q & 7;
+            if constexpr (kk == 1 && q == 0) {
+              // buffer 1 is in registers, buffer 0 has landed, in every wave
+              asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                Epi::SWAP ? b[kk][j] : a[kk][i], Epi::SWAP ? a[kk][i] : b[kk][j], acc[i][j], 0, 0, 0);
+            if constexpr (kk == 0 && q % 4 == 1) {
+              constexpr int n = q >> 2;
+              if constexpr (n < 8)
+                b[1][n] = rd_b(n, 1, 1);
+              else
+                a[1][n - 8] = rd_a(n - 8, 1, 1);
+            }
+            if constexpr (kk == 1 && q % 4 == 0) copy_q(more, copy_order(q >> 2), P1{});
+            if constexpr (kk == 1 && q % 2 == 1) {
+              constexpr int n = q >> 1, r = (n >> 1) & 7, k = n & 1;
+              if constexpr (n < 16)
+                fb[0][r][k] = rd_b(r, k, 0);
+              else
+                fa[r][k] = rd_a(r, k, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
           });
-          // every wave is done with buffer 1
-          asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
           if (nk == 0) return;
+        } else {
+          // stages 0 and 1 whole (stage 1 in the loop's copy order, which the
+          // first stage's waits assume)
+#pragma unroll
+          for (int q = 0; q < NCOPY; ++q) copy_q(0, q, P0{});
+#pragma unroll
+          for (int q = 0; q < NCOPY; ++q) copy_q(1, copy_order(q), P1{});
+          wait_vmcnt<NCOPY>();        // stage 0 landed (stage pairs: nk >= 2)
+          __builtin_amdgcn_s_barrier();
+          // stage 0's fragments
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+              fa[i][kk] = rd_a(i, kk, 0);
+              fb[0][i][kk] = rd_b(i, kk, 0);
+            }
         }
-        // stages 0 and 1 whole (stage 1 in the loop's copy order, which the
-        // first stage's waits assume)
-        if constexpr (!ODD)
-#pragma unroll
-        for (int q = 0; q < NCOPY; ++q) copy_q(0, q, P0{});
-#pragma unroll
-        for (int q = 0; q < NCOPY; ++q)
-          copy_q(1, copy_order(q), P1{});
-        wait_vmcnt<NCOPY>();        // stage 0 landed (stage pairs: nk >= 2)
-        __builtin_amdgcn_s_barrier();
-        // stage 0's fragments
-        bf16x8 fa[8][2], fa7[2], fb[2][8][2];
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int kk = 0; kk < 2; ++kk) {
-            fa[i][kk] = rd_a(i, kk, 0);
-            fb[0][i][kk] = rd_b(i, kk, 0);
-          }
         // Every stage runs the same code (one register assignment for the whole
         // loop): the last two stages copy the last stage again into the buffer
         // they free (its data is in registers already, nothing reads it again),

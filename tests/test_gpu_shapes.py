@@ -195,8 +195,8 @@ def test_compaction(T, offset):
     assert ((dH[act].double() - ref).norm() / ref.norm()) < 4e-3
 
 
-# bf16, a hidden size that is an odd number of 64-deep stages: one stage, three, seventeen
-@pytest.mark.parametrize("V,d,n_act", [(700, 64, 300), (513, 192, 257), (1000, 1088, 40)])
+# bf16, a hidden size that is an odd number of 64-deep stages: one stage, three, five, seventeen
+@pytest.mark.parametrize("V,d,n_act", [(700, 64, 300), (513, 192, 257), (900, 320, 300), (1000, 1088, 40)])
 def test_bf16_odd_stages(V, d, n_act):
     _case(torch.bfloat16, V, d, n_act)
 
