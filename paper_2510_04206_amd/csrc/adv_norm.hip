@@ -436,7 +436,7 @@ constexpr int64_t kSmallTokens = 32768;
 // 21.6 (11.1 and 22.3), 512 segments 24.2 and 30.3 (19.1 and 30.6); one trajectory and
 // 65535 tasks 2441 against 25.
 __host__ inline bool stages_are_short(int64_t T, int32_t n_traj, int32_t n_group, int32_t n_task) {
-  const int64_t turns = (int64_t)cdiv(n_group, 16) + cdiv(n_task, 16);
+  const int64_t turns = cdiv<int64_t>(n_group, 16) + cdiv<int64_t>(n_task, 16);
   const int64_t merged = T > 0 ? (int64_t)1024 * n_traj / T : 0;   // trajectories in a wave's tokens
   return turns * (5 + 8 * cdiv(n_traj, 64)) <= 155 + n_traj / 2 + 5 * (merged < 64 ? merged : 64);
 }
